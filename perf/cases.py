@@ -107,8 +107,8 @@ def _plummer(n, g, dev, spectrum=False):
     f = (u - c[k - 1]) / (c[k] - c[k - 1])
     v = (q[k - 1] + f * (q[k] - q[k - 1]))[:, None] * math.sqrt(2.0) * (r * r + B * B)[:, None] ** -0.25 * unit(n)
     m = torch.full((n,), 1.0 / n, dtype=F64, device=dev)
-    if spectrum:   # dN/dm ~ m^-2.3 over two decades
-        m = (1.0 - torch.rand(n, generator=g, dtype=F64, device=dev) * (1.0 - 100.0 ** -1.3)) ** (-1.0 / 1.3)
+    if spectrum:   # dN/dm ~ m^-2.3 over one decade
+        m = (1.0 - torch.rand(n, generator=g, dtype=F64, device=dev) * (1.0 - 10.0 ** -1.3)) ** (-1.0 / 1.3)
         m = m / m.sum()
     x = x - (m[:, None] * x).sum(0)
     v = v - (m[:, None] * v).sum(0)
