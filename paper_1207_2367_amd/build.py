@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libnbody.so")
-SOURCES = ["force.hip", "integrate.hip", "capi.hip"]
+SOURCES = ["force.hip", "startup.hip", "integrate.hip", "capi.hip"]
 ARCH = os.environ.get("NBODY_OFFLOAD_ARCH", "gfx950")
 
 FLAGS = [

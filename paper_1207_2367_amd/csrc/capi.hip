@@ -433,43 +433,19 @@ int run_force(Ctx &c, const int32_t *idx, int64_t n_act, int64_t n_act_typ, cons
 // the two start-up passes over every particle (see nbody_init)
 int run_force_init(Ctx &c)
 {
-    hipStream_t s = c.stream;
-    const int64_t n = c.n;
-    HIPCHK(c, launch_segments(c, nullptr, n, s));
-    Launch L = pick_launch(c, c.nc == 1 ? n : std::max<int64_t>(1, n / c.nc), max_cluster(c));
-    L.split = 1;
-    L.ipt = 1;   // the start-up kernels take one particle per lane group
-    while (n * L.lpi < (int64_t(1) << 18) && L.lpi < 64)
-        L.lpi <<= 1;
-    const int64_t ib = iblock_size(L);
+    const StartupShape sh = startup_shape(c.n, c.nc, max_cluster(c), c.part_cap);
     ForceWork w{};
-    w.seg = c.d_seg;
     w.off = c.d_off;
-    w.split = 1;
+    w.split = sh.split;
     w.nc = c.nc;
-    if (c.nc == 1) {
-        w.n_blocks = (n + ib - 1) / ib;
-    } else {
-        const int64_t cap = n / ib + c.nc + 1;
-        HIPCHK(c, launch_blocks(c, ib, cap, s));
+    if (c.nc > 1) {
+        HIPCHK(c, launch_segments(c, nullptr, c.n, c.stream));
+        HIPCHK(c, launch_blocks(c, sh.ib, sh.n_blocks, c.stream));
         w.blk_cluster = c.d_blk_cluster;
         w.blk_first = c.d_blk_first;
-        w.n_blocks = cap;
     }
-    ForceOut o1{};
-    o1.vec[0] = c.fnew;
-    o1.vec[1] = c.fnew + 3 * n;
-    o1.sk = 1;
-    o1.sd = n;
-    HIPCHK(c, launch_force_init(c, w, L, o1, s));
-    HIPCHK(c, hipMemcpyAsync(c.st.acc, c.fnew, 3 * n * 8, hipMemcpyDeviceToDevice, s));
-    HIPCHK(c, hipMemcpyAsync(c.st.jrk, c.fnew + 3 * n, 3 * n * 8, hipMemcpyDeviceToDevice, s));
-    ForceOut o2{};
-    o2.vec[2] = c.st.snp;
-    o2.vec[3] = c.st.crk;
-    o2.sk = 1;
-    o2.sd = n;
-    HIPCHK(c, launch_force_init(c, w, L, o2, s));
+    HIPCHK(c, launch_startup(c, w, sh, 1, c.stream));
+    HIPCHK(c, launch_startup(c, w, sh, 2, c.stream));
     return NBODY_OK;
 }
 

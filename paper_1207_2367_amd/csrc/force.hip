@@ -447,25 +447,4 @@ hipError_t launch_energy_pot(Ctx &c, double *phi, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_force_init(Ctx &c, const ForceWork &w, const Launch &L,
-                             const ForceOut &out, hipStream_t s)
-{
-    if (w.n_blocks <= 0)
-        return hipSuccess;
-    JRecF64 J{};
-    J.x = c.st.pos; J.y = c.st.pos + c.n; J.z = c.st.pos + 2 * c.n;
-    J.vx = c.st.vel; J.vy = c.st.vel + c.n; J.vz = c.st.vel + 2 * c.n;
-    J.ax = c.st.acc; J.ay = c.st.acc + c.n; J.az = c.st.acc + 2 * c.n;
-    J.jx = c.st.jrk; J.jy = c.st.jrk + c.n; J.jz = c.st.jrk + 2 * c.n;
-    J.m = c.st.mass;
-    ForceWork w1 = w;
-    w1.split = 1;
-    const int lg = ilog2(L.lpi);
-    KF64 k = c.eps == 0.0 ? pick_kernel<PREC_INIT, true>(lg, L.waves)
-                          : pick_kernel<PREC_INIT, false>(lg, L.waves);
-    hipLaunchKernelGGL(k, dim3((unsigned)w1.n_blocks, 1), dim3(64 * L.waves), 0, s, J, w1, out,
-                       (double *)nullptr, (int64_t)0, c.eps * c.eps);
-    return hipGetLastError();
-}
-
 }  // namespace nb

@@ -9,9 +9,8 @@ namespace nb {
 
 namespace {
 
-// kernel variants: the two public mixed modes, the FP64 path and the
-// start-up pass
-constexpr int PREC_MIXED = 0, PREC_F64 = 1, PREC_INIT = 3, PREC_PAIR32 = 4;
+// kernel variants: the two public mixed modes and the FP64 path
+constexpr int PREC_MIXED = 0, PREC_F64 = 1, PREC_PAIR32 = 4;
 
 // Knuth's two-sum: (hi, lo) += p without rounding loss in the (hi, lo) pair.
 __device__ __forceinline__ void ds_add(float &hi, float &lo, float p)
@@ -39,10 +38,6 @@ struct Smem<PREC_PAIR32> {
 };
 template <>
 struct Smem<PREC_F64> {
-    using R = JRecF64;
-};
-template <>
-struct Smem<PREC_INIT> {
     using R = JRecF64;
 };
 
@@ -81,7 +76,6 @@ __device__ __forceinline__ double rinv_f64(double r2)
 template <int PREC, int NT>
 struct SrcTile {
     static constexpr bool P32 = PREC == PREC_PAIR32, MIXED = PREC == PREC_MIXED;
-    static constexpr int NJ = PREC == PREC_INIT ? NT : 1;
     using VV = typename std::conditional<P32, float, double>::type;
     using VA = typename std::conditional<MIXED || P32, float, double>::type;
     struct alignas(16) S {
@@ -90,7 +84,6 @@ struct SrcTile {
         VA ax, ay, az;
     };
     S s[NT];
-    double jx[NJ], jy[NJ], jz[NJ];   // sources' jerks: start-up evaluation only
 };
 
 template <int PREC, int NT>
@@ -104,7 +97,7 @@ __device__ __forceinline__ SrcTile<PREC, NT> &src_tile()
 // source split b.  The launch kernel calls it with (blockIdx.x, blockIdx.y);
 // the device-resident block-step loop calls it for the units it takes.
 // Every early return is uniform over the workgroup.  PHI: also sum the
-// potential (nbody_force, the start-up pass); a block step's evaluation
+// potential (nbody_force); a block step's evaluation
 // does not need it (the energy has its own pass).  IPT: active particles
 // per lane group (each source read from LDS serves IPT pairs).
 template <int PREC, int LPI, int NW, bool EPS0, bool PHI, int IPT = 1>
@@ -120,8 +113,7 @@ __device__ __forceinline__ void force_block(const typename Smem<PREC>::R &J, con
     constexpr int PER = NT / LPI;    // sources per lane per tile
     constexpr bool MIXED = PREC == PREC_MIXED;
     constexpr bool P32 = PREC == PREC_PAIR32;
-    constexpr bool INIT = PREC == PREC_INIT;
-    constexpr int NV = INIT ? 12 : 9;   // vector outputs (3 components each)
+    constexpr int NV = 9;            // vector outputs (a, da, d2a)
     // FP32 accumulators (mixed: snap; FP32-pair mode: all nine); FP64 ones
     // for the rest
     constexpr int NF = MIXED ? 3 : (P32 ? 9 : 1);
@@ -163,7 +155,6 @@ __device__ __forceinline__ void force_block(const typename Smem<PREC>::R &J, con
     double xi[IPT], yi[IPT], zi[IPT];
     VV vxi[IPT], vyi[IPT], vzi[IPT];
     VA axi[IPT], ayi[IPT], azi[IPT];
-    double jxi[IPT], jyi[IPT], jzi[IPT];
 #pragma unroll
     for (int u = 0; u < IPT; ++u) {
         k[u] = kb + il + u * NG;
@@ -181,10 +172,6 @@ __device__ __forceinline__ void force_block(const typename Smem<PREC>::R &J, con
         xi[u] = J.x[i[u]]; yi[u] = J.y[i[u]]; zi[u] = J.z[i[u]];
         vxi[u] = J.vx[i[u]]; vyi[u] = J.vy[i[u]]; vzi[u] = J.vz[i[u]];
         axi[u] = J.ax[i[u]]; ayi[u] = J.ay[i[u]]; azi[u] = J.az[i[u]];
-        jxi[u] = 0; jyi[u] = 0; jzi[u] = 0;
-        if constexpr (INIT) {
-            jxi[u] = J.jx[i[u]]; jyi[u] = J.jy[i[u]]; jzi[u] = J.jz[i[u]];
-        }
     }
 
     // FP64 sums (mixed: acceleration and jerk; FP64 passes: everything),
@@ -217,9 +204,6 @@ __device__ __forceinline__ void force_block(const typename Smem<PREC>::R &J, con
             tl.s[tid].m = J.m[jj];
             tl.s[tid].vx = J.vx[jj]; tl.s[tid].vy = J.vy[jj]; tl.s[tid].vz = J.vz[jj];
             tl.s[tid].ax = J.ax[jj]; tl.s[tid].ay = J.ay[jj]; tl.s[tid].az = J.az[jj];
-            if constexpr (INIT) {
-                tl.jx[tid] = J.jx[jj]; tl.jy[tid] = J.jy[jj]; tl.jz[tid] = J.jz[jj];
-            }
         } else {
             tl.s[tid].x = NULL_POS;
             tl.s[tid].y = NULL_POS;
@@ -227,9 +211,6 @@ __device__ __forceinline__ void force_block(const typename Smem<PREC>::R &J, con
             tl.s[tid].m = 0.0;
             tl.s[tid].vx = 0; tl.s[tid].vy = 0; tl.s[tid].vz = 0;
             tl.s[tid].ax = 0; tl.s[tid].ay = 0; tl.s[tid].az = 0;
-            if constexpr (INIT) {
-                tl.jx[tid] = 0; tl.jy[tid] = 0; tl.jz[tid] = 0;
-            }
         }
         __syncthreads();
 
@@ -341,40 +322,18 @@ __device__ __forceinline__ void force_block(const typename Smem<PREC>::R &J, con
                         const double qq = fma(dvx, dvx, fma(dvy, dvy, fma(dvz, dvz,
                                           fma(dxd, dax, fma(dyd, day, dzd * daz)))));
                         const double beta = fma(alpha, alpha, qq * rinv2);
-                        if constexpr (INIT) {
-                            // start-up evaluation with the crackle, term by term
-                            const double djx = tl.jx[t] - jxi[u], djy = tl.jy[t] - jyi[u],
-                                         djz = tl.jz[t] - jzi[u];
-                            const double gamma = (3.0 * (dvx * dax + dvy * day + dvz * daz) +
-                                                  dxd * djx + dyd * djy + dzd * djz) * rinv2 +
-                                                 alpha * (3.0 * beta - 4.0 * alpha * alpha);
-                            const double Ax = mr3 * dxd, Ay = mr3 * dyd, Az = mr3 * dzd;
-                            const double Jx = mr3 * dvx - 3.0 * alpha * Ax;
-                            const double Jy = mr3 * dvy - 3.0 * alpha * Ay;
-                            const double Jz = mr3 * dvz - 3.0 * alpha * Az;
-                            const double Sx = mr3 * dax - 6.0 * alpha * Jx - 3.0 * beta * Ax;
-                            const double Sy = mr3 * day - 6.0 * alpha * Jy - 3.0 * beta * Ay;
-                            const double Sz = mr3 * daz - 6.0 * alpha * Jz - 3.0 * beta * Az;
-                            Du[0] += Ax; Du[1] += Ay; Du[2] += Az;
-                            Du[3] += Jx; Du[4] += Jy; Du[5] += Jz;
-                            Du[6] += Sx; Du[7] += Sy; Du[8] += Sz;
-                            Du[ND - 3] += mr3 * djx - 9.0 * alpha * Sx - 9.0 * beta * Jx - 3.0 * gamma * Ax;
-                            Du[ND - 2] += mr3 * djy - 9.0 * alpha * Sy - 9.0 * beta * Jy - 3.0 * gamma * Ay;
-                            Du[ND - 1] += mr3 * djz - 9.0 * alpha * Sz - 9.0 * beta * Jz - 3.0 * gamma * Az;
-                        } else {
-                            const double a3 = -3.0 * alpha, a6 = a3 + a3, b3 = -3.0 * beta;
-                            const double jx = fma(a3, dxd, dvx), jy = fma(a3, dyd, dvy),
-                                         jz = fma(a3, dzd, dvz);
-                            Du[0] = fma(mr3, dxd, Du[0]);
-                            Du[1] = fma(mr3, dyd, Du[1]);
-                            Du[2] = fma(mr3, dzd, Du[2]);
-                            Du[3] = fma(mr3, jx, Du[3]);
-                            Du[4] = fma(mr3, jy, Du[4]);
-                            Du[5] = fma(mr3, jz, Du[5]);
-                            Du[6] = fma(mr3, fma(a6, jx, fma(b3, dxd, dax)), Du[6]);
-                            Du[7] = fma(mr3, fma(a6, jy, fma(b3, dyd, day)), Du[7]);
-                            Du[8] = fma(mr3, fma(a6, jz, fma(b3, dzd, daz)), Du[8]);
-                        }
+                        const double a3 = -3.0 * alpha, a6 = a3 + a3, b3 = -3.0 * beta;
+                        const double jx = fma(a3, dxd, dvx), jy = fma(a3, dyd, dvy),
+                                     jz = fma(a3, dzd, dvz);
+                        Du[0] = fma(mr3, dxd, Du[0]);
+                        Du[1] = fma(mr3, dyd, Du[1]);
+                        Du[2] = fma(mr3, dzd, Du[2]);
+                        Du[3] = fma(mr3, jx, Du[3]);
+                        Du[4] = fma(mr3, jy, Du[4]);
+                        Du[5] = fma(mr3, jz, Du[5]);
+                        Du[6] = fma(mr3, fma(a6, jx, fma(b3, dxd, dax)), Du[6]);
+                        Du[7] = fma(mr3, fma(a6, jy, fma(b3, dyd, day)), Du[7]);
+                        Du[8] = fma(mr3, fma(a6, jz, fma(b3, dzd, daz)), Du[8]);
                     }
                 }
             }
@@ -433,15 +392,6 @@ __device__ __forceinline__ void force_block(const typename Smem<PREC>::R &J, con
                     R[NV] += J.m[iu] * ri;
                 }
             }
-        }
-        if constexpr (INIT) {
-#pragma unroll
-            for (int q = 0; q < NV / 3; ++q)
-                if (out.vec[q])
-#pragma unroll
-                    for (int d = 0; d < 3; ++d)
-                        out.vec[q][ku * out.sk + d * out.sd] = R[3 * q + d];
-            continue;
         }
         if (part) {
             double *pb = part + (int64_t)b * 10 * n_act_total + ku;

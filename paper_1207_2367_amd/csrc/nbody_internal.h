@@ -31,7 +31,6 @@ using JRecMixed = JRecMix<double>;
 using JRecPair32 = JRecMix<float>;
 struct JRecF64 {
     double *x, *y, *z, *vx, *vy, *vz, *ax, *ay, *az, *m;
-    double *jx, *jy, *jz;   // sources' jerks: start-up evaluation only
 };
 
 // Hermite state, FP64 structure-of-arrays: component d of particle i of
@@ -42,11 +41,10 @@ struct State {
 };
 
 // Where a force evaluation writes: component d of output q (0 acc, 1 jrk,
-// 2 snp, 3 crackle -- start-up evaluation only) of active slot k goes to
-// vec[q][k * sk + d * sd]; the potential to pot[k].  A null vec[q] or pot
-// is not written.
+// 2 snp) of active slot k goes to vec[q][k * sk + d * sd]; the potential to
+// pot[k].  A null pot is not written.
 struct ForceOut {
-    double *vec[4];
+    double *vec[3];
     double *pot;
     int64_t sk, sd;
 };
@@ -119,12 +117,23 @@ hipError_t launch_reduce_correct(const Ctx &c, const ForceWork &w, int split, in
                                  bool levels = false);
 Launch pick_launch(const Ctx &c, int64_t n_act, int64_t n_src_max);
 Launch rule_launch(int64_t n_act, int64_t n_src, int64_t part_cap, int prec);
-// start-up evaluation (FP64, a, da, d2a and crackle of every particle from
-// the stored state): split = 1, results written straight to out
 hipError_t launch_energy_pot(Ctx &c, double *phi, hipStream_t s);
-hipError_t launch_force_init(Ctx &c, const ForceWork &w, const Launch &L,
-                             const ForceOut &out, hipStream_t s);
 int64_t iblock_size(const Launch &L);
+
+// startup.hip
+// shape of a start-up pass: lanes per particle, particles per workgroup,
+// i-blocks, source splits
+struct StartupShape {
+    int lpi = 1;
+    int64_t ib = 1, n_blocks = 1;
+    int32_t split = 1;
+};
+StartupShape startup_shape(int64_t n, int32_t nc, int64_t n_src, int64_t part_cap);
+// pass 1: acceleration and jerk of every particle from the stored positions
+// and velocities, into the stored state; pass 2: snap and crackle from those.
+// w.split = sh.split and, with several clusters, the i-block table for sh.ib.
+hipError_t launch_startup(Ctx &c, const ForceWork &w, const StartupShape &sh, int pass,
+                          hipStream_t s);
 
 // integrate.hip
 hipError_t launch_pack(const Ctx &c, const double *T_cluster, int own_time,

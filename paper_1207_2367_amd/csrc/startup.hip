@@ -1,0 +1,267 @@
+// Start-up evaluation of nbody_init on gfx950: acceleration and jerk of every
+// particle from positions and velocities (pass 1), then snap and crackle from
+// those (pass 2), both in FP64 from the stored state whatever the precision.
+//
+// Bound: FP64 vector issue (a wave's FP64 instruction takes ~4.4 cycles at a
+// clock of ~2.13 GHz under this load, measured), so the count of operations
+// per pair is what matters.  Each pass forms only what it returns, and every
+// pair term is a sum of a weight times a plain difference, so that the
+// constant factors are applied once per particle instead of once per pair:
+// with d, v, a, j the differences of position, velocity, acceleration and
+// jerk, rho = 1 / r^2, w = m / r^3, alpha = (d.v) rho, q = (v.v + d.a) rho,
+// t = (3 v.a + d.j) rho,
+//   a    = sum w d
+//   da   = sum w v - 3 sum w alpha d
+//   d2a  = sum w a - 6 sum w alpha v + 3 sum w kappa d
+//   d3a  = sum w j - 9 sum w alpha a + 9 sum w kappa v - 3 sum w lambda d
+// kappa = 5 alpha^2 - q, lambda = t + 5 alpha (7 alpha^2 - 3 q): the terms
+// A, J, S, C of the pairwise differentiation collected by difference.
+// 31 FP64 operations per pair in pass 1 and 72 in pass 2.  Measured at 65,536
+// bodies: pass 1 4.68 ms (918 G pairs/s), pass 2 10.3 ms (415 G pairs/s);
+// one kernel with all four terms written out took 14.3 ms in either pass.
+// With one particle per lane instead of two: 5.02 and 10.8 ms (each source's
+// LDS reads then serve one pair).
+#include "force_body.h"
+
+namespace nb {
+
+namespace {
+
+constexpr int SU_NT = 256;   // sources per LDS tile = lanes per workgroup
+
+// One source in LDS.  16-byte multiples whose word stride keeps neighbouring
+// lanes' 128-bit reads on different banks (20 and 28 words).
+template <int PASS>
+struct alignas(16) SuSrc {
+    double x, y, z, m, vx, vy, vz, pad[3];
+};
+template <>
+struct alignas(16) SuSrc<2> {
+    double x, y, z, m, vx, vy, vz, ax, ay, az, jx, jy, jz, pad;
+};
+
+// LPI lanes per particle, IPT particles per lane group; a workgroup takes
+// i-block blockIdx.x of its cluster against source split blockIdx.y.  Sums
+// go to out0 / out1 (components [3][n]) or, with part != nullptr, to
+// part[(b 6 + q) n + i].
+template <int PASS, int LPI, int IPT, bool EPS0>
+__global__ __launch_bounds__(SU_NT) void startup_kernel(State st, int64_t n, ForceWork w,
+                                                        double *out0, double *out1, double *part,
+                                                        double eps2)
+{
+    constexpr int GI = SU_NT / LPI;        // lane groups per workgroup
+    constexpr int IB = GI * IPT;           // particles per workgroup
+    constexpr int NA = PASS == 1 ? 9 : 21; // running sums
+    __shared__ SuSrc<PASS> tl[SU_NT];
+    const int64_t g = blockIdx.x;
+    const int b = blockIdx.y;
+    int64_t o0 = 0, o1 = n, gfirst = 0;
+    if (w.blk_cluster) {
+        const int c = w.blk_cluster[g];
+        if (c < 0)
+            return;   // grid padding past the last i-block
+        gfirst = w.blk_first[c];
+        o0 = w.off[c];
+        o1 = w.off[c + 1];
+    }
+    const int64_t chunk = split_chunk(o1 - o0, w.split, SU_NT);
+    if ((int64_t)b * chunk >= o1 - o0 && b > 0)
+        return;       // no sources left for this split
+    const int64_t j0 = o0 + (int64_t)b * chunk;
+    const int64_t j1 = j0 + chunk < o1 ? j0 + chunk : o1;
+    const double *X = st.pos, *Y = X + n, *Z = Y + n, *VX = st.vel, *VY = VX + n, *VZ = VY + n;
+    const double *AX = st.acc, *AY = AX + n, *AZ = AY + n, *JX = st.jrk, *JY = JX + n,
+                 *JZ = JY + n;
+
+    const int tid = threadIdx.x, il = tid / LPI, js = tid % LPI;
+    int64_t i[IPT];
+    double xi[IPT], yi[IPT], zi[IPT], vxi[IPT], vyi[IPT], vzi[IPT];
+    double axi[IPT], ayi[IPT], azi[IPT], jxi[IPT], jyi[IPT], jzi[IPT];
+    double S[IPT][NA];
+#pragma unroll
+    for (int u = 0; u < IPT; ++u) {
+        i[u] = o0 + (g - gfirst) * IB + il + u * GI;
+        const int64_t k = i[u] < o1 ? i[u] : o0;
+        xi[u] = X[k]; yi[u] = Y[k]; zi[u] = Z[k];
+        vxi[u] = VX[k]; vyi[u] = VY[k]; vzi[u] = VZ[k];
+        if constexpr (PASS == 2) {
+            axi[u] = AX[k]; ayi[u] = AY[k]; azi[u] = AZ[k];
+            jxi[u] = JX[k]; jyi[u] = JY[k]; jzi[u] = JZ[k];
+        }
+#pragma unroll
+        for (int q = 0; q < NA; ++q)
+            S[u][q] = 0.0;
+    }
+
+    for (int64_t t0 = j0; t0 < j1; t0 += SU_NT) {
+        __syncthreads();
+        const int64_t jj = t0 + tid;
+        SuSrc<PASS> &d = tl[tid];
+        if (jj < j1) {
+            d.x = X[jj]; d.y = Y[jj]; d.z = Z[jj]; d.m = st.mass[jj];
+            d.vx = VX[jj]; d.vy = VY[jj]; d.vz = VZ[jj];
+            if constexpr (PASS == 2) {
+                d.ax = AX[jj]; d.ay = AY[jj]; d.az = AZ[jj];
+                d.jx = JX[jj]; d.jy = JY[jj]; d.jz = JZ[jj];
+            }
+        } else {
+            d.x = NULL_POS; d.y = NULL_POS; d.z = NULL_POS; d.m = 0.0;
+            d.vx = 0.0; d.vy = 0.0; d.vz = 0.0;
+            if constexpr (PASS == 2) {
+                d.ax = 0.0; d.ay = 0.0; d.az = 0.0;
+                d.jx = 0.0; d.jy = 0.0; d.jz = 0.0;
+            }
+        }
+        __syncthreads();
+#pragma unroll 2
+        for (int t = js; t < SU_NT; t += LPI) {
+            const SuSrc<PASS> &s = tl[t];
+#pragma unroll
+            for (int u = 0; u < IPT; ++u) {
+                const double dx = s.x - xi[u], dy = s.y - yi[u], dz = s.z - zi[u];
+                const double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, eps2)));
+                double rinv = rinv_f64(r2);
+                if constexpr (EPS0)
+                    rinv = r2 > 0.0 ? rinv : 0.0;
+                const double rho = rinv * rinv, wt = s.m * rinv * rho;
+                const double vx = s.vx - vxi[u], vy = s.vy - vyi[u], vz = s.vz - vzi[u];
+                const double al = fma(dx, vx, fma(dy, vy, dz * vz)) * rho;
+                const double wa = wt * al;
+                double *Q = S[u];
+                if constexpr (PASS == 1) {
+                    Q[0] = fma(wt, dx, Q[0]); Q[1] = fma(wt, dy, Q[1]); Q[2] = fma(wt, dz, Q[2]);
+                    Q[3] = fma(wt, vx, Q[3]); Q[4] = fma(wt, vy, Q[4]); Q[5] = fma(wt, vz, Q[5]);
+                    Q[6] = fma(wa, dx, Q[6]); Q[7] = fma(wa, dy, Q[7]); Q[8] = fma(wa, dz, Q[8]);
+                } else {
+                    const double ax = s.ax - axi[u], ay = s.ay - ayi[u], az = s.az - azi[u];
+                    const double jx = s.jx - jxi[u], jy = s.jy - jyi[u], jz = s.jz - jzi[u];
+                    const double q = rho * fma(vx, vx, fma(vy, vy, fma(vz, vz,
+                                           fma(dx, ax, fma(dy, ay, dz * az)))));
+                    const double va = fma(vx, ax, fma(vy, ay, vz * az));
+                    const double tt = fma(3.0, va, fma(dx, jx, fma(dy, jy, dz * jz)));
+                    const double a5 = 5.0 * al;
+                    const double wk = wt * fma(a5, al, -q);
+                    const double wl = wt * fma(a5, fma(7.0 * al, al, -3.0 * q), tt * rho);
+                    Q[0] = fma(wt, ax, Q[0]); Q[1] = fma(wt, ay, Q[1]); Q[2] = fma(wt, az, Q[2]);
+                    Q[3] = fma(wa, vx, Q[3]); Q[4] = fma(wa, vy, Q[4]); Q[5] = fma(wa, vz, Q[5]);
+                    Q[6] = fma(wk, dx, Q[6]); Q[7] = fma(wk, dy, Q[7]); Q[8] = fma(wk, dz, Q[8]);
+                    Q[9] = fma(wt, jx, Q[9]); Q[10] = fma(wt, jy, Q[10]); Q[11] = fma(wt, jz, Q[11]);
+                    Q[12] = fma(wa, ax, Q[12]); Q[13] = fma(wa, ay, Q[13]); Q[14] = fma(wa, az, Q[14]);
+                    Q[15] = fma(wk, vx, Q[15]); Q[16] = fma(wk, vy, Q[16]); Q[17] = fma(wk, vz, Q[17]);
+                    Q[18] = fma(wl, dx, Q[18]); Q[19] = fma(wl, dy, Q[19]); Q[20] = fma(wl, dz, Q[20]);
+                }
+            }
+        }
+    }
+
+#pragma unroll
+    for (int u = 0; u < IPT; ++u) {
+        double R[6];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            if constexpr (PASS == 1) {
+                R[d] = S[u][d];
+                R[3 + d] = fma(-3.0, S[u][6 + d], S[u][3 + d]);
+            } else {
+                R[d] = fma(3.0, S[u][6 + d], fma(-6.0, S[u][3 + d], S[u][d]));
+                R[3 + d] = fma(-3.0, S[u][18 + d], fma(9.0, S[u][15 + d],
+                               fma(-9.0, S[u][12 + d], S[u][9 + d])));
+            }
+        }
+        // lanes of a particle, in a fixed order (xor butterfly)
+#pragma unroll
+        for (int msk = 1; msk < LPI; msk <<= 1)
+#pragma unroll
+            for (int q = 0; q < 6; ++q)
+                R[q] += __shfl_xor(R[q], msk, 64);
+        if (i[u] >= o1 || js != 0)
+            continue;
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+            if (part)
+                part[((int64_t)b * 6 + q) * n + i[u]] = R[q];
+            else
+                (q < 3 ? out0 : out1)[(q % 3) * n + i[u]] = R[q];
+        }
+    }
+}
+
+// sums over the splits in use, in the order b = 0, 1, ...; one lane per
+// (component, particle)
+__global__ __launch_bounds__(256) void startup_reduce(const double *part, int32_t B, int64_t n,
+                                                      const int64_t *off,
+                                                      const int32_t *cluster_of, double *out0,
+                                                      double *out1)
+{
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t >= 6 * n)
+        return;
+    const int q = (int)(t / n);
+    const int64_t i = t - (int64_t)q * n;
+    const int c = cluster_of ? cluster_of[i] : 0;
+    const int64_t used = splits_used(cluster_of ? off[c + 1] - off[c] : n, B, SU_NT);
+    double r = 0.0;
+#pragma unroll 8
+    for (int64_t b = 0; b < used; ++b)
+        r += part[(b * 6 + q) * n + i];
+    (q < 3 ? out0 : out1)[(q % 3) * n + i] = r;
+}
+
+using KStart = void (*)(State, int64_t, ForceWork, double *, double *, double *, double);
+
+template <int PASS, bool EPS0>
+KStart pick_startup(int lpi)
+{
+    switch (lpi) {
+    case 1: return startup_kernel<PASS, 1, 2, EPS0>;
+    case 4: return startup_kernel<PASS, 4, 1, EPS0>;
+    case 16: return startup_kernel<PASS, 16, 1, EPS0>;
+    default: return startup_kernel<PASS, 64, 1, EPS0>;
+    }
+}
+
+}  // namespace
+
+// Launch shape: the fewest lanes per particle (1 with two particles per
+// lane, 4, 16, 64) with which i-blocks times tiles of sources still give the
+// chip's 256 compute units four workgroups each, then splits of whole tiles
+// up to eight workgroups per unit, while the 6 B n partial sums fit the
+// split buffer.  Fewer lanes mean fewer LDS reads and no lane sums; more
+// than eight workgroups per unit only add partial sums.
+StartupShape startup_shape(int64_t n, int32_t nc, int64_t n_src, int64_t part_cap)
+{
+    const int64_t want = 1024, most = 2048;
+    const int64_t tiles = (n_src + SU_NT - 1) / SU_NT;
+    StartupShape s;
+    for (int lpi : {1, 4, 16, 64}) {
+        s.lpi = lpi;
+        s.ib = SU_NT / lpi * (lpi == 1 ? 2 : 1);
+        s.n_blocks = nc == 1 ? (n + s.ib - 1) / s.ib : n / s.ib + nc + 1;
+        if (s.n_blocks * tiles >= want)
+            break;
+    }
+    s.split = 1;
+    while (s.n_blocks * s.split * 2 <= most && s.split * 2 <= tiles &&
+           (int64_t)s.split * 2 * 6 * n <= 10 * part_cap)
+        s.split *= 2;
+    return s;
+}
+
+hipError_t launch_startup(Ctx &c, const ForceWork &w, const StartupShape &sh, int pass,
+                          hipStream_t s)
+{
+    double *o0 = pass == 1 ? c.st.acc : c.st.snp, *o1 = pass == 1 ? c.st.jrk : c.st.crk;
+    double *part = sh.split > 1 ? c.part : nullptr;
+    const bool e0 = c.eps == 0.0;
+    KStart k = pass == 1 ? (e0 ? pick_startup<1, true>(sh.lpi) : pick_startup<1, false>(sh.lpi))
+                         : (e0 ? pick_startup<2, true>(sh.lpi) : pick_startup<2, false>(sh.lpi));
+    hipLaunchKernelGGL(k, dim3((unsigned)sh.n_blocks, (unsigned)sh.split), dim3(SU_NT), 0, s, c.st,
+                       c.n, w, o0, o1, part, c.eps * c.eps);
+    if (part)
+        hipLaunchKernelGGL(startup_reduce, dim3((unsigned)((6 * c.n + 255) / 256)), dim3(256), 0,
+                           s, (const double *)part, sh.split, c.n, (const int64_t *)c.d_off,
+                           (const int32_t *)(c.nc > 1 ? c.d_cluster_of : nullptr), o0, o1);
+    return hipGetLastError();
+}
+
+}  // namespace nb
