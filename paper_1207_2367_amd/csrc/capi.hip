@@ -144,10 +144,11 @@ hipError_t scratch_address(int dev, unsigned char **out)
 }
 
 // Scratch layout of nbody_force_noalloc for n sources: the records of the
-// context's precision, seg[2] and off[2]; the split partials follow at the
-// returned offset.  With base == nullptr only the size is computed.
-int64_t noalloc_layout(int64_t n, int32_t prec, Ctx *c, unsigned char *base, int64_t **seg,
-                       int64_t **off)
+// context's precision (used by calls without the potential; the limit on the
+// sizes counts them for every call) and 512 bytes left free; the split
+// partials follow at the returned offset.  With base == nullptr only the size
+// is computed.
+int64_t noalloc_layout(int64_t n, int32_t prec, Ctx *c, unsigned char *base)
 {
     int64_t o = 0;
     auto take = [&](int64_t bytes) -> unsigned char * {
@@ -176,9 +177,7 @@ int64_t noalloc_layout(int64_t n, int32_t prec, Ctx *c, unsigned char *base, int
         for (auto p : dl)
             *p = (double *)take(n * d);
     }
-    *seg = (int64_t *)take(2 * 8);
-    *off = (int64_t *)take(2 * 8);
-    return o;
+    return o + 2 * ALIGN;
 }
 
 }  // namespace
@@ -260,6 +259,8 @@ int64_t nb::ws_layout(int64_t n, int32_t nc, int32_t prec, Ctx *c, char *base)
     double *phi = (double *)take(n * d);
     if (c) {
         c->st = st;
+        c->js = JSrc{st.pos, st.pos + n, st.pos + 2 * n, st.vel, st.vel + n, st.vel + 2 * n,
+                     st.acc, st.acc + n, st.acc + 2 * n, st.mass, 1};
         c->jm = jm;
         c->jp = jp;
         c->jd = jd;
@@ -408,6 +409,8 @@ int run_force(Ctx &c, const int32_t *idx, int64_t n_act, int64_t n_act_typ, cons
     w.nc = c.nc;
     w.err = c.d_err;
     if (c.nc == 1) {
+        w.n_act = n_act;
+        w.n_src = c.n;
         w.n_blocks = (n_act + ib - 1) / ib;
     } else {
         const int64_t cap = n_act / ib + c.nc + 1;
@@ -625,7 +628,6 @@ int plan_ensemble(Ctx &c, int G)
     c.ens.cl = c.d_ens_i32 + 4 * LOOP_GMAX + 1;
     c.ens.part_off = c.d_ens_i64;
     c.ens.part_cap = c.d_ens_i64 + LOOP_GMAX;
-    c.ens.seg = c.d_ens_i64 + 2 * LOOP_GMAX;
     return wg;
 }
 
@@ -796,7 +798,7 @@ int block_step(Ctx &c, double t_target, int64_t *n_act_out, double *t_block_out,
         return rc;
     rec = prof_begin(c, PH_CORRECT);
     if (w.split > 1)
-        HIPCHK(c, launch_reduce_correct(c, w, w.split, 64 * L.waves, n_act, t_target, c.stream,
+        HIPCHK(c, launch_reduce_correct(c, w, w.split, split_unit(L.lpi, L.waves), n_act, t_target, c.stream,
                                         levels));
     else
         HIPCHK(c, launch_correct(c, n_act, c.act, t_target, out.vec[0], out.vec[1], out.vec[2], 1,
@@ -1008,8 +1010,12 @@ int nbody_force(nbody_ctx *ctx, int64_t n_act, const int32_t *d_idx, double *d_a
         if (rc)
             return rc;
     }
-    HIPCHK(c, launch_pack(c, nullptr, 1, nullptr, c.stream));
-    HIPCHK(c, launch_segments(c, d_idx, n_act, c.stream));
+    // with the potential the kernels read the stored state itself (see
+    // SrcOf in force.hip); without it, records packed from it
+    if (!d_pot)
+        HIPCHK(c, launch_pack(c, nullptr, 1, nullptr, c.stream));
+    if (c.nc > 1)
+        HIPCHK(c, launch_segments(c, d_idx, n_act, c.stream));
     ForceOut out{};
     out.vec[0] = d_acc;
     out.vec[1] = d_jrk;
@@ -1338,7 +1344,7 @@ int nbody_autotune(nbody_ctx *ctx, double max_ms)
             rc = hip_fail(c, hipGetLastError(), "autotune copy");
             break;
         }
-        if (launch_segments(c, c.act, nt, s) != hipSuccess) {
+        if (c.nc > 1 && launch_segments(c, c.act, nt, s) != hipSuccess) {
             rc = hip_fail(c, hipGetLastError(), "autotune segments");
             break;
         }
@@ -1468,8 +1474,7 @@ int nbody_force_noalloc(int64_t n, const double *d_mass, const double *d_pos,
     c.cfg.precision = precision;
     c.cfg.stream = stream;
     c.stream = (hipStream_t)stream;
-    int64_t *seg = nullptr, *off = nullptr;
-    const int64_t head = noalloc_layout(n, precision, &c, nullptr, &seg, &off);
+    const int64_t head = noalloc_layout(n, precision, &c, nullptr);
     const int64_t cap = (NOALLOC_SCRATCH_BYTES - head) / (10 * (int64_t)sizeof(double));
     if (cap < n_act)
         return NBODY_EINVAL;   // records plus one split of partials exceed the scratch
@@ -1478,15 +1483,15 @@ int nbody_force_noalloc(int64_t n, const double *d_mass, const double *d_pos,
     unsigned char *base = nullptr;
     if (scratch_address(c.device, &base) != hipSuccess)
         return NBODY_EDEVICE;
-    noalloc_layout(n, precision, &c, base, &seg, &off);
+    noalloc_layout(n, precision, &c, base);
     c.part = reinterpret_cast<double *>(base + head);
     c.part_cap = cap;
     const Launch L = rule_launch(n_act, n, cap, precision);
     const int64_t ib = iblock_size(L);
     ForceWork w{};
     w.idx = d_idx;
-    w.seg = seg;
-    w.off = off;
+    w.n_act = n_act;
+    w.n_src = n;
     w.split = L.split;
     w.nc = 1;
     w.n_blocks = (n_act + ib - 1) / ib;
@@ -1497,9 +1502,12 @@ int nbody_force_noalloc(int64_t n, const double *d_mass, const double *d_pos,
     out.pot = d_pot_out;
     out.sk = 3;
     out.sd = 1;
-    if (launch_pack_arrays(c, d_mass, d_pos, d_vel, d_acc, n_act, seg, off, c.stream) !=
-            hipSuccess ||
-        launch_force(c, w, L, out, n_act, c.stream) != hipSuccess)
+    c.js = JSrc{d_pos, d_pos + 1, d_pos + 2, d_vel, d_vel + 1, d_vel + 2,
+                d_acc, d_acc + 1, d_acc + 2, d_mass, 3};
+    if (!d_pot_out &&
+        launch_pack_arrays(c, d_mass, d_pos, d_vel, d_acc, c.stream) != hipSuccess)
+        return NBODY_EDEVICE;
+    if (launch_force(c, w, L, out, n_act, c.stream) != hipSuccess)
         return NBODY_EDEVICE;
     return NBODY_OK;
 }

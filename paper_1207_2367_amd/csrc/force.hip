@@ -32,8 +32,8 @@
 //     accuracy by one third-order step;
 //   - the potential energy (energy_kernel) takes every pair once, with a
 //     cyclic half-window per particle that gives every workgroup equal work;
-//   - grid.y = B splits the sources (chunks of whole tiles; a cluster with
-//     fewer tiles uses fewer splits, the rest exit at once); partial results
+//   - grid.y = B splits the sources (whole units, sizes alike; a cluster with
+//     fewer units uses fewer splits, the rest exit at once); partial results
 //     go to a [B][10][n_act] buffer that a second kernel sums in fixed order
 //     b = 0 .. B_c-1 (reduce_split here, the corrector's kernel in a block
 //     step, or the correction phase of the device-resident loop), so the
@@ -92,9 +92,25 @@ __device__ __forceinline__ void xcd_order(int64_t &g, int &b)
 // PHI: also sum the potential (nbody_force, the start-up pass); a block
 // step's evaluation does not need it (the energy has its own pass).  IPT:
 // active particles per lane group.
+// Waves per SIMD that the registers are allotted for: as many as a shape
+// holds with hardly a spill outside its pair loop (left alone, the compiler
+// spends registers on deeper unrolling and drops to two waves).
+constexpr int force_waves(int prec, int lpi, int ipt)
+{
+    if (ipt == 2)
+        return prec == PREC_PAIR32 && lpi == 1 ? 2 : 3;
+    return prec == PREC_PAIR32 ? 3 : 4;
+}
+
+// Sources of an evaluation: with the potential (nbody_force, at the stored
+// state's own times) the FP64 state or the caller's arrays as they stand, so
+// that no packing pass runs first; in a block step the predicted records.
+template <int PREC, bool PHI>
+using SrcOf = typename std::conditional<PHI, JSrc, typename Smem<PREC>::R>::type;
+
 template <int PREC, int LPI, int NW, bool EPS0, bool PHI, int IPT>
-__global__ __launch_bounds__(NW * 64) void force_kernel(
-    typename Smem<PREC>::R J, ForceWork w, ForceOut out, double *part,
+__global__ __launch_bounds__(NW * 64, force_waves(PREC, LPI, IPT)) void force_kernel(
+    SrcOf<PREC, PHI> J, ForceWork w, ForceOut out, double *part,
     int64_t n_act_total, double eps2)
 {
     int64_t g;
@@ -186,47 +202,66 @@ __global__ __launch_bounds__(256) void energy_kernel(const double *X, const doub
         out[(int64_t)b * bstride + i] = phi;
 }
 
-// Sum the B split-source partials of every active slot in the fixed order
-// b = 0 .. B-1 (Table 1, section 4 of the paper).  One thread per (quantity,
-// active slot), so reads are coalesced over slots; the loads of 16 splits
-// are issued before their adds (the order of the adds is unchanged), which
-// keeps a tiny active set with a large B from waiting out B serial
-// round trips to L2.  With the evaluation's ForceWork (w.off != nullptr),
-// only the splits that hold sources of the slot's cluster are read (the
-// evaluation's chunks are whole tiles of nt sources).
+// Sum the B split-source partials of every active slot (Table 1, section 4
+// of the paper) in a fixed order: R lanes per (quantity, active slot), lane r
+// summing the splits [r B / R, (r + 1) B / R) in order with the loads of 16
+// splits issued before their adds, then the R sums in the order r = 0 .. R-1.
+// Neighbouring lanes take neighbouring slots, so reads are coalesced.  The
+// bound of a small active set is the chain of dependent round trips to L2,
+// which R lanes cut R-fold.  With the evaluation's ForceWork, only the splits
+// that hold sources of the slot's cluster are read (the evaluation's splits
+// are whole units of nt sources).
+template <int R>
 __global__ __launch_bounds__(256) void reduce_split(const double *part, int32_t B,
                                                     int64_t n_act, ForceOut out,
                                                     int pot_only, ForceWork w,
                                                     const int32_t *cluster_of, int nt)
 {
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    constexpr int S = 256 / R;   // sums per workgroup
+    __shared__ double ps[R][S];
+    const int kl = threadIdx.x % S, rl = threadIdx.x / S;
+    const int64_t t = (int64_t)blockIdx.x * S + kl;
     const int nq = pot_only ? 1 : 10;
-    if (t >= n_act * nq)
-        return;
+    const bool in = t < n_act * nq;
     const int q = pot_only ? 9 : (int)(t / n_act);
     const int64_t k = pot_only ? t : t - (int64_t)q * n_act;
-    const double *p = part + (int64_t)q * n_act + k;
-    if (w.off) {
-        const int64_t i = w.idx ? (int64_t)w.idx[k] : k;
-        // (an index out of range was skipped by the evaluation: any cluster)
-        const int c = cluster_of && i >= 0 && i < w.off[w.nc] ? cluster_of[i] : 0;
-        B = (int32_t)splits_used(w.off[c + 1] - w.off[c], B, nt);
-    }
-    const int64_t stride = 10 * n_act;
-    constexpr int U = 16;
     double r = 0.0;
-    int b = 0;
-    for (; b + U <= B; b += U) {
-        double v[U];
+    if (in) {
+        if (w.n_src > 0) {
+            B = (int32_t)splits_used(w.n_src, B, nt);
+        } else if (w.off) {
+            const int64_t i = w.idx ? (int64_t)w.idx[k] : k;
+            // (an index out of range was skipped by the evaluation: any cluster)
+            const int c = cluster_of && i >= 0 && i < w.off[w.nc] ? cluster_of[i] : 0;
+            B = (int32_t)splits_used(w.off[c + 1] - w.off[c], B, nt);
+        }
+        const int64_t stride = 10 * n_act;
+        const int b0 = (int)((int64_t)rl * B / R), b1 = (int)((int64_t)(rl + 1) * B / R);
+        const double *p = part + (int64_t)q * n_act + k;
+        constexpr int U = 16;
+        int b = b0;
+        for (; b + U <= b1; b += U) {
+            double v[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            v[u] = p[(int64_t)(b + u) * stride];
+            for (int u = 0; u < U; ++u)
+                v[u] = p[(int64_t)(b + u) * stride];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            r += v[u];
+            for (int u = 0; u < U; ++u)
+                r += v[u];
+        }
+        for (; b < b1; ++b)
+            r += p[(int64_t)b * stride];
     }
-    for (; b < B; ++b)
-        r += p[(int64_t)b * stride];
+    if constexpr (R > 1) {
+        ps[rl][kl] = r;
+        __syncthreads();
+        r = ps[0][kl];
+#pragma unroll
+        for (int u = 1; u < R; ++u)
+            r += ps[u][kl];
+    }
+    if (!in || rl != 0)
+        return;
     if (q == 9) {
         if (out.pot)
             out.pot[k] = r;
@@ -235,10 +270,21 @@ __global__ __launch_bounds__(256) void reduce_split(const double *part, int32_t 
     }
 }
 
+// R by the length of the chains: 16 loads in flight per lane.  Sums that fill
+// the chip by themselves (2^16 of them and more) take one lane each.
+void launch_reduce(const double *part, int32_t B, int64_t n_act, const ForceOut &out, int pot_only,
+                   const ForceWork &w, const int32_t *cluster_of, int nt, hipStream_t s)
+{
+    const int64_t sums = n_act * (pot_only ? 1 : 10);
+    const int R = B <= 16 || sums >= (int64_t(1) << 16) ? 1 : (B <= 64 ? 4 : 8);
+    const auto k = R == 1 ? reduce_split<1> : (R == 4 ? reduce_split<4> : reduce_split<8>);
+    hipLaunchKernelGGL(k, dim3((unsigned)((sums * R + 255) / 256)), dim3(256), 0, s, part, B,
+                       n_act, out, pot_only, w, cluster_of, nt);
+}
+
 // ---- dispatch table over the template parameters
-using KMixed = void (*)(JRecMixed, ForceWork, ForceOut, double *, int64_t, double);
-using KPair32 = void (*)(JRecPair32, ForceWork, ForceOut, double *, int64_t, double);
-using KF64 = void (*)(JRecF64, ForceWork, ForceOut, double *, int64_t, double);
+template <typename R>
+using KForce = void (*)(R, ForceWork, ForceOut, double *, int64_t, double);
 
 // Two active particles per lane group are built for 1, 2 and 4 lanes per
 // particle (the large active sets, where the LDS reads per pair matter);
@@ -246,7 +292,7 @@ using KF64 = void (*)(JRecF64, ForceWork, ForceOut, double *, int64_t, double);
 template <int PREC, bool EPS0, int NW, bool PHI>
 auto pick_lpi(int lpi_log2, int ipt)
 {
-    using K = void (*)(typename Smem<PREC>::R, ForceWork, ForceOut, double *, int64_t, double);
+    using K = KForce<SrcOf<PREC, PHI>>;
     static const K tab[7] = {
         force_kernel<PREC, 1, NW, EPS0, PHI, 1>,  force_kernel<PREC, 2, NW, EPS0, PHI, 1>,
         force_kernel<PREC, 4, NW, EPS0, PHI, 1>,  force_kernel<PREC, 8, NW, EPS0, PHI, 1>,
@@ -258,7 +304,7 @@ auto pick_lpi(int lpi_log2, int ipt)
     return ipt == 2 && lpi_log2 <= 2 ? tab2[lpi_log2] : tab[lpi_log2];
 }
 
-template <int PREC, bool EPS0, bool PHI = true>
+template <int PREC, bool EPS0, bool PHI>
 auto pick_kernel(int lpi_log2, int nw, int ipt = 1)
 {
     if (nw == 1)
@@ -268,15 +314,15 @@ auto pick_kernel(int lpi_log2, int nw, int ipt = 1)
     return pick_lpi<PREC, EPS0, 4, PHI>(lpi_log2, ipt);
 }
 
-// the four (eps = 0, potential) variants of one precision
-template <int PREC>
-auto pick_variant(int lpi_log2, int nw, int ipt, bool eps0, bool phi)
+// launch of the kernel for a shape, softening and outputs
+template <int PREC, bool PHI>
+void launch_variant(const SrcOf<PREC, PHI> &J, bool eps0, const Launch &L, int lpi_log2, dim3 grid,
+                    const ForceWork &w, const ForceOut &out, double *part, int64_t n_act,
+                    double eps2, hipStream_t s)
 {
-    if (eps0)
-        return phi ? pick_kernel<PREC, true, true>(lpi_log2, nw, ipt)
-                   : pick_kernel<PREC, true, false>(lpi_log2, nw, ipt);
-    return phi ? pick_kernel<PREC, false, true>(lpi_log2, nw, ipt)
-               : pick_kernel<PREC, false, false>(lpi_log2, nw, ipt);
+    const auto k = eps0 ? pick_kernel<PREC, true, PHI>(lpi_log2, L.waves, L.ipt)
+                        : pick_kernel<PREC, false, PHI>(lpi_log2, L.waves, L.ipt);
+    hipLaunchKernelGGL(k, grid, dim3(64 * L.waves), 0, s, J, w, out, part, n_act, eps2);
 }
 
 int ilog2(int64_t v)
@@ -312,25 +358,29 @@ Launch pick_launch(const Ctx &c, int64_t n_act, int64_t n_src)
     return rule_launch(n_act, n_src, c.part_cap, c.cfg.precision);
 }
 
-// Rule fitted to the autotuner's choices on 16,384- and 65,536-source
-// spheres: 4 waves; about 4096 lanes per split (lanes per particle
+// Launch rule.  4 waves; about 4096 lanes per split (lanes per particle
 // 4096 / N_act, between 1 and 64); two particles per lane group for active
 // sets of 2^15 and more in the modes with FP64 pair arithmetic (it halves
 // the LDS reads per pair: 1-3 % faster there, measured; the FP32-pair mode
-// is faster with one); then split the sources while every split keeps two
-// tiles, the partials (split x N_act slots) fit part_cap, and either the
-// grid stays within 2^19 lanes or every split still holds 2^17 sources or
-// more.  The second clause is for large source sets: there a split's work
-// dwarfs its partials' traffic, and a grid of many more workgroups than the
-// chip holds at once (3 per CU at the mixed kernel's register use) leaves
-// a shorter partly empty last round.  Measured at 65,536 active x 8,388,608
-// sources: split 16 / 32 / 64 / 128 / 256 -> 946 / 935 / 930 / 927 / 925 ms,
-// but 3.4 / 4.5 / 6.8 / 11.2 / 20.2 GB fetched (shorter walks, started at
-// staggered times, share the L2 less); 2^17 stops at 64.  For the same
-// reason a grid of at most 4096 workgroups (about five rounds of the 768
-// resident ones) is split further while every split keeps 2^15 sources:
-// 131,072 active x 2^20 sources 241 -> 238 ms (split 8 -> 16), 65,536 x 2^21
-// 243 -> 240 ms (16 -> 32), measured.
+// is faster with one).  Then the sources are split:
+//   - up to 4096 workgroups while every split keeps a tile: the chip holds
+//     768-1024 at once, and with several rounds of them a compute unit that
+//     is done takes the next.  Against the earlier limit of 2048 with two
+//     tiles per split: 7424 active x 32,768 sources 480 -> 436 us (64 -> 128
+//     splits), 2176 x 32,768 172 -> 148 us, 23,296 x 32,768 1387 -> 1357 us
+//     (16 -> 32); more do not help, and add partial sums;
+//   - with 16 or more lanes per particle and a split of few tiles, up to 1792
+//     workgroups while every split keeps two tiles: a workgroup's start, lane
+//     sums and partial results then weigh as much as its pairs, so one round
+//     is best: 64 active x 65,536 sources 20.2 + 4.1 us (evaluation + split
+//     sums) with 64 splits, 22.7 + 6.2 us with 128, 22.2 + 4.0 us with 32;
+//   - for large source sets further while every split holds 2^17 sources: a
+//     split's work dwarfs its partials' traffic there.  65,536 active x
+//     8,388,608 sources: split 16 / 32 / 64 / 128 / 256 -> 946 / 935 / 930 /
+//     927 / 925 ms, but 3.4 / 4.5 / 6.8 / 11.2 / 20.2 GB fetched (shorter
+//     walks, started at staggered times, share the L2 less); 2^17 stops at 64.
+// Powers of two only: some other splits of a particle pair per lane group
+// measured up to 16 % slower (65,536 x 65,536: 16 splits 7.50 ms, 18 8.74 ms).
 Launch rule_launch(int64_t n_act, int64_t n_src, int64_t part_cap, int prec)
 {
     Launch L;
@@ -341,16 +391,14 @@ Launch rule_launch(int64_t n_act, int64_t n_src, int64_t part_cap, int prec)
         L.lpi <<= 1;
     L.ipt = prec != NBODY_PREC_FP32PAIR && L.lpi <= 4 && n_act * L.lpi >= (int64_t(1) << 15) ? 2 : 1;
     const int64_t nt = 64 * L.waves;
-    const int64_t max_lanes = int64_t(1) << 19, long_split = int64_t(1) << 17;
-    const int64_t few_wgs = 4096, mid_split = int64_t(1) << 15;
+    const int64_t long_split = int64_t(1) << 17;
     const int64_t n_ib = (n_act + iblock_size(L) - 1) / iblock_size(L);
     for (;;) {
         const int64_t b2 = (int64_t)L.split * 2, per_split = n_src / b2;
-        if (per_split < 2 * nt || b2 * n_act > part_cap || b2 > 65535)   // grid y limit
+        const bool latency = L.lpi >= 16 && per_split < 16 * nt;
+        if (per_split < (latency ? 2 : 1) * nt || b2 * n_act > part_cap || b2 > 65535)   // grid y limit
             break;
-        const bool lanes_ok = n_act * L.lpi / L.ipt * b2 <= max_lanes;
-        const bool few = n_ib * b2 <= few_wgs && per_split >= mid_split;
-        if (!lanes_ok && per_split < long_split && !few)
+        if (n_ib * b2 > (latency ? 1792 : 4096) && per_split < long_split)
             break;
         L.split <<= 1;
     }
@@ -366,30 +414,33 @@ hipError_t launch_force(Ctx &c, const ForceWork &w, const Launch &L,
     const bool eps0 = c.eps == 0.0;
     const double eps2 = c.eps * c.eps;
     double *part = w.split > 1 ? c.part : nullptr;
-    const dim3 grid((unsigned)w.n_blocks, (unsigned)w.split);
-    const dim3 block(64 * L.waves);
+    // one cluster: no workgroups for splits without sources
+    const int64_t gy = w.blk_cluster ? w.split
+                                     : splits_used(w.n_src, w.split, split_unit(L.lpi, L.waves));
+    const dim3 grid((unsigned)w.n_blocks, (unsigned)gy);
     const int prec = c.cfg.precision;
     const bool phi = out.pot != nullptr;   // potential wanted (not in block steps)
     const int rec = prof_begin(c, PH_FORCE, n_act_total);
-    if (prec == NBODY_PREC_MIXED) {
-        const KMixed k = pick_variant<PREC_MIXED>(lg, L.waves, L.ipt, eps0, phi);
-        hipLaunchKernelGGL(k, grid, block, 0, s, c.jm, w, out, part, n_act_total, eps2);
-    } else if (prec == NBODY_PREC_FP32PAIR) {
-        const KPair32 k = pick_variant<PREC_PAIR32>(lg, L.waves, L.ipt, eps0, phi);
-        hipLaunchKernelGGL(k, grid, block, 0, s, c.jp, w, out, part, n_act_total, eps2);
-    } else {
-        const KF64 k = pick_variant<PREC_F64>(lg, L.waves, L.ipt, eps0, phi);
-        hipLaunchKernelGGL(k, grid, block, 0, s, c.jd, w, out, part, n_act_total, eps2);
-    }
+    auto go = [&](auto p, const auto &packed) {
+        constexpr int P = decltype(p)::value;
+        if (phi)
+            launch_variant<P, true>(c.js, eps0, L, lg, grid, w, out, part, n_act_total, eps2, s);
+        else
+            launch_variant<P, false>(packed, eps0, L, lg, grid, w, out, part, n_act_total, eps2, s);
+    };
+    if (prec == NBODY_PREC_MIXED)
+        go(std::integral_constant<int, PREC_MIXED>{}, c.jm);
+    else if (prec == NBODY_PREC_FP32PAIR)
+        go(std::integral_constant<int, PREC_PAIR32>{}, c.jp);
+    else
+        go(std::integral_constant<int, PREC_F64>{}, c.jd);
     prof_end(c, rec);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || w.split <= 1 || !reduce)
         return e;
-    const unsigned nb = (unsigned)((n_act_total * 10 + 255) / 256);
     const int rr = prof_begin(c, PH_REDUCE);
-    hipLaunchKernelGGL(reduce_split, dim3(nb), dim3(256), 0, s, (const double *)c.part,
-                       w.split, n_act_total, out, 0, w, (const int32_t *)c.d_cluster_of,
-                       64 * L.waves);
+    launch_reduce(c.part, w.split, n_act_total, out, 0, w, c.d_cluster_of,
+                  split_unit(L.lpi, L.waves), s);
     prof_end(c, rr);
     return hipGetLastError();
 }
@@ -400,8 +451,8 @@ hipError_t launch_energy_pot(Ctx &c, double *phi, hipStream_t s)
 {
     constexpr int64_t IB = 256;
     const int64_t n = c.n;
-    hipError_t e = launch_segments(c, nullptr, n, s);
-    if (e != hipSuccess)
+    hipError_t e = hipSuccess;
+    if (c.nc > 1 && (e = launch_segments(c, nullptr, n, s)) != hipSuccess)
         return e;
     ForceWork w{};
     w.seg = c.d_seg;
@@ -440,9 +491,7 @@ hipError_t launch_energy_pot(Ctx &c, double *phi, hipStream_t s)
     }
     ForceOut out{};
     out.pot = phi;
-    hipLaunchKernelGGL(reduce_split, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                       (const double *)c.part, split, n, out, 1, ForceWork{},
-                       (const int32_t *)nullptr, 0);
+    launch_reduce(c.part, split, n, out, 1, ForceWork{}, nullptr, 1, s);
     prof_end(c, rec);
     return hipGetLastError();
 }

@@ -65,6 +65,61 @@ __device__ __forceinline__ double rinv_f64(double r2)
     return fma(y0 * e, fma(e, 0.375, 0.5), y0);
 }
 
+// v of another lane by a data-parallel-primitive move of each half
+template <int CTRL>
+__device__ __forceinline__ double dpp_of(double v)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+
+// v + (v of the lane 16 or 32 apart): the swap leaves the even rows (lower
+// half) of v in one register and the odd rows (upper half) in the other
+template <int STEP>
+__device__ __forceinline__ double swap_sum(double v)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)b, hi = (uint32_t)(b >> 32);
+    double r[2];
+    if constexpr (STEP == 16) {
+        const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+        for (int k = 0; k < 2; ++k)
+            r[k] = __longlong_as_double((long long)((uint64_t)h[k] << 32 | l[k]));
+    } else {
+        const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+        for (int k = 0; k < 2; ++k)
+            r[k] = __longlong_as_double((long long)((uint64_t)h[k] << 32 | l[k]));
+    }
+    return r[0] + r[1];
+}
+
+// Sum over groups of LPI neighbouring lanes, on every lane of the group and
+// with the bits of a xor butterfly (at the steps of 4 and 8 a mirror of 8 or
+// 16 lanes meets the same partial sums, which are alike in a quad or half
+// row by then).  Register moves only: the same sum through LDS permutes was
+// a fifth of a small block's evaluation.
+template <int LPI>
+__device__ __forceinline__ double lane_sum(double v)
+{
+    if constexpr (LPI >= 2)
+        v += dpp_of<0xB1>(v);    // quad_perm 1 0 3 2
+    if constexpr (LPI >= 4)
+        v += dpp_of<0x4E>(v);    // quad_perm 2 3 0 1
+    if constexpr (LPI >= 8)
+        v += dpp_of<0x141>(v);   // row_half_mirror
+    if constexpr (LPI >= 16)
+        v += dpp_of<0x140>(v);   // row_mirror
+    if constexpr (LPI >= 32)
+        v = swap_sum<16>(v);
+    if constexpr (LPI >= 64)
+        v = swap_sum<32>(v);
+    return v;
+}
+
 // LDS tile of NT source records, one 16-byte aligned record per source
 // (its fields side by side): with one lane per particle every lane reads
 // the same record, and from one address every field is an immediate offset
@@ -93,24 +148,38 @@ __device__ __forceinline__ SrcTile<PREC, NT> &src_tile()
     return t;
 }
 
+// Distance between neighbouring particles of a source array
+template <typename R>
+__device__ __forceinline__ constexpr int64_t rec_stride(const R &)
+{
+    return 1;
+}
+__device__ __forceinline__ int64_t rec_stride(const JSrc &J) { return J.st; }
+
 // One workgroup's share of an evaluation: i-block g (IB active slots) against
-// source split b.  The launch kernel calls it with (blockIdx.x, blockIdx.y);
+// source split b.  J: packed records of the precision, or the FP64 sources as
+// they stand (JSrc), rounded to the record's types on the way to LDS.  The launch kernel calls it with (blockIdx.x, blockIdx.y);
 // the device-resident block-step loop calls it for the units it takes.
 // Every early return is uniform over the workgroup.  PHI: also sum the
 // potential (nbody_force); a block step's evaluation
 // does not need it (the energy has its own pass).  IPT: active particles
 // per lane group (each source read from LDS serves IPT pairs).
-template <int PREC, int LPI, int NW, bool EPS0, bool PHI, int IPT = 1>
-__device__ __forceinline__ void force_block(const typename Smem<PREC>::R &J, const ForceWork &w,
-                                            const ForceOut &out, double *part,
-                                            int64_t n_act_total, double eps2, int64_t g,
-                                            int b)
+template <int PREC, int LPI, int NW, bool EPS0, bool PHI, int IPT = 1, bool AHEAD = true,
+          typename R>
+__device__ __forceinline__ void force_block(const R &J, const ForceWork &w, const ForceOut &out,
+                                            double *part, int64_t n_act_total, double eps2,
+                                            int64_t g, int b)
 {
     constexpr int NT = NW * 64;      // sources per LDS tile
     constexpr int GI = 64 / LPI;     // lane groups (of LPI lanes) per wave
     constexpr int NG = NW * GI;      // lane groups per workgroup
     constexpr int IB = NG * IPT;     // active particles per workgroup
     constexpr int PER = NT / LPI;    // sources per lane per tile
+    // pairs per lane of one FP32 partial sum: a short one keeps its rounding
+    // small (64 pairs measured 3x better than 256 for FP32 jerk sums, at ~1%
+    // more instructions)
+    constexpr int FOLD = PER < 64 ? PER : 64;
+    static_assert(FOLD * LPI == split_unit(LPI, NW), "unit of a split");
     constexpr bool MIXED = PREC == PREC_MIXED;
     constexpr bool P32 = PREC == PREC_PAIR32;
     constexpr int NV = 9;            // vector outputs (a, da, d2a)
@@ -125,30 +194,57 @@ __device__ __forceinline__ void force_block(const typename Smem<PREC>::R &J, con
     SrcTile<PREC, NT> &tl = src_tile<PREC, NT>();
 
     // ---- which active slots and which sources this workgroup takes
-    int c = 0;
-    int64_t gfirst = 0;
+    int64_t gfirst = 0, s0 = 0, s1 = w.n_act, o0 = w.src0, o1 = w.src0 + w.n_src;
     if (w.blk_cluster) {
-        c = w.blk_cluster[g];
+        const int c = w.blk_cluster[g];
         if (c < 0)
             return;  // grid padding past the last i-block
         gfirst = w.blk_first[c];
+        s0 = w.seg[c];
+        s1 = w.seg[c + 1];
+        o0 = w.off[c];
+        o1 = w.off[c + 1];
     }
-    const int64_t s0 = w.seg[c], s1 = w.seg[c + 1];
     const int64_t kb = s0 + (g - gfirst) * IB;
-    const int64_t o0 = w.off[c], o1 = w.off[c + 1];
-    const int64_t chunk = split_chunk(o1 - o0, w.split, NT);
-    // splits past this cluster's sources (chunks are whole tiles, so a small
+    // splits past this cluster's sources (splits are whole units, so a small
     // cluster fills fewer than B of them): nothing to do, and the reduction
     // reads only the splits in use
-    if ((int64_t)b * chunk >= o1 - o0 && b > 0)
+    const int64_t used = splits_used(o1 - o0, w.split, FOLD * LPI);
+    if (b >= used)
         return;
-    const int64_t j0 = o0 + (int64_t)b * chunk;
-    const int64_t j1 = j0 + chunk < o1 ? j0 + chunk : o1;
+    const int64_t j0 = o0 + split_begin(o1 - o0, used, FOLD * LPI, b);
+    const int64_t j1 = o0 + split_begin(o1 - o0, used, FOLD * LPI, b + 1);
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int il = wave * GI + lane / LPI;   // lane group
     const int js = lane & (LPI - 1);         // slot within the group
+    // The record of this lane's source of tile t0, in registers.  Each tile
+    // is fetched one tile ahead: the first before the active particles (two
+    // dependent loads), the others while the tile before is evaluated.  A
+    // small active set has only a few tiles per workgroup, and their load
+    // latencies (1-2 us each, behind the launch's) were most of its time.
+    // Not with AHEAD false: the ensemble loop's four waves per SIMD have no
+    // registers left for it (7 % slower there, spilling).
+    using Rec = typename SrcTile<PREC, NT>::S;
+    const int64_t st = rec_stride(J);
+    auto fetch = [&](int64_t t0) {
+        Rec r;
+        const int64_t jj = t0 + tid, e = jj * st;
+        if (jj < j1) {
+            r.x = J.x[e]; r.y = J.y[e]; r.z = J.z[e]; r.m = J.m[jj];
+            r.vx = (VV)J.vx[e]; r.vy = (VV)J.vy[e]; r.vz = (VV)J.vz[e];
+            r.ax = (VA)J.ax[e]; r.ay = (VA)J.ay[e]; r.az = (VA)J.az[e];
+        } else {
+            r.x = NULL_POS; r.y = NULL_POS; r.z = NULL_POS; r.m = 0.0;
+            r.vx = 0; r.vy = 0; r.vz = 0;
+            r.ax = 0; r.ay = 0; r.az = 0;
+        }
+        return r;
+    };
+    Rec next;
+    if constexpr (AHEAD)
+        next = fetch(j0);
     // particle u of the lane group: active slot kb + il + u NG
     int64_t k[IPT], i[IPT];
     bool valid[IPT];
@@ -169,10 +265,19 @@ __device__ __forceinline__ void force_block(const typename Smem<PREC>::R &J, con
             valid[u] = false;
             i[u] = o0;
         }
-        xi[u] = J.x[i[u]]; yi[u] = J.y[i[u]]; zi[u] = J.z[i[u]];
-        vxi[u] = J.vx[i[u]]; vyi[u] = J.vy[i[u]]; vzi[u] = J.vz[i[u]];
-        axi[u] = J.ax[i[u]]; ayi[u] = J.ay[i[u]]; azi[u] = J.az[i[u]];
+        const int64_t e = i[u] * st;
+        xi[u] = J.x[e]; yi[u] = J.y[e]; zi[u] = J.z[e];
+        vxi[u] = (VV)J.vx[e]; vyi[u] = (VV)J.vy[e]; vzi[u] = (VV)J.vz[e];
+        axi[u] = (VA)J.ax[e]; ayi[u] = (VA)J.ay[e]; azi[u] = (VA)J.az[e];
     }
+
+    // the active particles' values are in registers from here on: without
+    // this the wait for their loads lands in the pair loop, where it also
+    // waits for the next tile's
+#pragma unroll
+    for (int u = 0; u < (AHEAD ? IPT : 0); ++u)
+        asm volatile("" : "+v"(xi[u]), "+v"(yi[u]), "+v"(zi[u]), "+v"(vxi[u]), "+v"(vyi[u]),
+                     "+v"(vzi[u]), "+v"(axi[u]), "+v"(ayi[u]), "+v"(azi[u]));
 
     // FP64 sums (mixed: acceleration and jerk; FP64 passes: everything),
     // the potential in FP64 always, and double-single (hi, lo) pairs for
@@ -196,28 +301,18 @@ __device__ __forceinline__ void force_block(const typename Smem<PREC>::R &J, con
 
     for (int64_t t0 = j0; t0 < j1; t0 += NT) {
         __syncthreads();
-        const int64_t jj = t0 + tid;
-        if (jj < j1) {
-            tl.s[tid].x = J.x[jj];
-            tl.s[tid].y = J.y[jj];
-            tl.s[tid].z = J.z[jj];
-            tl.s[tid].m = J.m[jj];
-            tl.s[tid].vx = J.vx[jj]; tl.s[tid].vy = J.vy[jj]; tl.s[tid].vz = J.vz[jj];
-            tl.s[tid].ax = J.ax[jj]; tl.s[tid].ay = J.ay[jj]; tl.s[tid].az = J.az[jj];
-        } else {
-            tl.s[tid].x = NULL_POS;
-            tl.s[tid].y = NULL_POS;
-            tl.s[tid].z = NULL_POS;
-            tl.s[tid].m = 0.0;
-            tl.s[tid].vx = 0; tl.s[tid].vy = 0; tl.s[tid].vz = 0;
-            tl.s[tid].ax = 0; tl.s[tid].ay = 0; tl.s[tid].az = 0;
-        }
+        if constexpr (AHEAD)
+            tl.s[tid] = next;
+        else
+            tl.s[tid] = fetch(t0);
         __syncthreads();
+        if constexpr (AHEAD)
+            if (t0 + NT < j1)
+                next = fetch(t0 + NT);
 
-        // a short FP32 partial keeps its rounding small (64 pairs measured
-        // 3x better than 256 for FP32 jerk sums, at ~1% more instructions)
-        constexpr int FOLD = (MIXED || P32) ? (PER < 64 ? PER : 64) : PER;
-        for (int p0 = 0; p0 < PER; p0 += FOLD) {
+        // the last tile of a walk may hold fewer units than a whole one
+        const int pend = t0 + NT <= j1 ? PER : (int)((j1 - t0 + LPI - 1) / LPI);
+        for (int p0 = 0; p0 < pend; p0 += FOLD) {
             float T[IPT][NF];
 #pragma unroll
             for (int u = 0; u < IPT; ++u)
@@ -225,7 +320,7 @@ __device__ __forceinline__ void force_block(const typename Smem<PREC>::R &J, con
                 for (int q = 0; q < NF; ++q)
                     T[u][q] = 0.0f;
 
-            constexpr int UNROLL = IPT == 1 ? 4 : 2;
+            constexpr int UNROLL = PER > 16 ? (IPT == 1 ? 4 : 2) : (AHEAD ? 1 : 4);
 #pragma unroll UNROLL
             for (int p = p0; p < p0 + FOLD; ++p) {
                 const int t = js + p * LPI;
@@ -350,30 +445,27 @@ __device__ __forceinline__ void force_block(const typename Smem<PREC>::R &J, con
 #pragma unroll
     for (int u = 0; u < IPT; ++u) {
         // ---- combine the LPI lanes of each active particle (xor butterfly)
-        double R[NV + 1];
+        double Q[NV + 1];
         if constexpr (P32) {
 #pragma unroll
             for (int q = 0; q < NF; ++q)
-                R[q] = (double)H[u][q] + (double)L[u][q];
+                Q[q] = (double)H[u][q] + (double)L[u][q];
         } else if constexpr (MIXED) {
 #pragma unroll
             for (int q = 0; q < 6; ++q)
-                R[q] = D[u][q];
+                Q[q] = D[u][q];
 #pragma unroll
             for (int q = 0; q < NF; ++q)
-                R[6 + q] = (double)H[u][q] + (double)L[u][q];
+                Q[6 + q] = (double)H[u][q] + (double)L[u][q];
         } else {
 #pragma unroll
             for (int q = 0; q < NV; ++q)
-                R[q] = D[u][q];
+                Q[q] = D[u][q];
         }
-        R[NV] = phi[u];
+        Q[NV] = phi[u];
 #pragma unroll
-        for (int msk = 1; msk < LPI; msk <<= 1) {
-#pragma unroll
-            for (int q = 0; q < NV + 1; ++q)
-                R[q] += __shfl_xor(R[q], msk, 64);
-        }
+        for (int q = 0; q < NV + 1; ++q)
+            Q[q] = lane_sum<LPI>(Q[q]);
 
         if (!valid[u] || js != 0)
             continue;
@@ -385,11 +477,11 @@ __device__ __forceinline__ void force_block(const typename Smem<PREC>::R &J, con
                 if constexpr (P32) {
                     const float e2f = (float)eps2;
                     const float ri = __builtin_amdgcn_rsqf(fmaf(0.0f, 0.0f, fmaf(0.0f, 0.0f, fmaf(0.0f, 0.0f, e2f))));
-                    R[NV] += (double)((float)J.m[iu] * ri);
+                    Q[NV] += (double)((float)J.m[iu] * ri);
                 } else {
                     const double r2 = fma(0.0, 0.0, fma(0.0, 0.0, fma(0.0, 0.0, eps2)));
                     const double ri = MIXED ? rinv_mixed(r2) : rinv_f64(r2);
-                    R[NV] += J.m[iu] * ri;
+                    Q[NV] += J.m[iu] * ri;
                 }
             }
         }
@@ -397,15 +489,15 @@ __device__ __forceinline__ void force_block(const typename Smem<PREC>::R &J, con
             double *pb = part + (int64_t)b * 10 * n_act_total + ku;
 #pragma unroll
             for (int q = 0; q < 10; ++q)
-                pb[(int64_t)q * n_act_total] = R[q];
+                pb[(int64_t)q * n_act_total] = Q[q];
         } else {
 #pragma unroll
             for (int q = 0; q < 3; ++q)
 #pragma unroll
                 for (int d = 0; d < 3; ++d)
-                    out.vec[q][ku * out.sk + d * out.sd] = R[3 * q + d];
+                    out.vec[q][ku * out.sk + d * out.sd] = Q[3 * q + d];
             if (out.pot)
-                out.pot[ku] = R[NV];
+                out.pot[ku] = Q[NV];
         }
     }
 }

@@ -755,12 +755,6 @@ __global__ void segments_kernel(const int32_t *idx, int64_t n_act, const int64_t
     seg[c] = c == nc ? n_act : lo;
 }
 
-__global__ void set_seg_kernel(int64_t *seg, int64_t a, int64_t b)
-{
-    seg[0] = a;
-    seg[1] = b;
-}
-
 // ----------------------------------------------------------- corrector
 // Corrector of paper Sect. 3 item 3 (velocity first, then position with the
 // corrected velocity), end-of-step crackle/pop/5th derivative from the
@@ -983,7 +977,8 @@ __global__ __launch_bounds__(TPB) void reduce_correct_kernel(
         o = load_old(st, n, ic);
     if (is >= 0 && is < n) {
         const int c = cluster_of ? cluster_of[is] : 0;
-        const int64_t bc = splits_used(w.off[c + 1] - w.off[c], B, nt);
+        const int64_t ns = cluster_of ? w.off[c + 1] - w.off[c] : w.n_src;
+        const int64_t bc = splits_used(ns, B, nt);
         const int64_t b0 = r * bc / R, b1 = (r + 1) * bc / R;
         ps[q][kl][r] = sum_splits(part + (int64_t)q * n_act + ks + b0 * 10 * n_act, 10 * n_act,
                                   b1 - b0);
@@ -1177,7 +1172,7 @@ __device__ __forceinline__ const typename Smem<PREC>::R &loop_records(const JRec
 // is never reset: each pass advances it by the units plus one failed take
 // per workgroup, which every workgroup of the group adds to *base alike.
 // Which workgroup evaluates a unit does not change its partial sums.
-template <int PREC, bool EPS0, int LPI>
+template <int PREC, bool EPS0, int LPI, bool AHEAD>
 __device__ __forceinline__ void group_units(const typename Smem<PREC>::R &J, const ForceWork &w,
                                           double *part, int64_t n_act, double eps2, int64_t n_ib,
                                           int64_t B, int r, int W, uint32_t *ctr,
@@ -1187,7 +1182,7 @@ __device__ __forceinline__ void group_units(const typename Smem<PREC>::R &J, con
     const int64_t units = n_ib * B;
     if (W == 1 || !ctr) {   // alone, or no counter: round-robin
         for (int64_t u = r; u < units; u += W)
-            force_block<PREC, LPI, LOOP_NW, EPS0, false>(J, w, none, part, n_act, eps2, u % n_ib,
+            force_block<PREC, LPI, LOOP_NW, EPS0, false, 1, AHEAD>(J, w, none, part, n_act, eps2, u % n_ib,
                                                           (int)(u / n_ib));
         return;
     }
@@ -1200,7 +1195,7 @@ __device__ __forceinline__ void group_units(const typename Smem<PREC>::R &J, con
         __syncthreads();
         if (u >= units)
             break;
-        force_block<PREC, LPI, LOOP_NW, EPS0, false>(J, w, none, part, n_act, eps2, u % n_ib,
+        force_block<PREC, LPI, LOOP_NW, EPS0, false, 1, AHEAD>(J, w, none, part, n_act, eps2, u % n_ib,
                                                       (int)(u / n_ib));
     }
     base += (uint32_t)(units + W);
@@ -1214,8 +1209,8 @@ __global__ __launch_bounds__(TPB) void step_loop_kernel(
     State st, JRecMixed jm, JRecPair32 jp, JRecF64 jd, int prec, int64_t n, double eps2,
     double t_target,
     double eta, double dt_min, double dt_max, int64_t a_max, int32_t *act, double *part,
-    int64_t *seg, const int64_t *off, uint64_t *wmin, int32_t *wcnt, uint32_t *bar,
-    uint32_t *err, int64_t *hist, int64_t *res, int64_t seq)
+    uint64_t *wmin, int32_t *wcnt, uint32_t *bar, uint32_t *err, int64_t *hist, int64_t *res,
+    int64_t seq)
 {
     __shared__ double sum[9][RC_SLOTS];
     const auto &J = loop_records<PREC>(jm, jp, jd);
@@ -1273,8 +1268,6 @@ __global__ __launch_bounds__(TPB) void step_loop_kernel(
             scatter_range(st.t, st.dt, T, r0, r1, first, act);
         pack_range(st, jm, jp, jd, prec, n, r0, r1, T);
         if (blockIdx.x == 0 && threadIdx.x == 0) {
-            seg[0] = 0;
-            seg[1] = n_act;
             int bb = 0;
             while ((int64_t(1) << (bb + 1)) <= n_act)
                 ++bb;
@@ -1301,19 +1294,19 @@ __global__ __launch_bounds__(TPB) void step_loop_kernel(
             B *= 2;
         ForceWork w{};
         w.idx = act;
-        w.seg = seg;
-        w.off = off;
+        w.n_act = n_act;
+        w.n_src = n;
         w.split = (int32_t)B;
         w.nc = 1;
         w.n_blocks = n_ib;
         if (lpi == 32)
-            group_units<PREC, EPS0, 32>(J, w, part, n_act, eps2, n_ib, B, (int)blockIdx.x, (int)G,
+            group_units<PREC, EPS0, 32, true>(J, w, part, n_act, eps2, n_ib, B, (int)blockIdx.x, (int)G,
                                         uctr, ubase);
         else if (lpi == 8)
-            group_units<PREC, EPS0, 8>(J, w, part, n_act, eps2, n_ib, B, (int)blockIdx.x, (int)G,
+            group_units<PREC, EPS0, 8, true>(J, w, part, n_act, eps2, n_ib, B, (int)blockIdx.x, (int)G,
                                        uctr, ubase);
         else
-            group_units<PREC, EPS0, 1>(J, w, part, n_act, eps2, n_ib, B, (int)blockIdx.x, (int)G,
+            group_units<PREC, EPS0, 1, true>(J, w, part, n_act, eps2, n_ib, B, (int)blockIdx.x, (int)G,
                                        uctr, ubase);
         if (!grid_sync(bar, G, err, epoch)) {
             reason = LOOP_ERR;
@@ -1321,7 +1314,7 @@ __global__ __launch_bounds__(TPB) void step_loop_kernel(
         }
         // (4) this range's active particles: split sums (fixed order) and
         // the corrector, RC_SLOTS particles per pass
-        const int64_t bc = splits_used(n, B, LOOP_NT);
+        const int64_t bc = splits_used(n, B, split_unit(lpi, LOOP_NW));
         const int q = threadIdx.x / RC_SLOTS, kl = threadIdx.x % RC_SLOTS;
         for (int64_t k0 = first; k0 < first + mine; k0 += RC_SLOTS) {
             const int64_t k = k0 + kl;
@@ -1389,7 +1382,6 @@ __global__ __launch_bounds__(TPB, 4) void ensemble_loop_kernel(
     const int g = plan.grp_of[blockIdx.x];
     const uint32_t f = (uint32_t)plan.first[g], W = (uint32_t)plan.size[g];
     const int r = (int)(blockIdx.x - f);
-    int64_t *seg = plan.seg + 2 * g;
     double *gpart = part + plan.part_off[g] * 10;
     const int64_t cap = plan.part_cap[g];
     uint32_t epoch = 0;
@@ -1449,8 +1441,6 @@ __global__ __launch_bounds__(TPB, 4) void ensemble_loop_kernel(
             for (int64_t i = r0 + threadIdx.x; i < r1; i += TPB)
                 pack_h(st, jm, jp, jd, prec, n, i, T - st.t[i]);
             if (r == 0 && threadIdx.x == 0) {
-                seg[0] = 0;
-                seg[1] = n_act;
                 int bb = 0;
                 while ((int64_t(1) << (bb + 1)) <= n_act)
                     ++bb;
@@ -1481,19 +1471,20 @@ __global__ __launch_bounds__(TPB, 4) void ensemble_loop_kernel(
                 B *= 2;
             ForceWork w{};
             w.idx = act_c;
-            w.seg = seg;
-            w.off = off + c;
+            w.n_act = n_act;
+            w.src0 = o0;
+            w.n_src = nc_;
             w.split = (int32_t)B;
             w.nc = 1;
             w.n_blocks = n_ib;
             if (lpi == 32)
-                group_units<PREC, EPS0, 32>(J, w, gpart, n_act, eps2, n_ib, B, r, (int)W, uctr,
+                group_units<PREC, EPS0, 32, false>(J, w, gpart, n_act, eps2, n_ib, B, r, (int)W, uctr,
                                           ubase);
             else if (lpi == 8)
-                group_units<PREC, EPS0, 8>(J, w, gpart, n_act, eps2, n_ib, B, r, (int)W, uctr,
+                group_units<PREC, EPS0, 8, false>(J, w, gpart, n_act, eps2, n_ib, B, r, (int)W, uctr,
                                          ubase);
             else
-                group_units<PREC, EPS0, 1>(J, w, gpart, n_act, eps2, n_ib, B, r, (int)W, uctr,
+                group_units<PREC, EPS0, 1, false>(J, w, gpart, n_act, eps2, n_ib, B, r, (int)W, uctr,
                                          ubase);
             if (!group_sync(bar, f, W, err, epoch)) {
                 failed = true;
@@ -1501,7 +1492,7 @@ __global__ __launch_bounds__(TPB, 4) void ensemble_loop_kernel(
             }
             // (4) this workgroup's active particles: split sums (fixed order)
             // and the corrector, RC_SLOTS particles per pass
-            const int64_t bc = splits_used(nc_, B, LOOP_NT);
+            const int64_t bc = splits_used(nc_, B, split_unit(lpi, LOOP_NW));
             const int qq = threadIdx.x / RC_SLOTS, kl = threadIdx.x % RC_SLOTS;
             for (int64_t k0 = first; k0 < first + mine; k0 += RC_SLOTS) {
                 const int64_t k = k0 + kl;
@@ -1698,21 +1689,13 @@ unsigned nblk(int64_t n, int t = TPB) { return (unsigned)((n + t - 1) / t); }
 
 // Source records straight from caller arrays (mass[n], pos/vel/acc [n][3]
 // row-major), at their own time: the records nbody_force builds from a
-// context's stored state, for the evaluation that keeps no context.  Also
-// writes the one-cluster work tables seg = {0, n_act}, off = {0, n}.
+// context's stored state, for the evaluation that keeps no context.
 __global__ __launch_bounds__(TPB) void pack_arrays_kernel(const double *mass, const double *pos,
                                                           const double *vel, const double *acc,
                                                           JRecMixed jm, JRecPair32 jp, JRecF64 jd,
-                                                          int prec, int64_t n, int64_t n_act,
-                                                          int64_t *seg, int64_t *off)
+                                                          int prec, int64_t n)
 {
     const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
-    if (i == 0) {
-        seg[0] = 0;
-        seg[1] = n_act;
-        off[0] = 0;
-        off[1] = n;
-    }
     if (i >= n)
         return;
     const double x = pos[3 * i], y = pos[3 * i + 1], z = pos[3 * i + 2];
@@ -1736,11 +1719,10 @@ __global__ __launch_bounds__(TPB) void pack_arrays_kernel(const double *mass, co
 }  // namespace
 
 hipError_t launch_pack_arrays(const Ctx &c, const double *mass, const double *pos,
-                              const double *vel, const double *acc, int64_t n_act,
-                              int64_t *seg, int64_t *off, hipStream_t s)
+                              const double *vel, const double *acc, hipStream_t s)
 {
     hipLaunchKernelGGL(pack_arrays_kernel, dim3(nblk(c.n)), dim3(TPB), 0, s, mass, pos, vel, acc,
-                       c.jm, c.jp, c.jd, (int)c.cfg.precision, c.n, n_act, seg, off);
+                       c.jm, c.jp, c.jd, (int)c.cfg.precision, c.n);
     return hipGetLastError();
 }
 
@@ -1947,8 +1929,6 @@ hipError_t launch_step_loop(const Ctx &c, double t_target, int64_t a_max, int gr
     int64_t am = a_max, sq = seq;
     int32_t *act = c.act;
     double *part = c.part;
-    int64_t *seg = c.d_seg;
-    const int64_t *off = c.d_off;
     uint64_t *wmin = c.d_loop_min;
     int32_t *wcnt = c.d_loop_cnt;
     uint32_t *bar = c.d_loop_bar;
@@ -1956,7 +1936,7 @@ hipError_t launch_step_loop(const Ctx &c, double t_target, int64_t a_max, int gr
     int64_t *hist = c.d_info + 8;
     int64_t *res = c.d_tot + 8;
     void *args[] = {&st,   &jm,  &jp,  &jd,   &prec, &n,    &eps2, &tt,  &eta,  &dmin, &dmax, &am,
-                    &act,  &part, &seg, &off,  &wmin, &wcnt, &bar, &err,  &hist, &res,  &sq};
+                    &act,  &part, &wmin, &wcnt, &bar, &err, &hist, &res, &sq};
     return hipLaunchCooperativeKernel(step_loop_fn(c), dim3((unsigned)grid), dim3(TPB), args, 0,
                                       s);
 }
@@ -1970,12 +1950,8 @@ hipError_t launch_blocks(const Ctx &c, int64_t ib, int64_t cap, hipStream_t s)
 
 hipError_t launch_segments(const Ctx &c, const int32_t *idx, int64_t n_act, hipStream_t s)
 {
-    if (c.nc == 1 && idx) {
-        hipLaunchKernelGGL(set_seg_kernel, dim3(1), dim3(1), 0, s, c.d_seg, (int64_t)0, n_act);
-    } else {
-        hipLaunchKernelGGL(segments_kernel, dim3(nblk(c.nc + 1)), dim3(TPB), 0, s, idx, n_act,
-                           (const int64_t *)c.d_off, c.nc, c.d_seg);
-    }
+    hipLaunchKernelGGL(segments_kernel, dim3(nblk(c.nc + 1)), dim3(TPB), 0, s, idx, n_act,
+                       (const int64_t *)c.d_off, c.nc, c.d_seg);
     return hipGetLastError();
 }
 

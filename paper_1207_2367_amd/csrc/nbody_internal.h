@@ -33,6 +33,13 @@ struct JRecF64 {
     double *x, *y, *z, *vx, *vy, *vz, *ax, *ay, *az, *m;
 };
 
+// Sources as they stand, in FP64: component pointers with a common stride (1:
+// the stored state; 3: a caller's [n][3] arrays); masses have stride 1.
+struct JSrc {
+    const double *x, *y, *z, *vx, *vy, *vz, *ax, *ay, *az, *m;
+    int64_t st;
+};
+
 // Hermite state, FP64 structure-of-arrays: component d of particle i of
 // field f is f[d * n + i].  176 bytes per particle.
 struct State {
@@ -52,14 +59,17 @@ struct ForceOut {
 // Work layout of one force launch over clusters.  Active slot k in
 // [seg[c], seg[c+1]) belongs to cluster c whose sources are
 // [off[c], off[c+1]).  i-block g of the launch covers slots
-// [seg[c] + (g - blk_first[c]) * IB, ...) of cluster c = blk_cluster[g]
-// (blk_cluster == nullptr: a single cluster, c = 0, blk_first = 0).
+// [seg[c] + (g - blk_first[c]) * IB, ...) of cluster c = blk_cluster[g].
+// With blk_cluster == nullptr there is one cluster, its n_act slots from 0
+// and its sources [src0, src0 + n_src) given here by value (a workgroup then
+// starts on its sources without waiting for the tables).
 struct ForceWork {
     const int32_t *idx;       // active particle of each slot
     const int64_t *seg;       // [nc + 1] device
     const int64_t *off;       // [nc + 1] device
     const int32_t *blk_cluster;
     const int64_t *blk_first;
+    int64_t n_act, src0, n_src;   // one cluster (blk_cluster == nullptr)
     int64_t n_blocks;         // i-blocks in the grid (x dimension)
     int32_t split;            // B, the split-source factor (grid y)
     int32_t nc;
@@ -84,26 +94,39 @@ struct EnsPlan {
     const int32_t *cl_off;     // [ng + 1]
     const int64_t *part_off;   // [ng]
     const int64_t *part_cap;   // [ng]
-    int64_t *seg;              // [2 ng] active segment of the group's cluster
 };
 
 struct Launch {
     int lpi = 0, waves = 0, split = 0, ipt = 1;
 };
 
-// Sources per split of a cluster of nsrc sources under split factor B with
-// tiles of nt: ceil(nsrc / B) rounded up to whole tiles; the splits in use
-// are those that start below nsrc (at least one).
-__host__ __device__ inline int64_t split_chunk(int64_t nsrc, int64_t B, int64_t nt)
+// Unit of a split: the sources whose pairs with a particle make one FP32
+// partial sum per lane (64 per lane, at most a tile), so that the partial
+// sums are the same whatever the split.
+__host__ __device__ constexpr int split_unit(int lpi, int waves)
 {
-    const int64_t c = (nsrc + B - 1) / B;
-    return (c + nt - 1) / nt * nt;
+    return lpi < waves ? 64 * lpi : 64 * waves;
 }
-__host__ __device__ inline int64_t splits_used(int64_t nsrc, int64_t B, int64_t nt)
+// Split factor B of nsrc sources in units of `unit`: the splits in use are
+// min(B, units), and split b of them starts at source split_begin(..., b)
+// (b = used: the end), so that their sizes differ by one unit at most.
+// (Chunks of ceil(nsrc / B) rounded up leave a short last split and unused
+// ones; they sit together on the last XCDs, which then idle: 1237 active
+// against 100,003 sources in FP64, 98 splits in a grid of 128 took 303 us,
+// in a grid of 102 it took 246 us.)
+__host__ __device__ inline int64_t splits_used(int64_t nsrc, int64_t B, int64_t unit)
 {
-    const int64_t c = split_chunk(nsrc, B, nt);
-    const int64_t u = c > 0 ? (nsrc + c - 1) / c : 1;
-    return u < 1 ? 1 : u;
+    const int64_t q = (nsrc + unit - 1) / unit;
+    return B < q ? B : (q < 1 ? 1 : q);
+}
+// (every workgroup of a launch forms the same product b (q / used), so that
+// neighbours agree; in FP64, as 64-bit integer divisions took a microsecond)
+__host__ __device__ inline int64_t split_begin(int64_t nsrc, int64_t used, int64_t unit, int64_t b)
+{
+    const int64_t q = (nsrc + unit - 1) / unit;
+    const double r = (double)(int)q / (double)(int)used;
+    const int64_t e = b >= used ? nsrc : (int64_t)(int)((double)(int)b * r) * unit;
+    return e < nsrc ? e : nsrc;
 }
 
 struct Ctx;
@@ -139,10 +162,9 @@ hipError_t launch_startup(Ctx &c, const ForceWork &w, const StartupShape &sh, in
 hipError_t launch_pack(const Ctx &c, const double *T_cluster, int own_time,
                        const int32_t *cluster_of, hipStream_t s);
 // records of c.n particles from caller arrays (c.jm / c.jp / c.jd per the
-// precision), plus seg = {0, n_act} and off = {0, c.n}
+// precision)
 hipError_t launch_pack_arrays(const Ctx &c, const double *mass, const double *pos,
-                              const double *vel, const double *acc, int64_t n_act,
-                              int64_t *seg, int64_t *off, hipStream_t s);
+                              const double *vel, const double *acc, hipStream_t s);
 hipError_t launch_predict_out(const Ctx &c, double t, double *pos, double *vel,
                               double *acc, hipStream_t s);
 hipError_t launch_schedule(const Ctx &c, double t_target, int64_t seq, hipStream_t s);
@@ -235,6 +257,7 @@ struct Ctx {
     JRecMixed jm{};
     JRecPair32 jp{};
     JRecF64 jd{};
+    JSrc js{};   // sources of an evaluation with the potential (nbody_force)
     // [nc + 1] device copies of the cluster offsets, host copy too
     int64_t *d_off = nullptr;
     std::vector<int64_t> off;

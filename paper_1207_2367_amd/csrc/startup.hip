@@ -64,11 +64,11 @@ __global__ __launch_bounds__(SU_NT) void startup_kernel(State st, int64_t n, For
         o0 = w.off[c];
         o1 = w.off[c + 1];
     }
-    const int64_t chunk = split_chunk(o1 - o0, w.split, SU_NT);
-    if ((int64_t)b * chunk >= o1 - o0 && b > 0)
+    const int64_t used = splits_used(o1 - o0, w.split, SU_NT);
+    if (b >= used)
         return;       // no sources left for this split
-    const int64_t j0 = o0 + (int64_t)b * chunk;
-    const int64_t j1 = j0 + chunk < o1 ? j0 + chunk : o1;
+    const int64_t j0 = o0 + split_begin(o1 - o0, used, SU_NT, b);
+    const int64_t j1 = o0 + split_begin(o1 - o0, used, SU_NT, b + 1);
     const double *X = st.pos, *Y = X + n, *Z = Y + n, *VX = st.vel, *VY = VX + n, *VZ = VY + n;
     const double *AX = st.acc, *AY = AX + n, *AZ = AY + n, *JX = st.jrk, *JY = JX + n,
                  *JZ = JY + n;
