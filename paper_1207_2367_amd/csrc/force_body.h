@@ -12,6 +12,28 @@ namespace {
 // kernel variants: the two public mixed modes and the FP64 path
 constexpr int PREC_MIXED = 0, PREC_F64 = 1, PREC_PAIR32 = 4;
 
+// Accesses to data that the workgroups of a persistent launch exchange.  COH:
+// single accesses that are coherent over the device (relaxed atomics at agent
+// scope), so that a barrier between the workgroups needs only to wait for
+// them, not to write back and invalidate the XCDs' L2 caches; otherwise plain
+// ones (data of other launches, or of one workgroup).
+template <bool COH, typename T>
+__device__ __forceinline__ T ld(const T *p)
+{
+    if constexpr (COH)
+        return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else
+        return *p;
+}
+template <bool COH, typename T>
+__device__ __forceinline__ void put(T *p, T v)
+{
+    if constexpr (COH)
+        __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else
+        *p = v;
+}
+
 // Knuth's two-sum: (hi, lo) += p without rounding loss in the (hi, lo) pair.
 __device__ __forceinline__ void ds_add(float &hi, float &lo, float p)
 {
@@ -165,7 +187,7 @@ __device__ __forceinline__ int64_t rec_stride(const JSrc &J) { return J.st; }
 // does not need it (the energy has its own pass).  IPT: active particles
 // per lane group (each source read from LDS serves IPT pairs).
 template <int PREC, int LPI, int NW, bool EPS0, bool PHI, int IPT = 1, bool AHEAD = true,
-          typename R>
+          bool COH = false, typename R>
 __device__ __forceinline__ void force_block(const R &J, const ForceWork &w, const ForceOut &out,
                                             double *part, int64_t n_act_total, double eps2,
                                             int64_t g, int b)
@@ -232,9 +254,10 @@ __device__ __forceinline__ void force_block(const R &J, const ForceWork &w, cons
         Rec r;
         const int64_t jj = t0 + tid, e = jj * st;
         if (jj < j1) {
-            r.x = J.x[e]; r.y = J.y[e]; r.z = J.z[e]; r.m = J.m[jj];
-            r.vx = (VV)J.vx[e]; r.vy = (VV)J.vy[e]; r.vz = (VV)J.vz[e];
-            r.ax = (VA)J.ax[e]; r.ay = (VA)J.ay[e]; r.az = (VA)J.az[e];
+            r.x = ld<COH>(J.x + e); r.y = ld<COH>(J.y + e); r.z = ld<COH>(J.z + e);
+            r.m = ld<COH>(J.m + jj);
+            r.vx = (VV)ld<COH>(J.vx + e); r.vy = (VV)ld<COH>(J.vy + e); r.vz = (VV)ld<COH>(J.vz + e);
+            r.ax = (VA)ld<COH>(J.ax + e); r.ay = (VA)ld<COH>(J.ay + e); r.az = (VA)ld<COH>(J.az + e);
         } else {
             r.x = NULL_POS; r.y = NULL_POS; r.z = NULL_POS; r.m = 0.0;
             r.vx = 0; r.vy = 0; r.vz = 0;
@@ -256,7 +279,7 @@ __device__ __forceinline__ void force_block(const R &J, const ForceWork &w, cons
         k[u] = kb + il + u * NG;
         valid[u] = k[u] < s1;
         const int64_t kk = valid[u] ? k[u] : kb;
-        i[u] = w.idx ? (int64_t)w.idx[kk] : kk;
+        i[u] = w.idx ? (int64_t)ld<COH>(w.idx + kk) : kk;
         if (i[u] < o0 || i[u] >= o1) {
             // an index outside its cluster (a caller's bad list): skip the
             // slot, load a valid particle, report
@@ -266,9 +289,11 @@ __device__ __forceinline__ void force_block(const R &J, const ForceWork &w, cons
             i[u] = o0;
         }
         const int64_t e = i[u] * st;
-        xi[u] = J.x[e]; yi[u] = J.y[e]; zi[u] = J.z[e];
-        vxi[u] = (VV)J.vx[e]; vyi[u] = (VV)J.vy[e]; vzi[u] = (VV)J.vz[e];
-        axi[u] = (VA)J.ax[e]; ayi[u] = (VA)J.ay[e]; azi[u] = (VA)J.az[e];
+        xi[u] = ld<COH>(J.x + e); yi[u] = ld<COH>(J.y + e); zi[u] = ld<COH>(J.z + e);
+        vxi[u] = (VV)ld<COH>(J.vx + e); vyi[u] = (VV)ld<COH>(J.vy + e);
+        vzi[u] = (VV)ld<COH>(J.vz + e);
+        axi[u] = (VA)ld<COH>(J.ax + e); ayi[u] = (VA)ld<COH>(J.ay + e);
+        azi[u] = (VA)ld<COH>(J.az + e);
     }
 
     // the active particles' values are in registers from here on: without
@@ -489,7 +514,7 @@ __device__ __forceinline__ void force_block(const R &J, const ForceWork &w, cons
             double *pb = part + (int64_t)b * 10 * n_act_total + ku;
 #pragma unroll
             for (int q = 0; q < 10; ++q)
-                pb[(int64_t)q * n_act_total] = Q[q];
+                put<COH>(pb + (int64_t)q * n_act_total, Q[q]);
         } else {
 #pragma unroll
             for (int q = 0; q < 3; ++q)

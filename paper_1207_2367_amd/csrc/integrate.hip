@@ -80,6 +80,7 @@ __device__ uint32_t block_dt(double crit, double dt_old, double t_new, double t_
 // Taylor series of paper Sect. 3 item 1 (Horner form) to the source
 // records.  T is the block time of the particle's cluster, or its own time
 // (h = 0: the records are the stored state) when own_time is set.
+template <bool COH = false>
 __device__ __forceinline__ void pack_h(const State &st, const JRecMixed &jm,
                                        const JRecPair32 &jp, const JRecF64 &jd, int prec,
                                        int64_t n, int64_t i, double h);
@@ -125,22 +126,25 @@ __device__ __forceinline__ PredIn load_pred(const State &st, int64_t n, int64_t 
     return q;
 }
 
+template <bool COH>
 __device__ __forceinline__ void store_pred(const PredIn &q, const JRecMixed &jm,
                                            const JRecPair32 &jp, const JRecF64 &jd, int prec,
                                            int64_t i, double h);
 
 // the records of particle i advanced by h from its own time
+template <bool COH>
 __device__ __forceinline__ void pack_h(const State &st, const JRecMixed &jm,
                                        const JRecPair32 &jp, const JRecF64 &jd, int prec,
                                        int64_t n, int64_t i, double h)
 {
-    store_pred(load_pred(st, n, i), jm, jp, jd, prec, i, h);
+    store_pred<COH>(load_pred(st, n, i), jm, jp, jd, prec, i, h);
 }
 
 // the records of the particles [r0, r1) of one workgroup advanced to T, two
 // particles per lane and pass with all loads of both issued before either
 // particle's stores (the stores could alias the loads as far as the
 // compiler knows, so it would not overlap two passes by itself)
+template <bool COH>
 __device__ __forceinline__ void pack_range(const State &st, const JRecMixed &jm,
                                            const JRecPair32 &jp, const JRecF64 &jd, int prec,
                                            int64_t n, int64_t r0, int64_t r1, double T)
@@ -152,12 +156,13 @@ __device__ __forceinline__ void pack_range(const State &st, const JRecMixed &jm,
         PredIn b{};
         if (two)
             b = load_pred(st, n, i2);
-        store_pred(a, jm, jp, jd, prec, i, T - a.t);
+        store_pred<COH>(a, jm, jp, jd, prec, i, T - a.t);
         if (two)
-            store_pred(b, jm, jp, jd, prec, i2, T - b.t);
+            store_pred<COH>(b, jm, jp, jd, prec, i2, T - b.t);
     }
 }
 
+template <bool COH>
 __device__ __forceinline__ void store_pred(const PredIn &q, const JRecMixed &jm,
                                            const JRecPair32 &jp, const JRecF64 &jd, int prec,
                                            int64_t i, double h)
@@ -173,20 +178,20 @@ __device__ __forceinline__ void store_pred(const PredIn &q, const JRecMixed &jm,
     }
     const double m = q.m;
     if (prec == NBODY_PREC_MIXED) {
-        jm.x[i] = xp[0]; jm.y[i] = xp[1]; jm.z[i] = xp[2];
-        jm.vx[i] = vp[0]; jm.vy[i] = vp[1]; jm.vz[i] = vp[2];
-        jm.ax[i] = (float)ap[0]; jm.ay[i] = (float)ap[1]; jm.az[i] = (float)ap[2];
-        jm.m[i] = m;
+        put<COH>(jm.x + i, xp[0]); put<COH>(jm.y + i, xp[1]); put<COH>(jm.z + i, xp[2]);
+        put<COH>(jm.vx + i, vp[0]); put<COH>(jm.vy + i, vp[1]); put<COH>(jm.vz + i, vp[2]);
+        put<COH>(jm.ax + i, (float)ap[0]); put<COH>(jm.ay + i, (float)ap[1]); put<COH>(jm.az + i, (float)ap[2]);
+        put<COH>(jm.m + i, m);
     } else if (prec == NBODY_PREC_FP32PAIR) {
-        jp.x[i] = xp[0]; jp.y[i] = xp[1]; jp.z[i] = xp[2];
-        jp.vx[i] = (float)vp[0]; jp.vy[i] = (float)vp[1]; jp.vz[i] = (float)vp[2];
-        jp.ax[i] = (float)ap[0]; jp.ay[i] = (float)ap[1]; jp.az[i] = (float)ap[2];
-        jp.m[i] = m;
+        put<COH>(jp.x + i, xp[0]); put<COH>(jp.y + i, xp[1]); put<COH>(jp.z + i, xp[2]);
+        put<COH>(jp.vx + i, (float)vp[0]); put<COH>(jp.vy + i, (float)vp[1]); put<COH>(jp.vz + i, (float)vp[2]);
+        put<COH>(jp.ax + i, (float)ap[0]); put<COH>(jp.ay + i, (float)ap[1]); put<COH>(jp.az + i, (float)ap[2]);
+        put<COH>(jp.m + i, m);
     } else {
-        jd.x[i] = xp[0]; jd.y[i] = xp[1]; jd.z[i] = xp[2];
-        jd.vx[i] = vp[0]; jd.vy[i] = vp[1]; jd.vz[i] = vp[2];
-        jd.ax[i] = ap[0]; jd.ay[i] = ap[1]; jd.az[i] = ap[2];
-        jd.m[i] = m;
+        put<COH>(jd.x + i, xp[0]); put<COH>(jd.y + i, xp[1]); put<COH>(jd.z + i, xp[2]);
+        put<COH>(jd.vx + i, vp[0]); put<COH>(jd.vy + i, vp[1]); put<COH>(jd.vz + i, vp[2]);
+        put<COH>(jd.ax + i, ap[0]); put<COH>(jd.ay + i, ap[1]); put<COH>(jd.az + i, ap[2]);
+        put<COH>(jd.m + i, m);
     }
 }
 
@@ -449,6 +454,7 @@ __global__ __launch_bounds__(1024) void sched_scan(const uint64_t *cmin, const i
 }
 
 // ordered compaction of the due particles of each chunk
+template <bool COH = false>
 __device__ __forceinline__ void scatter_range(const double *t, const double *dt, double T,
                                               int64_t b, int64_t e, int64_t pos, int32_t *act);
 
@@ -465,6 +471,7 @@ __device__ __forceinline__ void scatter_chunk(const double *t, const double *dt,
 }
 
 // the due particles of [b, e) in ascending order to act[pos ...]
+template <bool COH>
 __device__ __forceinline__ void scatter_range(const double *t, const double *dt, double T,
                                               int64_t b, int64_t e, int64_t pos, int32_t *act)
 {
@@ -484,7 +491,7 @@ __device__ __forceinline__ void scatter_range(const double *t, const double *dt,
             tot += wsum[w];
         }
         if (f)
-            act[pos + woff + before] = (int32_t)i;
+            put<COH>(act + pos + woff + before, (int32_t)i);
         pos += tot;
         __syncthreads();
     }
@@ -922,6 +929,7 @@ constexpr int RC_SLOTS = TPB / 9;
 
 // sum of bc split partials p[0], p[stride], ... in the order b = 0 .. bc-1,
 // 16 loads in flight
+template <bool COH = false>
 __device__ __forceinline__ double sum_splits(const double *p, int64_t stride, int64_t bc)
 {
     constexpr int U = 16;
@@ -931,13 +939,13 @@ __device__ __forceinline__ double sum_splits(const double *p, int64_t stride, in
         double v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            v[u] = p[(b + u) * stride];
+            v[u] = ld<COH>(p + (b + u) * stride);
 #pragma unroll
         for (int u = 0; u < U; ++u)
             r += v[u];
     }
     for (; b < bc; ++b)
-        r += p[b * stride];
+        r += ld<COH>(p + b * stride);
     return r;
 }
 
@@ -1033,20 +1041,20 @@ constexpr uint32_t LOOP_SPINS = 1u << 21;                 // barrier wait bound 
 
 // Barrier over the workgroups [f, f + W) of a cooperative launch: one
 // arrival counter (bar[LOOP_FLAG * f], monotonic within a launch) and one
-// generation word (bar[LOOP_FLAG * (f + 1)], its own 128-byte line).  Each
-// workgroup releases its writes (agent-scope release fence) and adds 1 to the
-// counter; the arrival that brings it to e W (epoch e, uint32 arithmetic,
-// so it wraps consistently) acquires the others' writes and stores e into
-// the generation word with release order; the others poll that word and
-// acquire once it holds e or later.  One release and one acquire per
-// workgroup and barrier: the fences (which write back / invalidate the
-// XCD's L2) are what a barrier costs here, about 1.1 us at W = 16 and growing
-// with W (measured: 3.3 us at W = 64, 11 us at 256, against 6.9 and 26 us
-// for one flag per workgroup polled by every workgroup with two full fences
-// each).  A wait longer than LOOP_SPINS polls sets ERR_LOOP and returns
-// false (the workgroup then leaves the loop; the others follow at their next
-// barrier), so no wave waits forever.  Epochs start at 1 in every launch;
-// the host clears the words before it.
+// generation word (bar[LOOP_FLAG * (f + 1)], its own 128-byte line).  Every
+// wave waits for its own accesses, then each workgroup adds 1 to the counter;
+// the arrival that brings it to e W (epoch e, uint32 arithmetic, so it wraps
+// consistently) stores e into the generation word, which the others poll.
+// What the workgroups exchange between barriers goes through coherent
+// accesses (ld / put with COH), which have reached the device's coherence
+// point when the wait ends; everything else a workgroup reads is its own or
+// constant for the launch.  So no cache is written back or invalidated: with
+// a release and an acquire fence per workgroup the barrier took 3.3 us at
+// W = 64, without 1.8 us (the probe's lower bound), and the workgroups' own
+// state stays in L2.  A wait longer than LOOP_SPINS polls sets ERR_LOOP and
+// returns false (the workgroup then leaves the loop; the others follow at
+// their next barrier), so no wave waits forever.  Epochs start at 1 in every
+// launch; the host clears the words before it.
 constexpr int LOOP_FLAG = 32;   // uint32 words per line
 __device__ __forceinline__ bool group_sync(uint32_t *bar, uint32_t f, uint32_t W, uint32_t *err,
                                            uint32_t &epoch)
@@ -1057,16 +1065,15 @@ __device__ __forceinline__ bool group_sync(uint32_t *bar, uint32_t f, uint32_t W
     }
     __shared__ int ok;
     const uint32_t e = ++epoch;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) {
         ok = 1;
         uint32_t *cnt = bar + LOOP_FLAG * f, *gen = bar + LOOP_FLAG * (f + 1);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         const uint32_t old = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED,
                                                     __HIP_MEMORY_SCOPE_AGENT);
         if (old == e * W - 1u) {
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-            __hip_atomic_store(gen, e, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(gen, e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else {
             uint32_t spins = 0;
             while ((int32_t)(__hip_atomic_load(gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) -
@@ -1079,7 +1086,6 @@ __device__ __forceinline__ bool group_sync(uint32_t *bar, uint32_t f, uint32_t W
                 }
             }
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
     __syncthreads();
     return ok != 0;
@@ -1172,7 +1178,7 @@ __device__ __forceinline__ const typename Smem<PREC>::R &loop_records(const JRec
 // is never reset: each pass advances it by the units plus one failed take
 // per workgroup, which every workgroup of the group adds to *base alike.
 // Which workgroup evaluates a unit does not change its partial sums.
-template <int PREC, bool EPS0, int LPI, bool AHEAD>
+template <int PREC, bool EPS0, int LPI, bool AHEAD, bool COH>
 __device__ __forceinline__ void group_units(const typename Smem<PREC>::R &J, const ForceWork &w,
                                           double *part, int64_t n_act, double eps2, int64_t n_ib,
                                           int64_t B, int r, int W, uint32_t *ctr,
@@ -1182,7 +1188,7 @@ __device__ __forceinline__ void group_units(const typename Smem<PREC>::R &J, con
     const int64_t units = n_ib * B;
     if (W == 1 || !ctr) {   // alone, or no counter: round-robin
         for (int64_t u = r; u < units; u += W)
-            force_block<PREC, LPI, LOOP_NW, EPS0, false, 1, AHEAD>(J, w, none, part, n_act, eps2, u % n_ib,
+            force_block<PREC, LPI, LOOP_NW, EPS0, false, 1, AHEAD, COH>(J, w, none, part, n_act, eps2, u % n_ib,
                                                           (int)(u / n_ib));
         return;
     }
@@ -1195,7 +1201,7 @@ __device__ __forceinline__ void group_units(const typename Smem<PREC>::R &J, con
         __syncthreads();
         if (u >= units)
             break;
-        force_block<PREC, LPI, LOOP_NW, EPS0, false, 1, AHEAD>(J, w, none, part, n_act, eps2, u % n_ib,
+        force_block<PREC, LPI, LOOP_NW, EPS0, false, 1, AHEAD, COH>(J, w, none, part, n_act, eps2, u % n_ib,
                                                       (int)(u / n_ib));
     }
     base += (uint32_t)(units + W);
@@ -1229,8 +1235,8 @@ __global__ __launch_bounds__(TPB) void step_loop_kernel(
     int cnt;
     range_min_count(st.t, st.dt, r0, r1, v, cnt);
     if (threadIdx.x == 0) {
-        wmin[blockIdx.x] = v;
-        wcnt[blockIdx.x] = cnt;
+        put<true>(wmin + blockIdx.x, v);
+        put<true>(wcnt + blockIdx.x, cnt);
     }
     for (;;) {
         if (!grid_sync(bar, G, err, epoch)) {
@@ -1240,20 +1246,21 @@ __global__ __launch_bounds__(TPB) void step_loop_kernel(
         // (2) block time, N_act and this workgroup's offset, everywhere alike
         uint64_t tv = ~0ull;
         for (uint32_t w = threadIdx.x; w < G; w += TPB) {
-            const uint64_t x = wmin[w];
+            const uint64_t x = ld<true>(wmin + w);
             tv = x < tv ? x : tv;
         }
         const uint64_t T_bits = block_min_u64(tv);
         int64_t tot = 0, before = 0;
         for (uint32_t w = threadIdx.x; w < G; w += TPB)
-            if (wmin[w] == T_bits) {
-                tot += wcnt[w];
-                before += w < blockIdx.x ? wcnt[w] : 0;
+            if (ld<true>(wmin + w) == T_bits) {
+                const int k = ld<true>(wcnt + w);
+                tot += k;
+                before += w < blockIdx.x ? k : 0;
             }
         const int64_t n_act = block_sum_i64(tot);
         const int64_t first = block_sum_i64(before);
         const double T = __longlong_as_double((long long)T_bits);
-        if (*(volatile uint32_t *)err != 0)
+        if (ld<true>(err) != 0)
             reason = LOOP_ERR;
         else if (n_act == 0 || !(T <= t_target))
             reason = LOOP_DONE;
@@ -1263,10 +1270,12 @@ __global__ __launch_bounds__(TPB) void step_loop_kernel(
             stop_n = n_act;
             break;
         }
-        const int64_t mine = wmin[blockIdx.x] == T_bits ? (int64_t)wcnt[blockIdx.x] : 0;
+        const int64_t mine = ld<true>(wmin + blockIdx.x) == T_bits
+                                 ? (int64_t)ld<true>(wcnt + blockIdx.x)
+                                 : 0;
         if (mine > 0)
-            scatter_range(st.t, st.dt, T, r0, r1, first, act);
-        pack_range(st, jm, jp, jd, prec, n, r0, r1, T);
+            scatter_range<true>(st.t, st.dt, T, r0, r1, first, act);
+        pack_range<true>(st, jm, jp, jd, prec, n, r0, r1, T);
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             int bb = 0;
             while ((int64_t(1) << (bb + 1)) <= n_act)
@@ -1300,13 +1309,13 @@ __global__ __launch_bounds__(TPB) void step_loop_kernel(
         w.nc = 1;
         w.n_blocks = n_ib;
         if (lpi == 32)
-            group_units<PREC, EPS0, 32, true>(J, w, part, n_act, eps2, n_ib, B, (int)blockIdx.x, (int)G,
+            group_units<PREC, EPS0, 32, true, true>(J, w, part, n_act, eps2, n_ib, B, (int)blockIdx.x, (int)G,
                                         uctr, ubase);
         else if (lpi == 8)
-            group_units<PREC, EPS0, 8, true>(J, w, part, n_act, eps2, n_ib, B, (int)blockIdx.x, (int)G,
+            group_units<PREC, EPS0, 8, true, true>(J, w, part, n_act, eps2, n_ib, B, (int)blockIdx.x, (int)G,
                                        uctr, ubase);
         else
-            group_units<PREC, EPS0, 1, true>(J, w, part, n_act, eps2, n_ib, B, (int)blockIdx.x, (int)G,
+            group_units<PREC, EPS0, 1, true, true>(J, w, part, n_act, eps2, n_ib, B, (int)blockIdx.x, (int)G,
                                        uctr, ubase);
         if (!grid_sync(bar, G, err, epoch)) {
             reason = LOOP_ERR;
@@ -1322,15 +1331,15 @@ __global__ __launch_bounds__(TPB) void step_loop_kernel(
             const bool corr = threadIdx.x < RC_SLOTS && in;
             OldState o{};
             if (corr)
-                o = load_old(st, n, act[k]);
+                o = load_old(st, n, ld<true>(act + k));
             if (q < 9 && in)
-                sum[q][kl] = sum_splits(part + (int64_t)q * n_act + k, 10 * n_act, bc);
+                sum[q][kl] = sum_splits<true>(part + (int64_t)q * n_act + k, 10 * n_act, bc);
             __syncthreads();
             if (corr) {
                 const double a1[3] = {sum[0][kl], sum[1][kl], sum[2][kl]};
                 const double j1[3] = {sum[3][kl], sum[4][kl], sum[5][kl]};
                 const double s1[3] = {sum[6][kl], sum[7][kl], sum[8][kl]};
-                correct_loaded(st, n, act[k], o, a1, j1, s1, t_target, eta, dt_min, dt_max,
+                correct_loaded(st, n, ld<true>(act + k), o, a1, j1, s1, t_target, eta, dt_min, dt_max,
                                err);
             }
             __syncthreads();
@@ -1338,8 +1347,8 @@ __global__ __launch_bounds__(TPB) void step_loop_kernel(
         // (1) of the next step, over the range this workgroup just updated
         range_min_count(st.t, st.dt, r0, r1, v, cnt);
         if (threadIdx.x == 0) {
-            wmin[blockIdx.x] = v;
-            wcnt[blockIdx.x] = cnt;
+            put<true>(wmin + blockIdx.x, v);
+            put<true>(wcnt + blockIdx.x, cnt);
         }
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -1370,8 +1379,10 @@ __global__ __launch_bounds__(TPB) void step_loop_kernel(
 // res (device): [0] sum of N_act, [1] sum of N_act * N_c, [2] largest number
 // of block steps of a cluster (the number of batched block steps of the
 // host-sized path)
-template <int PREC, bool EPS0>
-__global__ __launch_bounds__(TPB, 4) void ensemble_loop_kernel(
+// COH: the group has several workgroups, which exchange through coherent
+// accesses (see ld and group_sync); one workgroup uses plain ones.
+template <int PREC, bool EPS0, bool COH>
+__device__ __forceinline__ void ensemble_group(
     State st, JRecMixed jm, JRecPair32 jp, JRecF64 jd, int prec, int64_t n, double eps2,
     double t_target, double eta, double dt_min, double dt_max, int32_t *act, double *part,
     const int64_t *off, EnsPlan plan, uint64_t *wmin, int32_t *wcnt, uint32_t *bar,
@@ -1403,8 +1414,8 @@ __global__ __launch_bounds__(TPB, 4) void ensemble_loop_kernel(
         int cnt;
         range_min_count(st.t, st.dt, r0, r1, v, cnt);
         if (threadIdx.x == 0) {
-            wm[blockIdx.x] = v;
-            wc[blockIdx.x] = cnt;
+            put<COH>(wm + blockIdx.x, v);
+            put<COH>(wc + blockIdx.x, cnt);
         }
         for (;;) {
             if (!group_sync(bar, f, W, err, epoch)) {
@@ -1414,32 +1425,35 @@ __global__ __launch_bounds__(TPB, 4) void ensemble_loop_kernel(
             // (2) block time, N_act and this workgroup's offset, alike in the group
             uint64_t tv = ~0ull;
             for (uint32_t k = threadIdx.x; k < W; k += TPB) {
-                const uint64_t x = wm[f + k];
+                const uint64_t x = ld<COH>(wm + f + k);
                 tv = x < tv ? x : tv;
             }
             const uint64_t T_bits = block_min_u64(tv);
             int64_t tot = 0, before = 0;
             for (uint32_t k = threadIdx.x; k < W; k += TPB)
-                if (wm[f + k] == T_bits) {
-                    tot += wc[f + k];
-                    before += (int)k < r ? wc[f + k] : 0;
+                if (ld<COH>(wm + f + k) == T_bits) {
+                    const int kc = ld<COH>(wc + f + k);
+                    tot += kc;
+                    before += (int)k < r ? kc : 0;
                 }
             const int64_t n_act = block_sum_i64(tot);
             const int64_t first = block_sum_i64(before);
             const double T = __longlong_as_double((long long)T_bits);
-            if (*(volatile uint32_t *)err != 0) {
+            if (ld<true>(err) != 0) {
                 failed = true;
                 break;
             }
             if (n_act == 0 || !(T <= t_target))
                 break;
-            const int64_t mine = wm[blockIdx.x] == T_bits ? (int64_t)wc[blockIdx.x] : 0;
+            const int64_t mine = ld<COH>(wm + blockIdx.x) == T_bits
+                                     ? (int64_t)ld<COH>(wc + blockIdx.x)
+                                     : 0;
             if (mine > 0)
-                scatter_range(st.t, st.dt, T, r0, r1, first, act_c);
+                scatter_range<COH>(st.t, st.dt, T, r0, r1, first, act_c);
             // one particle per lane and pass: the kernel is held to 128
             // registers, and two in flight would spill
             for (int64_t i = r0 + threadIdx.x; i < r1; i += TPB)
-                pack_h(st, jm, jp, jd, prec, n, i, T - st.t[i]);
+                pack_h<COH>(st, jm, jp, jd, prec, n, i, T - st.t[i]);
             if (r == 0 && threadIdx.x == 0) {
                 int bb = 0;
                 while ((int64_t(1) << (bb + 1)) <= n_act)
@@ -1478,13 +1492,13 @@ __global__ __launch_bounds__(TPB, 4) void ensemble_loop_kernel(
             w.nc = 1;
             w.n_blocks = n_ib;
             if (lpi == 32)
-                group_units<PREC, EPS0, 32, false>(J, w, gpart, n_act, eps2, n_ib, B, r, (int)W, uctr,
+                group_units<PREC, EPS0, 32, false, COH>(J, w, gpart, n_act, eps2, n_ib, B, r, (int)W, uctr,
                                           ubase);
             else if (lpi == 8)
-                group_units<PREC, EPS0, 8, false>(J, w, gpart, n_act, eps2, n_ib, B, r, (int)W, uctr,
+                group_units<PREC, EPS0, 8, false, COH>(J, w, gpart, n_act, eps2, n_ib, B, r, (int)W, uctr,
                                          ubase);
             else
-                group_units<PREC, EPS0, 1, false>(J, w, gpart, n_act, eps2, n_ib, B, r, (int)W, uctr,
+                group_units<PREC, EPS0, 1, false, COH>(J, w, gpart, n_act, eps2, n_ib, B, r, (int)W, uctr,
                                          ubase);
             if (!group_sync(bar, f, W, err, epoch)) {
                 failed = true;
@@ -1500,15 +1514,15 @@ __global__ __launch_bounds__(TPB, 4) void ensemble_loop_kernel(
                 const bool corr = threadIdx.x < RC_SLOTS && in;
                 OldState o{};
                 if (corr)
-                    o = load_old(st, n, act_c[k]);
+                    o = load_old(st, n, ld<COH>(act_c + k));
                 if (qq < 9 && in)
-                    sum[qq][kl] = sum_splits(gpart + (int64_t)qq * n_act + k, 10 * n_act, bc);
+                    sum[qq][kl] = sum_splits<COH>(gpart + (int64_t)qq * n_act + k, 10 * n_act, bc);
                 __syncthreads();
                 if (corr) {
                     const double a1[3] = {sum[0][kl], sum[1][kl], sum[2][kl]};
                     const double j1[3] = {sum[3][kl], sum[4][kl], sum[5][kl]};
                     const double s1[3] = {sum[6][kl], sum[7][kl], sum[8][kl]};
-                    correct_loaded(st, n, act_c[k], o, a1, j1, s1, t_target, eta, dt_min,
+                    correct_loaded(st, n, ld<COH>(act_c + k), o, a1, j1, s1, t_target, eta, dt_min,
                                    dt_max, err);
                 }
                 __syncthreads();
@@ -1516,8 +1530,8 @@ __global__ __launch_bounds__(TPB, 4) void ensemble_loop_kernel(
             // (1) of the next step, over the range this workgroup just updated
             range_min_count(st.t, st.dt, r0, r1, v, cnt);
             if (threadIdx.x == 0) {
-                wm[blockIdx.x] = v;
-                wc[blockIdx.x] = cnt;
+                put<COH>(wm + blockIdx.x, v);
+                put<COH>(wc + blockIdx.x, cnt);
             }
         }
         steps_max = steps > steps_max ? steps : steps_max;
@@ -1527,6 +1541,23 @@ __global__ __launch_bounds__(TPB, 4) void ensemble_loop_kernel(
         atomicAdd(&res[1], (unsigned long long)pairs);
         atomicMax(&res[2], (unsigned long long)steps_max);
     }
+}
+
+template <int PREC, bool EPS0>
+__global__ __launch_bounds__(TPB, 4) void ensemble_loop_kernel(
+    State st, JRecMixed jm, JRecPair32 jp, JRecF64 jd, int prec, int64_t n, double eps2,
+    double t_target, double eta, double dt_min, double dt_max, int32_t *act, double *part,
+    const int64_t *off, EnsPlan plan, uint64_t *wmin, int32_t *wcnt, uint32_t *bar,
+    uint32_t *err, int64_t *hist, unsigned long long *res)
+{
+    if (plan.size[plan.grp_of[blockIdx.x]] > 1)
+        ensemble_group<PREC, EPS0, true>(st, jm, jp, jd, prec, n, eps2, t_target, eta, dt_min,
+                                         dt_max, act, part, off, plan, wmin, wcnt, bar, err, hist,
+                                         res);
+    else
+        ensemble_group<PREC, EPS0, false>(st, jm, jp, jd, prec, n, eps2, t_target, eta, dt_min,
+                                          dt_max, act, part, off, plan, wmin, wcnt, bar, err,
+                                          hist, res);
 }
 
 // first step after the start-up evaluation: the generalized criterion at
