@@ -1125,35 +1125,54 @@ __device__ __forceinline__ void range_min_count(const double *t, const double *d
     __syncthreads();
 }
 
-// workgroup-wide minimum / sum, returned to every lane
-__device__ __forceinline__ uint64_t block_min_u64(uint64_t v)
+// Decision of a block step from the results of a group's W <= 256 workgroups
+// (their minima of t + dt and how many particles reach them): the block time
+// (as bits), the active particles in all and in the workgroups before r.
+// Every wave reads all of them and forms the same result, so that no
+// workgroup barrier and no second read is needed.
+struct Decision {
+    uint64_t T;
+    int n_act, first, mine;
+};
+template <bool COH>
+__device__ __forceinline__ Decision decide(const uint64_t *wmin, const int32_t *wcnt, uint32_t W,
+                                           uint32_t r)
 {
-    __shared__ uint64_t r[TPB / 64];
-    v = wave_min_u64(v);
-    if ((threadIdx.x & 63) == 0)
-        r[threadIdx.x >> 6] = v;
-    __syncthreads();
-    uint64_t m = r[0];
-    for (int w = 1; w < TPB / 64; ++w)
-        m = r[w] < m ? r[w] : m;
-    __syncthreads();
-    return m;
-}
-
-__device__ __forceinline__ int64_t block_sum_i64(int64_t v)
-{
-    __shared__ int64_t r[TPB / 64];
+    constexpr int K = ENS_GROUP_MAX / 64;
+    const uint32_t lane = threadIdx.x & 63;
+    uint64_t v[K];
+    int c[K];
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1)
-        v += __shfl_xor(v, m, 64);
-    if ((threadIdx.x & 63) == 0)
-        r[threadIdx.x >> 6] = v;
-    __syncthreads();
-    int64_t s = 0;
-    for (int w = 0; w < TPB / 64; ++w)
-        s += r[w];
-    __syncthreads();
-    return s;
+    for (int k = 0; k < K; ++k) {
+        const uint32_t w = lane + 64 * k;
+        v[k] = w < W ? ld<COH>(wmin + w) : ~0ull;
+        c[k] = w < W ? ld<COH>(wcnt + w) : 0;
+    }
+    Decision d;
+    uint64_t t = v[0];
+#pragma unroll
+    for (int k = 1; k < K; ++k)
+        t = v[k] < t ? v[k] : t;
+    d.T = wave_min_u64(t);
+    int tot = 0, before = 0, mine = 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const uint32_t w = lane + 64 * k;
+        const int n = w < W && v[k] == d.T ? c[k] : 0;
+        tot += n;
+        before += w < r ? n : 0;
+        mine += w == r ? n : 0;
+    }
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) {
+        tot += __shfl_xor(tot, m, 64);
+        before += __shfl_xor(before, m, 64);
+        mine += __shfl_xor(mine, m, 64);
+    }
+    d.n_act = __builtin_amdgcn_readfirstlane(tot);
+    d.first = __builtin_amdgcn_readfirstlane(before);
+    d.mine = __builtin_amdgcn_readfirstlane(mine);
+    return d;
 }
 
 template <int PREC>
@@ -1170,8 +1189,9 @@ __device__ __forceinline__ const typename Smem<PREC>::R &loop_records(const JRec
 }
 
 // A group's evaluation units (i-block u % n_ib against split u / n_ib).  A
-// workgroup alone takes them in order (without a counter, workgroup r of W
-// takes every W-th from r); in a group of several, each
+// workgroup alone takes them in order (without a counter, or with no more
+// units than workgroups, workgroup r of W takes every W-th from r: a counter
+// costs two round trips to memory); in a group of several, each
 // workgroup takes the next unit from the group's counter (*ctr, one atomic
 // add per unit) until none is left, so that a workgroup slowed by its
 // neighbours on the compute unit does not hold the others up.  The counter
@@ -1186,7 +1206,7 @@ __device__ __forceinline__ void group_units(const typename Smem<PREC>::R &J, con
 {
     const ForceOut none{};
     const int64_t units = n_ib * B;
-    if (W == 1 || !ctr) {   // alone, or no counter: round-robin
+    if (W == 1 || !ctr || units <= W) {   // alone, no counter, or one unit each
         for (int64_t u = r; u < units; u += W)
             force_block<PREC, LPI, LOOP_NW, EPS0, false, 1, AHEAD, COH>(J, w, none, part, n_act, eps2, u % n_ib,
                                                           (int)(u / n_ib));
@@ -1244,22 +1264,9 @@ __global__ __launch_bounds__(TPB) void step_loop_kernel(
             break;
         }
         // (2) block time, N_act and this workgroup's offset, everywhere alike
-        uint64_t tv = ~0ull;
-        for (uint32_t w = threadIdx.x; w < G; w += TPB) {
-            const uint64_t x = ld<true>(wmin + w);
-            tv = x < tv ? x : tv;
-        }
-        const uint64_t T_bits = block_min_u64(tv);
-        int64_t tot = 0, before = 0;
-        for (uint32_t w = threadIdx.x; w < G; w += TPB)
-            if (ld<true>(wmin + w) == T_bits) {
-                const int k = ld<true>(wcnt + w);
-                tot += k;
-                before += w < blockIdx.x ? k : 0;
-            }
-        const int64_t n_act = block_sum_i64(tot);
-        const int64_t first = block_sum_i64(before);
-        const double T = __longlong_as_double((long long)T_bits);
+        const Decision dec = decide<true>(wmin, wcnt, G, blockIdx.x);
+        const int64_t n_act = dec.n_act, first = dec.first, mine = dec.mine;
+        const double T = __longlong_as_double((long long)dec.T);
         if (ld<true>(err) != 0)
             reason = LOOP_ERR;
         else if (n_act == 0 || !(T <= t_target))
@@ -1270,9 +1277,6 @@ __global__ __launch_bounds__(TPB) void step_loop_kernel(
             stop_n = n_act;
             break;
         }
-        const int64_t mine = ld<true>(wmin + blockIdx.x) == T_bits
-                                 ? (int64_t)ld<true>(wcnt + blockIdx.x)
-                                 : 0;
         if (mine > 0)
             scatter_range<true>(st.t, st.dt, T, r0, r1, first, act);
         pack_range<true>(st, jm, jp, jd, prec, n, r0, r1, T);
@@ -1423,31 +1427,15 @@ __device__ __forceinline__ void ensemble_group(
                 break;
             }
             // (2) block time, N_act and this workgroup's offset, alike in the group
-            uint64_t tv = ~0ull;
-            for (uint32_t k = threadIdx.x; k < W; k += TPB) {
-                const uint64_t x = ld<COH>(wm + f + k);
-                tv = x < tv ? x : tv;
-            }
-            const uint64_t T_bits = block_min_u64(tv);
-            int64_t tot = 0, before = 0;
-            for (uint32_t k = threadIdx.x; k < W; k += TPB)
-                if (ld<COH>(wm + f + k) == T_bits) {
-                    const int kc = ld<COH>(wc + f + k);
-                    tot += kc;
-                    before += (int)k < r ? kc : 0;
-                }
-            const int64_t n_act = block_sum_i64(tot);
-            const int64_t first = block_sum_i64(before);
-            const double T = __longlong_as_double((long long)T_bits);
+            const Decision dec = decide<COH>(wm + f, wc + f, W, (uint32_t)r);
+            const int64_t n_act = dec.n_act, first = dec.first, mine = dec.mine;
+            const double T = __longlong_as_double((long long)dec.T);
             if (ld<true>(err) != 0) {
                 failed = true;
                 break;
             }
             if (n_act == 0 || !(T <= t_target))
                 break;
-            const int64_t mine = ld<COH>(wm + blockIdx.x) == T_bits
-                                     ? (int64_t)ld<COH>(wc + blockIdx.x)
-                                     : 0;
             if (mine > 0)
                 scatter_range<COH>(st.t, st.dt, T, r0, r1, first, act_c);
             // one particle per lane and pass: the kernel is held to 128
