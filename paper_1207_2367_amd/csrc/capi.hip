@@ -749,9 +749,11 @@ int levels_ready(Ctx &c, bool *ok)
 
 // one block step; fills n_act / t_block and adds to stats.  levels: the
 // schedule comes from the per-level counts (levels_ready said so), which
-// the corrector keeps up to date
+// the corrector keeps up to date; *ahead is then the sequence number of this
+// block's schedule if the last block's corrector already made it (else 0),
+// and is set for the next one
 int block_step(Ctx &c, double t_target, int64_t *n_act_out, double *t_block_out,
-               nbody_step_stats *stats, bool levels)
+               nbody_step_stats *stats, bool levels, int64_t *ahead)
 {
     // the host needs N_act (and the block time) to size the evaluation; it
     // waits for the scan's totals only (written into mapped host memory),
@@ -759,11 +761,11 @@ int block_step(Ctx &c, double t_target, int64_t *n_act_out, double *t_block_out,
     // predictor (which skips clusters past the target, so it is harmless
     // when nothing is due)
     int rec = prof_begin(c, PH_SCHED);
-    const int64_t seq = ++c.sched_seq;
-    if (levels)
-        HIPCHK(c, launch_levels_sched(c, t_target, seq, c.stream));
-    else
+    const int64_t seq = levels && *ahead ? *ahead : ++c.sched_seq;
+    if (!levels)
         HIPCHK(c, launch_sched_head(c, t_target, seq, c.stream));
+    else if (!*ahead)
+        HIPCHK(c, launch_levels_sched(c, t_target, seq, c.stream));
     prof_end(c, rec);
     rec = prof_begin(c, PH_PREDICT);   // the compaction of the active list runs here too
     HIPCHK(c, launch_scatter_pack(c, c.stream, levels));
@@ -796,14 +798,19 @@ int block_step(Ctx &c, double t_target, int64_t *n_act_out, double *t_block_out,
     int rc = run_force(c, c.act, n_act, typ, out, (double)tot[2], tot[5], false, &L, &w);
     if (rc)
         return rc;
+    // (a profiled run times the schedule by itself)
+    const int64_t next = levels && !c.prof ? c.sched_seq + 1 : 0;
+    bool tail = false;
     rec = prof_begin(c, PH_CORRECT);
     if (w.split > 1)
-        HIPCHK(c, launch_reduce_correct(c, w, w.split, split_unit(L.lpi, L.waves), n_act, t_target, c.stream,
-                                        levels));
+        HIPCHK(c, launch_reduce_correct(c, w, w.split, split_unit(L.lpi, L.waves), n_act, t_target,
+                                        c.stream, levels, next, &tail));
     else
         HIPCHK(c, launch_correct(c, n_act, c.act, t_target, out.vec[0], out.vec[1], out.vec[2], 1,
-                                 n_act, c.stream, levels));
+                                 n_act, c.stream, levels, next, &tail));
     prof_end(c, rec);
+    if (levels)
+        *ahead = tail ? ++c.sched_seq : 0;
     if (stats) {
         stats->block_steps += 1;
         stats->active_total += n_act;
@@ -1083,7 +1090,7 @@ int nbody_block_step(nbody_ctx *ctx, double t_target, int64_t *n_act, double *t_
     Ctx &c = ctx->c;
     if (!n_act || !t_block || !on_grid(t_target, c.cfg.dt_min))
         return fail(c, NBODY_EINVAL, "bad argument");
-    int rc = block_step(c, t_target, n_act, t_block, nullptr, false);
+    int rc = block_step(c, t_target, n_act, t_block, nullptr, false, nullptr);
     if (rc)
         return rc;
     return take_err(c);
@@ -1109,6 +1116,7 @@ int nbody_step(nbody_ctx *ctx, double t_target, nbody_step_stats *stats)
     if (rc)
         return rc;
     bool levels = false;
+    int64_t ahead = 0;
     if (!done && (rc = levels_ready(c, &levels)) != NBODY_OK)
         return rc;
     for (; !done;) {
@@ -1121,7 +1129,7 @@ int nbody_step(nbody_ctx *ctx, double t_target, nbody_step_stats *stats)
             break;
         int64_t na = 0;
         double tb = 0.0;
-        rc = block_step(c, t_target, &na, &tb, stats, levels);
+        rc = block_step(c, t_target, &na, &tb, stats, levels, &ahead);
         if (rc)
             return rc;
         if (na == 0)

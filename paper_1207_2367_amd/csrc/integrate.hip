@@ -510,37 +510,6 @@ __global__ __launch_bounds__(TPB) void sched_scatter(const double *t, const doub
 // workgroups compact one chunk each, the rest predict TPB sources each to
 // their cluster's block time.  Both read only the schedule's results and
 // the stored state; they write disjoint arrays.
-// With fill != nullptr (one system, schedule from levels) a chunk counts its
-// due particles, takes their place in the list with one atomic add on *fill
-// and writes them in ascending order there (chunks land in any order; the
-// evaluation and the corrector of a particle do not depend on its slot).
-__device__ __forceinline__ void scatter_chunk_fill(const double *t, const double *dt, double T,
-                                                   int64_t b, int64_t e, int32_t *act,
-                                                   int64_t *fill)
-{
-    __shared__ int wcnt[TPB / 64];
-    __shared__ int64_t base;
-    int mine = 0;
-    for (int64_t i = b + threadIdx.x; i < e; i += TPB)
-        mine += due(t[i], dt[i], T) ? 1 : 0;
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1)
-        mine += __shfl_xor(mine, m, 64);
-    if ((threadIdx.x & 63) == 0)
-        wcnt[threadIdx.x >> 6] = mine;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int tot = 0;
-        for (int w = 0; w < TPB / 64; ++w)
-            tot += wcnt[w];
-        base = tot > 0 ? (int64_t)atomicAdd((unsigned long long *)fill, (unsigned long long)tot)
-                       : 0;
-    }
-    __syncthreads();
-    if (wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3] > 0)
-        scatter_range(t, dt, T, b, e, base, act);
-}
-
 __global__ __launch_bounds__(TPB) void scatter_pack_kernel(State st, JRecMixed jm, JRecPair32 jp, JRecF64 jd,
                                                            int prec, int64_t n,
                                                            const int32_t *cluster_of,
@@ -548,20 +517,59 @@ __global__ __launch_bounds__(TPB) void scatter_pack_kernel(State st, JRecMixed j
                                                            const int32_t *chunk_cluster,
                                                            const double *tblock,
                                                            const int64_t *chunk_pos,
-                                                           int32_t *act, int64_t n_chunks,
-                                                           int64_t *fill)
+                                                           int32_t *act, int64_t n_chunks)
 {
-    if ((int64_t)blockIdx.x < n_chunks && fill) {
-        const double T = tblock[0];
-        if (T < DBL_MAX)
-            scatter_chunk_fill(st.t, st.dt, T, chunk_begin[blockIdx.x],
-                               chunk_begin[blockIdx.x + 1], act, fill);
-    } else if ((int64_t)blockIdx.x < n_chunks)
+    if ((int64_t)blockIdx.x < n_chunks)
         scatter_chunk(st.t, st.dt, chunk_begin, chunk_cluster, tblock, chunk_pos, act,
                       blockIdx.x);
     else
         pack_one(st, jm, jp, jd, prec, n, tblock, cluster_of, 0,
                  ((int64_t)blockIdx.x - n_chunks) * TPB + threadIdx.x);
+}
+
+// The same for one system scheduled from its level counts, where the active
+// list's order is free: a workgroup predicts its TPB particles and, if some of
+// them are due, takes their place in the list with one atomic add on *fill
+// (workgroups land in any order; the evaluation and the corrector of a
+// particle do not depend on its slot).  Latency-bound on small systems: every
+// load is issued before the block time is known to be finite, and the list
+// takes one atomic round trip next to the prediction (32,768 bodies: 4.2 us;
+// with 2048-particle chunks counted and then compacted in eight passes each
+// 7.2 us).
+__global__ __launch_bounds__(TPB) void fill_pack_kernel(State st, JRecMixed jm, JRecPair32 jp, JRecF64 jd,
+                                                        int prec, int64_t n, const double *tblock,
+                                                        int32_t *act, int64_t *fill)
+{
+    __shared__ int cnt[TPB / 64];
+    __shared__ int64_t base;
+    const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
+    const bool in = i < n;
+    const int64_t ii = in ? i : n - 1;
+    const double T = tblock[0];
+    const double dt = st.dt[ii];
+    const PredIn q = load_pred(st, n, ii);
+    if (!(T < DBL_MAX))
+        return;   // nothing due up to the target
+    const bool f = in && due(q.t, dt, T);
+    const uint64_t mask = __ballot(f);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (lane == 0)
+        cnt[wave] = __popcll(mask);
+    __syncthreads();
+    int before = __popcll(mask & ((1ull << lane) - 1ull)), tot = 0;
+    for (int w = 0; w < TPB / 64; ++w) {
+        before += w < wave ? cnt[w] : 0;
+        tot += cnt[w];
+    }
+    if (threadIdx.x == 0 && tot > 0)
+        base = (int64_t)atomicAdd((unsigned long long *)fill, (unsigned long long)tot);
+    if (in)
+        store_pred<false>(q, jm, jp, jd, prec, i, T - q.t);
+    if (tot == 0)
+        return;
+    __syncthreads();
+    if (f)
+        act[base + before] = (int32_t)i;
 }
 
 // ------------------------------------------ schedule from per-level counts
@@ -619,22 +627,34 @@ __global__ __launch_bounds__(TPB) void levels_check_kernel(const double *t, cons
         atomicOr((unsigned long long *)&lvl[LVL_BAD], 1ull);
 }
 
+// What the schedule from counts reads and writes.
+struct LevelSched {
+    int64_t *lvl;        // counts and state words (LVL_*)
+    int64_t n;
+    int e0;              // exponent of dt_max
+    double t_target;
+    double *tblock;
+    int64_t *info, *hist;
+    uint32_t *err;
+    int64_t *info_host;  // totals and, last, seq, in mapped host memory
+    int64_t seq;         // 0: no schedule
+};
+
 // One wave: the next block from the counts (the totals as sched_scan writes
 // them, into info and the mapped host words with the sequence number), the
 // time of the last block moved to it, and the active list's fill position
 // cleared.  A fill position that does not match the N_act announced by the
 // previous schedule (the compaction found other particles due than the counts
-// said) sets ERR_LEVELS.
-__global__ __launch_bounds__(64) void levels_sched_kernel(int64_t *lvl, int64_t n, int e0,
-                                                          double t_target, int64_t *seg,
-                                                          double *tblock, int64_t *info,
-                                                          int64_t *hist, uint32_t *err,
-                                                          int64_t *info_host, int64_t seq)
+// said) sets ERR_LEVELS.  The counts are read coherently: other workgroups of
+// the same launch may have changed them.  The host words are single
+// system-scope stores, waited for before the sequence number is stored.
+__device__ __forceinline__ void levels_next(const LevelSched &s)
 {
     const int k = threadIdx.x;
-    const int64_t c = lvl[k];
-    const double Tl = __longlong_as_double((long long)lvl[LVL_TPREV]);
-    const double step = ldexp(1.0, e0 - k);
+    const int64_t c = ld<true>(s.lvl + k);
+    const double Tl = __longlong_as_double((long long)s.lvl[LVL_TPREV]);
+    const int64_t pos = s.lvl[LVL_POS], announced = s.lvl[LVL_NACT];
+    const double step = ldexp(1.0, s.e0 - k);
     const double next = c > 0 ? (floor(Tl / step) + 1.0) * step : INFINITY;
     double T = next;
 #pragma unroll
@@ -642,35 +662,59 @@ __global__ __launch_bounds__(64) void levels_sched_kernel(int64_t *lvl, int64_t 
         const double o = __shfl_xor(T, m, 64);
         T = o < T ? o : T;
     }
-    const bool act = T <= t_target;
+    const bool act = T <= s.t_target;
     int64_t na = act && c > 0 && next == T ? c : 0;
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1)
         na += __shfl_xor(na, m, 64);
     if (k != 0)
         return;
-    if (lvl[LVL_POS] != lvl[LVL_NACT])
-        atomicOr(err, ERR_LEVELS);
-    lvl[LVL_POS] = 0;
-    lvl[LVL_NACT] = na;
+    if (pos != announced)
+        atomicOr(s.err, ERR_LEVELS);
+    s.lvl[LVL_POS] = 0;
+    s.lvl[LVL_NACT] = na;
     const double Tb = act ? T : INFINITY;
     if (na > 0) {
-        lvl[LVL_TPREV] = __double_as_longlong(T);
+        s.lvl[LVL_TPREV] = __double_as_longlong(T);
         int bb = 0;
         while ((int64_t(1) << (bb + 1)) <= na)
             ++bb;
-        atomicAdd((unsigned long long *)&hist[bb], 1ull);
+        atomicAdd((unsigned long long *)&s.hist[bb], 1ull);
     }
-    seg[0] = 0;
-    seg[1] = na;
-    tblock[0] = na > 0 ? T : INFINITY;
-    const int64_t tot[6] = {na, (int64_t)__double_as_longlong(Tb), na * n, (int64_t)*err,
-                            na > 0 ? 1 : 0, n};
+    s.tblock[0] = na > 0 ? T : INFINITY;
+    const int64_t e = (int64_t)ld<true>(s.err) | (pos != announced ? (int64_t)ERR_LEVELS : 0);
+    const int64_t tot[6] = {na, (int64_t)__double_as_longlong(Tb), na * s.n, e, na > 0 ? 1 : 0,
+                            s.n};
     for (int q = 0; q < 6; ++q) {
-        info[q] = tot[q];
-        info_host[q] = tot[q];
+        s.info[q] = tot[q];
+        __hip_atomic_store(&s.info_host[q], tot[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
-    __hip_atomic_store(&info_host[6], seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __hip_atomic_store(&s.info_host[6], s.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+__global__ __launch_bounds__(64) void levels_sched_kernel(LevelSched s) { levels_next(s); }
+
+// The next block's schedule at the end of a corrector launch: the workgroup
+// that finishes last (a counter after the level counts, back to 0 for the
+// next launch) runs it.  Every wave first waits for its own count updates and
+// error bits, which are device-scope atomics.  As a launch of its own the
+// schedule cost 4.2 us and a launch gap in every block step.
+__device__ __forceinline__ void levels_tail(const LevelSched &s)
+{
+    __shared__ int last;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const unsigned long long done =
+            atomicAdd((unsigned long long *)&s.lvl[LVL_DONE], 1ull) + 1ull;
+        last = done == gridDim.x;
+        if (last)
+            s.lvl[LVL_DONE] = 0;
+    }
+    __syncthreads();
+    if (last && threadIdx.x < 64)
+        levels_next(s);
 }
 
 // i-block tables of a force launch over clusters: cluster c gets
@@ -881,16 +925,16 @@ struct LevelDelta {
     }
 };
 
-// lvl: per-level counts to keep up to date (nullptr: none), e0 the exponent
-// of dt_max
+// ls.lvl: per-level counts to keep up to date (nullptr: none); ls.seq != 0:
+// the last workgroup then schedules the next block
 __global__ __launch_bounds__(TPB) void correct_kernel(
     State st, int64_t n, int64_t n_act, const int32_t *idx, double t_target,
     const double *fa, const double *fj, const double *fs, int64_t sk, int64_t sd,
-    double eta, double dt_min, double dt_max, uint32_t *err, int64_t *lvl, int e0)
+    double eta, double dt_min, double dt_max, uint32_t *err, LevelSched ls)
 {
-    LevelDelta ld;
-    if (lvl) {
-        ld.init();
+    LevelDelta ldl;
+    if (ls.lvl) {
+        ldl.init();
         __syncthreads();
     }
     const int64_t k = (int64_t)blockIdx.x * TPB + threadIdx.x;
@@ -908,13 +952,15 @@ __global__ __launch_bounds__(TPB) void correct_kernel(
             }
             const OldState o = load_old(st, n, i);
             correct_loaded(st, n, i, o, a1, j1, s1, t_target, eta, dt_min, dt_max, err);
-            if (lvl)
-                ld.move(o.h, st.dt[i], e0);
+            if (ls.lvl)
+                ldl.move(o.h, st.dt[i], ls.e0);
         }
     }
-    if (lvl) {
+    if (ls.lvl) {
         __syncthreads();
-        ld.flush(lvl);
+        ldl.flush(ls.lvl);
+        if (ls.seq)
+            levels_tail(ls);
     }
 }
 
@@ -957,13 +1003,13 @@ template <int R>
 __global__ __launch_bounds__(TPB) void reduce_correct_kernel(
     State st, int64_t n, int64_t n_act, const double *part, int32_t B, int nt, ForceWork w,
     const int32_t *cluster_of, double t_target, double eta, double dt_min, double dt_max,
-    uint32_t *err, int64_t *lvl, int e0)
+    uint32_t *err, LevelSched ls)
 {
     constexpr int S = TPB / (9 * R);   // active slots per workgroup
     __shared__ double ps[9][S][R];
-    LevelDelta ld;
-    if (lvl)
-        ld.init();
+    LevelDelta ldl;
+    if (ls.lvl)
+        ldl.init();
     const int t = threadIdx.x;
     const int64_t k0 = (int64_t)blockIdx.x * S;
     // corrector lanes: t < S takes slot t.  An index outside the system (an
@@ -1006,12 +1052,14 @@ __global__ __launch_bounds__(TPB) void reduce_correct_kernel(
         const double j1[3] = {f[3], f[4], f[5]};
         const double s1[3] = {f[6], f[7], f[8]};
         correct_loaded(st, n, ic, o, a1, j1, s1, t_target, eta, dt_min, dt_max, err);
-        if (lvl)
-            ld.move(o.h, st.dt[ic], e0);
+        if (ls.lvl)
+            ldl.move(o.h, st.dt[ic], ls.e0);
     }
-    if (lvl) {
+    if (ls.lvl) {
         __syncthreads();
-        ld.flush(lvl);
+        ldl.flush(ls.lvl);
+        if (ls.seq)
+            levels_tail(ls);
     }
 }
 
@@ -1786,12 +1834,18 @@ hipError_t launch_sched_head(const Ctx &c, double t_target, int64_t seq, hipStre
 // compaction of the active list and predictor of a block step, one launch
 hipError_t launch_scatter_pack(const Ctx &c, hipStream_t s, bool levels)
 {
+    if (levels) {
+        hipLaunchKernelGGL(fill_pack_kernel, dim3(nblk(c.n)), dim3(TPB), 0, s, c.st, c.jm, c.jp,
+                           c.jd, (int)c.cfg.precision, c.n, (const double *)c.d_tblock, c.act,
+                           c.d_lvl + LVL_POS);
+        return hipGetLastError();
+    }
     const unsigned nb = (unsigned)c.n_chunks + nblk(c.n);
     hipLaunchKernelGGL(scatter_pack_kernel, dim3(nb), dim3(TPB), 0, s, c.st, c.jm, c.jp, c.jd,
                        (int)c.cfg.precision, c.n, (const int32_t *)c.d_cluster_of,
                        (const int64_t *)c.d_chunk_begin, (const int32_t *)c.d_chunk_cluster,
                        (const double *)c.d_tblock, (const int64_t *)c.d_chunk_pos, c.act,
-                       c.n_chunks, levels ? c.d_lvl + LVL_POS : (int64_t *)nullptr);
+                       c.n_chunks);
     return hipGetLastError();
 }
 
@@ -1810,11 +1864,19 @@ hipError_t launch_levels_build(const Ctx &c, hipStream_t s)
     return hipGetLastError();
 }
 
+namespace {
+
+LevelSched level_args(const Ctx &c, double t_target, int64_t seq)
+{
+    return LevelSched{c.d_lvl,  c.n,          std::ilogb(c.cfg.dt_max), t_target, c.d_tblock,
+                      c.d_info, c.d_info + 8, c.d_err,                  c.d_tot,  seq};
+}
+
+}  // namespace
+
 hipError_t launch_levels_sched(const Ctx &c, double t_target, int64_t seq, hipStream_t s)
 {
-    hipLaunchKernelGGL(levels_sched_kernel, dim3(1), dim3(64), 0, s, c.d_lvl, c.n,
-                       std::ilogb(c.cfg.dt_max), t_target, c.d_seg, c.d_tblock, c.d_info,
-                       c.d_info + 8, c.d_err, c.d_tot, seq);
+    hipLaunchKernelGGL(levels_sched_kernel, dim3(1), dim3(64), 0, s, level_args(c, t_target, seq));
     return hipGetLastError();
 }
 
@@ -1974,21 +2036,37 @@ hipError_t launch_segments(const Ctx &c, const int32_t *idx, int64_t n_act, hipS
     return hipGetLastError();
 }
 
+// Schedule arguments of a corrector launch of nb workgroups: none without
+// levels, and the next block's schedule at its end (levels_tail; *tail set)
+// if one is wanted (seq) and the launch is small: all workgroups count on one
+// word, about 10 ns each, so a large launch leaves it to a launch of its own.
+namespace {
+LevelSched corrector_levels(const Ctx &c, double t_target, bool levels, int64_t seq, unsigned nb,
+                            bool *tail)
+{
+    const bool t = levels && seq != 0 && nb <= 256;
+    if (tail)
+        *tail = t;
+    return levels ? level_args(c, t_target, t ? seq : 0) : LevelSched{};
+}
+}  // namespace
+
 hipError_t launch_correct(const Ctx &c, int64_t n_act, const int32_t *idx, double t_target,
                           const double *fa, const double *fj, const double *fs, int64_t sk,
-                          int64_t sd, hipStream_t s, bool levels)
+                          int64_t sd, hipStream_t s, bool levels, int64_t seq, bool *tail)
 {
     if (n_act <= 0)
         return hipSuccess;
-    hipLaunchKernelGGL(correct_kernel, dim3(nblk(n_act)), dim3(TPB), 0, s, c.st, c.n, n_act,
+    const unsigned nb = nblk(n_act);
+    hipLaunchKernelGGL(correct_kernel, dim3(nb), dim3(TPB), 0, s, c.st, c.n, n_act,
                        idx, t_target, fa, fj, fs, sk, sd, c.cfg.eta, c.cfg.dt_min,
-                       c.cfg.dt_max, c.d_err, levels ? c.d_lvl : nullptr,
-                       std::ilogb(c.cfg.dt_max));
+                       c.cfg.dt_max, c.d_err, corrector_levels(c, t_target, levels, seq, nb, tail));
     return hipGetLastError();
 }
 
 hipError_t launch_reduce_correct(const Ctx &c, const ForceWork &w, int split, int nt,
-                                 int64_t n_act, double t_target, hipStream_t s, bool levels)
+                                 int64_t n_act, double t_target, hipStream_t s, bool levels,
+                                 int64_t seq, bool *tail)
 {
     if (n_act <= 0)
         return hipSuccess;
@@ -2001,8 +2079,7 @@ hipError_t launch_reduce_correct(const Ctx &c, const ForceWork &w, int split, in
     hipLaunchKernelGGL(k, dim3(nb), dim3(TPB), 0, s, c.st, c.n, n_act,
                        (const double *)c.part, (int32_t)split, nt, w,
                        (const int32_t *)c.d_cluster_of, t_target, c.cfg.eta, c.cfg.dt_min,
-                       c.cfg.dt_max, c.d_err, levels ? c.d_lvl : nullptr,
-                       std::ilogb(c.cfg.dt_max));
+                       c.cfg.dt_max, c.d_err, corrector_levels(c, t_target, levels, seq, nb, tail));
     return hipGetLastError();
 }
 

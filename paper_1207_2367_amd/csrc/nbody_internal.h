@@ -137,7 +137,7 @@ hipError_t launch_force(Ctx &c, const ForceWork &w, const Launch &L,
                         bool reduce = true);
 hipError_t launch_reduce_correct(const Ctx &c, const ForceWork &w, int split, int nt,
                                  int64_t n_act, double t_target, hipStream_t s,
-                                 bool levels = false);
+                                 bool levels = false, int64_t seq = 0, bool *tail = nullptr);
 Launch pick_launch(const Ctx &c, int64_t n_act, int64_t n_src_max);
 Launch rule_launch(int64_t n_act, int64_t n_src, int64_t part_cap, int prec);
 hipError_t launch_energy_pot(Ctx &c, double *phi, hipStream_t s);
@@ -194,7 +194,7 @@ hipError_t launch_segments(const Ctx &c, const int32_t *idx, int64_t n_act, hipS
 hipError_t launch_correct(const Ctx &c, int64_t n_act, const int32_t *idx,
                           double t_target, const double *fa, const double *fj,
                           const double *fs, int64_t sk, int64_t sd, hipStream_t s,
-                          bool levels = false);
+                          bool levels = false, int64_t seq = 0, bool *tail = nullptr);
 hipError_t launch_recap(const Ctx &c, double t_target, hipStream_t s);
 hipError_t launch_energy_sums(const Ctx &c, const double *phi, double *out5,
                               hipStream_t s);
@@ -218,10 +218,10 @@ enum : uint32_t {
 // Schedule from per-level counts (a single system, nbody_step): lvl[k] =
 // number of particles whose step is dt_max 2^-k (k < LVL_N), then the time
 // of the last block (as bits), a violation flag, the active list's fill
-// position and the N_act the schedule announced.
+// position, the N_act the schedule announced, and the corrector workgroups done.
 constexpr int LVL_N = 64;
 enum : int { LVL_TPREV = LVL_N, LVL_BAD = LVL_N + 1, LVL_POS = LVL_N + 2, LVL_NACT = LVL_N + 3,
-             LVL_WORDS = LVL_N + 4 };
+             LVL_DONE = LVL_N + 4, LVL_WORDS = LVL_N + 5 };
 
 // Device-resident block-step loop: why it stopped, and the largest grid.
 enum : int { LOOP_DONE = 1, LOOP_BIG = 2, LOOP_ERR = 3 };
