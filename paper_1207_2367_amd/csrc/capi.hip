@@ -1186,16 +1186,18 @@ int nbody_energy(nbody_ctx *ctx, double *ekin, double *epot, double L[3])
     if (!ctx)
         return NBODY_EINVAL;
     Ctx &c = ctx->c;
+    // a state off a common time sets the error word, which the pair kernel
+    // looks at before any work: one wait for the check and the sums
+    int split = 1;
+    const double *phi = nullptr;
     HIPCHK(c, launch_sync_check(c, c.stream));
-    const int rc = take_err(c);
-    if (rc)
-        return rc;
-    HIPCHK(c, launch_energy_pot(c, c.d_phi, c.stream));
+    HIPCHK(c, launch_energy_pot(c, &split, &phi, c.stream));
     const int rec = prof_begin(c, PH_ENERGY);
-    HIPCHK(c, launch_energy_sums(c, c.d_phi, c.d_red + c.red_cap - 8, c.stream));
+    HIPCHK(c, launch_energy_sums(c, phi, split, c.d_red + c.red_cap - 8, c.stream));
     prof_end(c, rec);
     HIPCHK(c, hipMemcpyAsync(c.h_red, c.d_red + c.red_cap - 8, 5 * 8, hipMemcpyDeviceToHost, c.stream));
-    HIPCHK(c, hipStreamSynchronize(c.stream));
+    if (const int rc = take_err(c))
+        return rc;
     if (ekin)
         *ekin = c.h_red[0];
     if (epot)

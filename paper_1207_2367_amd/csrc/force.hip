@@ -47,26 +47,36 @@ namespace nb {
 
 namespace {
 
-// Potential terms of one LDS tile of NT sources for one lane: phi -= m_j /
-// r_ij, FP64.  MASK keeps only the tile slots lo <= t <= hi.
-template <int NT, bool MASK, bool EPS0>
-__device__ __forceinline__ double pot_tile(const double *sx, const double *sy,
-                                           const double *sz, const double *sm,
-                                           double xi, double yi, double zi, double eps2,
-                                           int lo, int hi, double phi)
+// One source of the energy pass in LDS.
+struct alignas(16) PotSrc {
+    double x, y, z, m;
+};
+
+// Potential terms of one LDS tile of NT sources for the IPT particles of one
+// lane: phi -= m_j / r_ij, FP64.  MASK keeps only the tile slots lo <= t <= hi
+// of each particle.
+template <int NT, int IPT, bool MASK, bool EPS0>
+__device__ __forceinline__ void pot_tile(const PotSrc *s, const double *xi, const double *yi,
+                                         const double *zi, double eps2, const int *lo,
+                                         const int *hi, double *phi)
 {
-#pragma unroll 8
+#pragma unroll 4
     for (int t = 0; t < NT; ++t) {
-        const double dx = sx[t] - xi, dy = sy[t] - yi, dz = sz[t] - zi;
-        const double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, eps2)));
-        double rinv = rinv_f64(r2);
-        if constexpr (EPS0)
-            rinv = r2 > 0.0 ? rinv : 0.0;
-        if constexpr (MASK)
-            rinv = (t >= lo && t <= hi) ? rinv : 0.0;
-        phi = fma(-sm[t], rinv, phi);
+        const double sx = s[t].x, sy = s[t].y, sz = s[t].z, sm = s[t].m;
+#pragma unroll
+        for (int u = 0; u < IPT; ++u) {
+            const double dx = sx - xi[u], dy = sy - yi[u], dz = sz - zi[u];
+            const double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, eps2)));
+            double rinv = rinv_f64(r2);
+            if constexpr (EPS0)
+                rinv = r2 > 0.0 ? rinv : 0.0;
+            // the mass is masked, not 1/r: the compiler would branch around 1/r
+            double m = sm;
+            if constexpr (MASK)
+                m = (t >= lo[u] && t <= hi[u]) ? m : 0.0;
+            phi[u] = fma(-m, rinv, phi[u]);
+        }
     }
-    return phi;
 }
 
 // Which (i-block, split) a workgroup of a launch takes.  The hardware deals
@@ -126,80 +136,89 @@ __global__ __launch_bounds__(NW * 64, force_waves(PREC, LPI, IPT)) void force_ke
 // and n_c / 2 - 1 otherwise: each pair at cyclic distance d < n_c / 2 is
 // then taken by exactly one of its ends, and the pair at d = n_c / 2 by the
 // end with the smaller index, so sum_l W_l = n_c (n_c - 1) / 2 and every
-// workgroup does the same work (no triangle).  A workgroup holds IB = 256
-// consecutive particles, one per lane; the union of their windows (virtual
-// positions ib0 + 1 .. last + W, folded back into the cluster) goes through
-// LDS in tiles of 256, split over grid.y = B; lanes mask only the tiles at
-// the two ends of the union.  Output: partial sums -sum m_j / r_ij per
-// particle and split, out[b * bstride + i].
-template <bool EPS0>
+// workgroup does the same work (no triangle).  A workgroup holds IB = 256 IPT
+// consecutive particles, IPT per lane (each source read from LDS serves IPT
+// pairs: with one, the two 128-bit reads per pair take 64 of the 71 cycles of
+// its vector instructions; 2150 / 2280 / 2330 G pairs/s with 1 / 2 / 4); the
+// union of their windows (virtual positions ib0 + 1 .. last + W, folded back
+// into the cluster) goes through LDS in tiles of 256, split over grid.y = B;
+// lanes mask only the tiles at the two ends of the union.  Output: partial
+// sums -sum m_j / r_ij per particle and split, out[b n + i].  Nothing is done
+// if the error word says that the particles are not at one time.
+template <bool EPS0, int IPT>
 __global__ __launch_bounds__(256) void energy_kernel(const double *X, const double *Y,
                                                      const double *Z, const double *M,
-                                                     ForceWork w, double *out, int64_t bstride,
+                                                     ForceWork w, double *out, int64_t n,
                                                      double eps2)
 {
-    constexpr int NT = 256;
-    __shared__ double s_x[NT], s_y[NT], s_z[NT], s_m[NT];
+    constexpr int NT = 256, IB = NT * IPT;
+    __shared__ PotSrc s[NT];
+    if (*w.err & ERR_STATE)
+        return;
     const int64_t g = blockIdx.x;
     const int b = blockIdx.y;
-    int c = 0;
-    int64_t gfirst = 0;
+    int64_t gfirst = 0, o0 = 0, nc = n;
     if (w.blk_cluster) {
-        c = w.blk_cluster[g];
+        const int c = w.blk_cluster[g];
         if (c < 0)
             return;  // grid padding past the last i-block
         gfirst = w.blk_first[c];
+        o0 = w.off[c];
+        nc = w.off[c + 1] - o0;
     }
-    const int64_t o0 = w.off[c];
-    const int64_t nc = w.off[c + 1] - o0;
-    const int64_t ib0 = (g - gfirst) * NT;          // local index of lane 0's particle
-    const int64_t last = (ib0 + NT < nc ? ib0 + NT : nc) - 1;
+    const int64_t ib0 = (g - gfirst) * IB;          // local index of lane 0's first particle
+    const int64_t last = (ib0 + IB < nc ? ib0 + IB : nc) - 1;
     const int tid = threadIdx.x;
-    const int64_t l = ib0 + tid;
-    const bool valid = l < nc;
     const int64_t half = nc / 2;
-    const int64_t wl = (nc & 1) ? half : (l < half ? half : half - 1);
     const int64_t wmin = (nc & 1) ? half : half - 1;   // smallest window of the cluster
-    const int64_t i = o0 + (valid ? l : ib0);
-    const double xi = X[i], yi = Y[i], zi = Z[i];
+    int64_t l[IPT], wl[IPT];
+    double xi[IPT], yi[IPT], zi[IPT], phi[IPT];
+#pragma unroll
+    for (int u = 0; u < IPT; ++u) {
+        l[u] = ib0 + tid + u * NT;
+        wl[u] = (nc & 1) ? half : (l[u] < half ? half : half - 1);
+        const int64_t i = o0 + (l[u] < nc ? l[u] : ib0);
+        xi[u] = X[i];
+        yi[u] = Y[i];
+        zi[u] = Z[i];
+        phi[u] = 0.0;
+    }
 
     // this split's share of the union of the windows, in whole tiles
-    const int64_t u_beg = ib0 + 1, u_end = last + half + 1;
-    int64_t chunk = (u_end - u_beg + w.split - 1) / w.split;
-    chunk = (chunk + NT - 1) / NT * NT;
-    const int64_t u0 = u_beg + (int64_t)b * chunk;
-    const int64_t u1 = u0 + chunk < u_end ? u0 + chunk : u_end;
+    const int64_t u_beg = ib0 + 1, len = last + half + 1 - u_beg;
+    const int64_t used = splits_used(len, w.split, NT);
+    const int64_t u0 = u_beg + (b < used ? split_begin(len, used, NT, b) : len);
+    const int64_t u1 = u_beg + (b < used ? split_begin(len, used, NT, b + 1) : len);
 
-    double phi = 0.0;
     for (int64_t t0 = u0; t0 < u1; t0 += NT) {
         __syncthreads();
-        const int64_t u = t0 + tid;
-        if (u < u1) {
-            const int64_t j = o0 + (u < nc ? u : u - nc);   // u < 2 n_c always
-            s_x[tid] = X[j];
-            s_y[tid] = Y[j];
-            s_z[tid] = Z[j];
-            s_m[tid] = M[j];
+        const int64_t v = t0 + tid;
+        if (v < u1) {
+            const int64_t j = o0 + (v < nc ? v : v - nc);   // v < 2 n_c always
+            s[tid] = PotSrc{X[j], Y[j], Z[j], M[j]};
         } else {
-            s_x[tid] = NULL_POS;
-            s_y[tid] = NULL_POS;
-            s_z[tid] = NULL_POS;
-            s_m[tid] = 0.0;
+            s[tid] = PotSrc{NULL_POS, NULL_POS, NULL_POS, 0.0};
         }
         __syncthreads();
-        // slots s of this tile with 1 <= t0 + s - l <= w_l; every lane's
+        // slots t of this tile with 1 <= t0 + t - l <= w_l; every particle's
         // range covers the whole tile when t0 > last and t0 + NT - 1 <= ib0 + wmin
+        int lo[IPT], hi[IPT];
         if (t0 > last && t0 + NT - 1 <= ib0 + wmin) {
-            phi = pot_tile<NT, false, EPS0>(s_x, s_y, s_z, s_m, xi, yi, zi, eps2, 0, NT - 1, phi);
+            pot_tile<NT, IPT, false, EPS0>(s, xi, yi, zi, eps2, lo, hi, phi);
         } else {
-            const int64_t lo = l + 1 - t0, hi = l + wl - t0;
-            const int slo = lo < 0 ? 0 : (lo > NT ? NT : (int)lo);
-            const int shi = hi < -1 ? -1 : (hi > NT - 1 ? NT - 1 : (int)hi);
-            phi = pot_tile<NT, true, EPS0>(s_x, s_y, s_z, s_m, xi, yi, zi, eps2, slo, shi, phi);
+#pragma unroll
+            for (int u = 0; u < IPT; ++u) {
+                const int64_t a = l[u] + 1 - t0, z = l[u] + wl[u] - t0;
+                lo[u] = a < 0 ? 0 : (a > NT ? NT : (int)a);
+                hi[u] = z < -1 ? -1 : (z > NT - 1 ? NT - 1 : (int)z);
+            }
+            pot_tile<NT, IPT, true, EPS0>(s, xi, yi, zi, eps2, lo, hi, phi);
         }
     }
-    if (valid)
-        out[(int64_t)b * bstride + i] = phi;
+#pragma unroll
+    for (int u = 0; u < IPT; ++u)
+        if (l[u] < nc)
+            out[(int64_t)b * n + o0 + l[u]] = phi[u];
 }
 
 // Sum the B split-source partials of every active slot (Table 1, section 4
@@ -213,18 +232,16 @@ __global__ __launch_bounds__(256) void energy_kernel(const double *X, const doub
 // are whole units of nt sources).
 template <int R>
 __global__ __launch_bounds__(256) void reduce_split(const double *part, int32_t B,
-                                                    int64_t n_act, ForceOut out,
-                                                    int pot_only, ForceWork w,
+                                                    int64_t n_act, ForceOut out, ForceWork w,
                                                     const int32_t *cluster_of, int nt)
 {
     constexpr int S = 256 / R;   // sums per workgroup
     __shared__ double ps[R][S];
     const int kl = threadIdx.x % S, rl = threadIdx.x / S;
     const int64_t t = (int64_t)blockIdx.x * S + kl;
-    const int nq = pot_only ? 1 : 10;
-    const bool in = t < n_act * nq;
-    const int q = pot_only ? 9 : (int)(t / n_act);
-    const int64_t k = pot_only ? t : t - (int64_t)q * n_act;
+    const bool in = t < n_act * 10;
+    const int q = (int)(t / n_act);
+    const int64_t k = t - (int64_t)q * n_act;
     double r = 0.0;
     if (in) {
         if (w.n_src > 0) {
@@ -272,14 +289,14 @@ __global__ __launch_bounds__(256) void reduce_split(const double *part, int32_t 
 
 // R by the length of the chains: 16 loads in flight per lane.  Sums that fill
 // the chip by themselves (2^16 of them and more) take one lane each.
-void launch_reduce(const double *part, int32_t B, int64_t n_act, const ForceOut &out, int pot_only,
+void launch_reduce(const double *part, int32_t B, int64_t n_act, const ForceOut &out,
                    const ForceWork &w, const int32_t *cluster_of, int nt, hipStream_t s)
 {
-    const int64_t sums = n_act * (pot_only ? 1 : 10);
+    const int64_t sums = n_act * 10;
     const int R = B <= 16 || sums >= (int64_t(1) << 16) ? 1 : (B <= 64 ? 4 : 8);
     const auto k = R == 1 ? reduce_split<1> : (R == 4 ? reduce_split<4> : reduce_split<8>);
     hipLaunchKernelGGL(k, dim3((unsigned)((sums * R + 255) / 256)), dim3(256), 0, s, part, B,
-                       n_act, out, pot_only, w, cluster_of, nt);
+                       n_act, out, w, cluster_of, nt);
 }
 
 // ---- dispatch table over the template parameters
@@ -439,59 +456,60 @@ hipError_t launch_force(Ctx &c, const ForceWork &w, const Launch &L,
     if (e != hipSuccess || w.split <= 1 || !reduce)
         return e;
     const int rr = prof_begin(c, PH_REDUCE);
-    launch_reduce(c.part, w.split, n_act_total, out, 0, w, c.d_cluster_of,
+    launch_reduce(c.part, w.split, n_act_total, out, w, c.d_cluster_of,
                   split_unit(L.lpi, L.waves), s);
     prof_end(c, rr);
     return hipGetLastError();
 }
 
-// Potential of the stored state for the energy: phi[i] = -sum over the
-// particle's half-window of m_j / r_ij (every pair of a cluster once).
-hipError_t launch_energy_pot(Ctx &c, double *phi, hipStream_t s)
+// Potential of the stored state for the energy: split b's part of
+// phi[i] = -sum over the particle's half-window of m_j / r_ij (every pair of a
+// cluster once) to c.part[b n + i], or to c.d_phi[i] when *split is 1.
+hipError_t launch_energy_pot(Ctx &c, int *split, const double **phi, hipStream_t s)
 {
-    constexpr int64_t IB = 256;
     const int64_t n = c.n;
+    int64_t ncmax = 0;
+    for (size_t k = 0; k + 1 < c.off.size(); ++k)
+        ncmax = std::max(ncmax, c.off[k + 1] - c.off[k]);
+    // particles per lane: the masked ends of a workgroup's window cost 256 of
+    // them each, a few per cent of half the cluster at these sizes
+    const int ipt = ncmax >= 65536 ? 4 : (ncmax >= 16384 ? 2 : 1);
+    const int64_t ib = 256 * ipt;
     hipError_t e = hipSuccess;
-    if (c.nc > 1 && (e = launch_segments(c, nullptr, n, s)) != hipSuccess)
-        return e;
     ForceWork w{};
-    w.seg = c.d_seg;
     w.off = c.d_off;
     w.nc = c.nc;
+    w.err = c.d_err;
     if (c.nc == 1) {
-        w.n_blocks = (n + IB - 1) / IB;
+        w.n_blocks = (n + ib - 1) / ib;
     } else {
-        const int64_t cap = n / IB + c.nc + 1;
-        if ((e = launch_blocks(c, IB, cap, s)) != hipSuccess)
+        const int64_t cap = n / ib + c.nc + 1;
+        if ((e = launch_segments(c, nullptr, n, s)) != hipSuccess ||
+            (e = launch_blocks(c, ib, cap, s)) != hipSuccess)
             return e;
         w.blk_cluster = c.d_blk_cluster;
         w.blk_first = c.d_blk_first;
         w.n_blocks = cap;
     }
-    // splits: up to ~2048 workgroups, at least two tiles per split, and the
-    // partial sums within the split buffer
-    int64_t ncmax = 0;
-    for (size_t k = 0; k + 1 < c.off.size(); ++k)
-        ncmax = std::max(ncmax, c.off[k + 1] - c.off[k]);
-    int split = 1;
-    while (w.n_blocks * split * 2 <= 2048 && (ncmax / 2 + IB) / (split * 2) >= 2 * IB &&
-           (int64_t)split * 2 * n <= c.part_cap)
-        split <<= 1;
-    w.split = split;
+    // splits of at least two tiles, up to ~8192 workgroups (several rounds of
+    // the 1024-2048 resident ones: 100,003 bodies 2.72 ms in 1564 workgroups
+    // of one particle per lane, 2.47 ms in 6272 of four), and the partial
+    // sums within the split buffer
+    *split = 1;
+    while (w.n_blocks * *split * 2 <= 8192 && (ncmax / 2 + ib) / (*split * 2) >= 2 * 256 &&
+           (int64_t)*split * 2 * n <= 10 * c.part_cap)
+        *split *= 2;
+    w.split = *split;
     const double *X = c.st.pos, *Y = c.st.pos + n, *Z = c.st.pos + 2 * n;
-    double *dst = split > 1 ? c.part + 9 * n : phi;
-    const int64_t bstride = 10 * n;   // the [B][10][n] layout of the split buffer, slot 9
-    auto k = c.eps == 0.0 ? energy_kernel<true> : energy_kernel<false>;
+    double *dst = *split > 1 ? c.part : c.d_phi;
+    *phi = dst;
+    const bool e0 = c.eps == 0.0;
+    auto k = ipt == 4 ? (e0 ? energy_kernel<true, 4> : energy_kernel<false, 4>)
+                      : (ipt == 2 ? (e0 ? energy_kernel<true, 2> : energy_kernel<false, 2>)
+                                  : (e0 ? energy_kernel<true, 1> : energy_kernel<false, 1>));
     const int rec = prof_begin(c, PH_ENERGY);
-    hipLaunchKernelGGL(k, dim3((unsigned)w.n_blocks, (unsigned)split), dim3(IB), 0, s, X, Y, Z,
-                       (const double *)c.st.mass, w, dst, bstride, c.eps * c.eps);
-    if ((e = hipGetLastError()) != hipSuccess || split == 1) {
-        prof_end(c, rec);
-        return e;
-    }
-    ForceOut out{};
-    out.pot = phi;
-    launch_reduce(c.part, split, n, out, 1, ForceWork{}, nullptr, 1, s);
+    hipLaunchKernelGGL(k, dim3((unsigned)w.n_blocks, (unsigned)*split), dim3(256), 0, s, X, Y, Z,
+                       (const double *)c.st.mass, w, dst, n, c.eps * c.eps);
     prof_end(c, rec);
     return hipGetLastError();
 }

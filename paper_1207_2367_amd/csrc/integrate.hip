@@ -1643,26 +1643,20 @@ __global__ __launch_bounds__(TPB) void recap_kernel(State st, int64_t n, double 
 
 // ------------------------------------------------------------- energy
 // per-workgroup partial sums of E_kin, sum_i m_i phi_i (phi_i over j > i,
-// so each pair once), L; then one workgroup adds the partials in order
-__device__ __forceinline__ double block_sum(double v, double *sh)
+// so each pair once, its `split` parts added in order), L; then one wave per
+// quantity adds the partials in a fixed order
+__device__ __forceinline__ double wave_sum(double v)
 {
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1)
         v += __shfl_xor(v, m, 64);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0)
-        sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    double s = 0.0;
-    for (int w = 0; w < (int)(blockDim.x >> 6); ++w)
-        s += sh[w];
-    return s;
+    return v;
 }
 
 __global__ __launch_bounds__(TPB) void energy_partial(State st, int64_t n, const double *phi,
-                                                      double *red)
+                                                      int split, double *red)
 {
-    __shared__ double sh[TPB / 64];
+    __shared__ double sh[5][TPB / 64];
     const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
     double q[5] = {0, 0, 0, 0, 0};
     if (i < n) {
@@ -1670,30 +1664,37 @@ __global__ __launch_bounds__(TPB) void energy_partial(State st, int64_t n, const
         const double x = st.pos[i], y = st.pos[n + i], z = st.pos[2 * n + i];
         const double vx = st.vel[i], vy = st.vel[n + i], vz = st.vel[2 * n + i];
         q[0] = 0.5 * m * (vx * vx + vy * vy + vz * vz);
-        q[1] = m * phi[i];   // phi[i] = -sum of m_j / r_ij over the half-window of i
+        q[1] = m * sum_splits(phi + i, n, split);   // -sum of m_j / r_ij over the half-window
         q[2] = m * (y * vz - z * vy);
         q[3] = m * (z * vx - x * vz);
         q[4] = m * (x * vy - y * vx);
     }
+#pragma unroll
     for (int r = 0; r < 5; ++r) {
-        const double s = block_sum(q[r], sh);
-        if (threadIdx.x == 0)
-            red[(int64_t)blockIdx.x * 5 + r] = s;
+        const double s = wave_sum(q[r]);
+        if ((threadIdx.x & 63) == 0)
+            sh[r][threadIdx.x >> 6] = s;
+    }
+    __syncthreads();
+    if (threadIdx.x < 5) {
+        double s = 0.0;
+        for (int w = 0; w < TPB / 64; ++w)
+            s += sh[threadIdx.x][w];
+        red[(int64_t)blockIdx.x * 5 + threadIdx.x] = s;
     }
 }
 
-__global__ __launch_bounds__(1024) void energy_final(const double *red, int64_t nblk,
-                                                     double *out)
+__global__ __launch_bounds__(320) void energy_final(const double *red, int64_t nblk,
+                                                    double *out)
 {
-    __shared__ double sh[1024 / 64];
-    for (int r = 0; r < 5; ++r) {
-        double v = 0.0;
-        for (int64_t b = threadIdx.x; b < nblk; b += 1024)
-            v += red[b * 5 + r];
-        const double s = block_sum(v, sh);
-        if (threadIdx.x == 0)
-            out[r] = s;
-    }
+    const int r = threadIdx.x >> 6;
+    double v = 0.0;
+#pragma unroll 8
+    for (int64_t b = threadIdx.x & 63; b < nblk; b += 64)
+        v += red[b * 5 + r];
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0)
+        out[r] = v;
 }
 
 // ------------------------------------------------------------ utilities
@@ -2097,11 +2098,12 @@ hipError_t launch_init_dt(const Ctx &c, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_energy_sums(const Ctx &c, const double *phi, double *out5, hipStream_t s)
+hipError_t launch_energy_sums(const Ctx &c, const double *phi, int split, double *out5,
+                              hipStream_t s)
 {
     const unsigned nb = nblk(c.n);
-    hipLaunchKernelGGL(energy_partial, dim3(nb), dim3(TPB), 0, s, c.st, c.n, phi, c.d_red);
-    hipLaunchKernelGGL(energy_final, dim3(1), dim3(1024), 0, s, (const double *)c.d_red,
+    hipLaunchKernelGGL(energy_partial, dim3(nb), dim3(TPB), 0, s, c.st, c.n, phi, split, c.d_red);
+    hipLaunchKernelGGL(energy_final, dim3(1), dim3(320), 0, s, (const double *)c.d_red,
                        (int64_t)nb, out5);
     return hipGetLastError();
 }

@@ -140,7 +140,8 @@ hipError_t launch_reduce_correct(const Ctx &c, const ForceWork &w, int split, in
                                  bool levels = false, int64_t seq = 0, bool *tail = nullptr);
 Launch pick_launch(const Ctx &c, int64_t n_act, int64_t n_src_max);
 Launch rule_launch(int64_t n_act, int64_t n_src, int64_t part_cap, int prec);
-hipError_t launch_energy_pot(Ctx &c, double *phi, hipStream_t s);
+// parts of the half-window potentials: *split arrays of n at *phi
+hipError_t launch_energy_pot(Ctx &c, int *split, const double **phi, hipStream_t s);
 int64_t iblock_size(const Launch &L);
 
 // startup.hip
@@ -196,7 +197,7 @@ hipError_t launch_correct(const Ctx &c, int64_t n_act, const int32_t *idx,
                           const double *fs, int64_t sk, int64_t sd, hipStream_t s,
                           bool levels = false, int64_t seq = 0, bool *tail = nullptr);
 hipError_t launch_recap(const Ctx &c, double t_target, hipStream_t s);
-hipError_t launch_energy_sums(const Ctx &c, const double *phi, double *out5,
+hipError_t launch_energy_sums(const Ctx &c, const double *phi, int split, double *out5,
                               hipStream_t s);
 hipError_t launch_validate_idx(const Ctx &c, int64_t n_act, const int32_t *idx,
                                hipStream_t s);
