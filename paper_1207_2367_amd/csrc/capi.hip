@@ -949,9 +949,11 @@ int nbody_init(nbody_ctx **out, int64_t n, const double *d_mass, const double *d
     H(hipMemsetAsync(c.d_err, 0, 4, s), "err");
     H(hipMemsetAsync(c.d_info, 0, 64 * 8, s), "info");
     H(launch_sched_reset(c, s), "sched");   // the scan keeps them reset afterwards
-    H(hipMemcpyAsync(c.st.mass, d_mass, n * 8, hipMemcpyDeviceToDevice, s), "mass");
-    H(launch_aos_to_soa(d_pos, c.st.pos, n, s), "pos");
-    H(launch_aos_to_soa(d_vel, c.st.vel, n, s), "vel");
+    StateCopy in;
+    in.add(c.st.mass, d_mass, 0);
+    in.add(c.st.pos, d_pos, 1);
+    in.add(c.st.vel, d_vel, 1);
+    H(launch_state_copy(in, false, n, s), "inputs");
     H(hipMemsetAsync(c.st.acc, 0, 3 * n * 8, s), "acc");
     H(hipMemsetAsync(c.st.jrk, 0, 3 * n * 8, s), "jrk");
     H(hipMemsetAsync(c.st.snp, 0, 3 * n * 8, s), "snp");
@@ -1150,15 +1152,16 @@ int nbody_get_state(nbody_ctx *ctx, double *d_pos, double *d_vel, double *d_acc,
     if (!ctx)
         return NBODY_EINVAL;
     Ctx &c = ctx->c;
-    const double *src[6] = {c.st.pos, c.st.vel, c.st.acc, c.st.jrk, c.st.snp, c.st.crk};
-    double *dst[6] = {d_pos, d_vel, d_acc, d_jrk, d_snp, d_crk};
-    for (int q = 0; q < 6; ++q)
-        if (dst[q])
-            HIPCHK(c, launch_soa_to_aos(src[q], dst[q], c.n, c.stream));
-    if (d_t)
-        HIPCHK(c, hipMemcpyAsync(d_t, c.st.t, c.n * 8, hipMemcpyDeviceToDevice, c.stream));
-    if (d_dt)
-        HIPCHK(c, hipMemcpyAsync(d_dt, c.st.dt, c.n * 8, hipMemcpyDeviceToDevice, c.stream));
+    StateCopy q;
+    q.add(c.st.pos, d_pos, 1);
+    q.add(c.st.vel, d_vel, 1);
+    q.add(c.st.acc, d_acc, 1);
+    q.add(c.st.jrk, d_jrk, 1);
+    q.add(c.st.snp, d_snp, 1);
+    q.add(c.st.crk, d_crk, 1);
+    q.add(c.st.t, d_t, 0);
+    q.add(c.st.dt, d_dt, 0);
+    HIPCHK(c, launch_state_copy(q, true, c.n, c.stream));
     return NBODY_OK;
 }
 
@@ -1169,15 +1172,16 @@ int nbody_set_state(nbody_ctx *ctx, const double *d_pos, const double *d_vel,
     if (!ctx)
         return NBODY_EINVAL;
     Ctx &c = ctx->c;
-    const double *src[6] = {d_pos, d_vel, d_acc, d_jrk, d_snp, d_crk};
-    double *dst[6] = {c.st.pos, c.st.vel, c.st.acc, c.st.jrk, c.st.snp, c.st.crk};
-    for (int q = 0; q < 6; ++q)
-        if (src[q])
-            HIPCHK(c, launch_aos_to_soa(src[q], dst[q], c.n, c.stream));
-    if (d_t)
-        HIPCHK(c, hipMemcpyAsync(c.st.t, d_t, c.n * 8, hipMemcpyDeviceToDevice, c.stream));
-    if (d_dt)
-        HIPCHK(c, hipMemcpyAsync(c.st.dt, d_dt, c.n * 8, hipMemcpyDeviceToDevice, c.stream));
+    StateCopy q;
+    q.add(c.st.pos, d_pos, 1);
+    q.add(c.st.vel, d_vel, 1);
+    q.add(c.st.acc, d_acc, 1);
+    q.add(c.st.jrk, d_jrk, 1);
+    q.add(c.st.snp, d_snp, 1);
+    q.add(c.st.crk, d_crk, 1);
+    q.add(c.st.t, d_t, 0);
+    q.add(c.st.dt, d_dt, 0);
+    HIPCHK(c, launch_state_copy(q, false, c.n, c.stream));
     return NBODY_OK;
 }
 

@@ -203,10 +203,21 @@ hipError_t launch_validate_idx(const Ctx &c, int64_t n_act, const int32_t *idx,
                                hipStream_t s);
 // ERR_STATE unless every cluster's particles share one time
 hipError_t launch_sync_check(const Ctx &c, hipStream_t s);
-hipError_t launch_aos_to_soa(const double *src, double *dst, int64_t n,
-                             hipStream_t s);
-hipError_t launch_soa_to_aos(const double *src, double *dst, int64_t n,
-                             hipStream_t s);
+// Arrays copied between the state and a caller: vectors [3][n] <-> [n][3],
+// scalars [n].
+struct StateCopy {
+    struct Item {
+        double *own, *user;
+        int vec;
+    } a[9];
+    int count = 0;
+    void add(double *own, const double *user, int vec)
+    {
+        if (user)
+            a[count++] = Item{own, const_cast<double *>(user), vec};
+    }
+};
+hipError_t launch_state_copy(const StateCopy &c, bool out, int64_t n, hipStream_t s);
 hipError_t launch_check_finite(const Ctx &c, hipStream_t s);
 hipError_t launch_init_dt(const Ctx &c, hipStream_t s);
 
