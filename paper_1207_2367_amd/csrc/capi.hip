@@ -143,6 +143,54 @@ hipError_t scratch_address(int dev, unsigned char **out)
     return hipSuccess;
 }
 
+// A context's words in pinned, mapped, coherent host memory: the GPU-written
+// totals (16 words), readback words (64), sums (64) and the error word.
+// Allocating and freeing such memory takes longer than starting a system of a
+// few thousand bodies, so up to HOST_BLOCKS blocks of closed contexts are kept
+// for the next ones (per device, any thread; more are freed at once).
+constexpr int64_t HOST_BLOCK_BYTES = (16 + 64 + 64 + 8) * 8;
+constexpr int HOST_BLOCKS = 8;
+struct HostBlock {
+    int64_t *p;
+    int dev;
+};
+std::mutex g_host_mu;
+HostBlock g_host_blocks[HOST_BLOCKS];
+int g_host_count = 0;
+
+int64_t *host_block_take(int dev)
+{
+    {
+        std::lock_guard<std::mutex> lock(g_host_mu);
+        for (int k = 0; k < g_host_count; ++k)
+            if (g_host_blocks[k].dev == dev) {
+                int64_t *p = g_host_blocks[k].p;
+                g_host_blocks[k] = g_host_blocks[--g_host_count];
+                return p;
+            }
+    }
+    void *p = nullptr;
+    if (hipHostMalloc(&p, HOST_BLOCK_BYTES, hipHostMallocMapped | hipHostMallocCoherent) !=
+        hipSuccess)
+        return nullptr;
+    return static_cast<int64_t *>(p);
+}
+
+// (no work that writes the block may be in flight)
+void host_block_give(int64_t *p, int dev)
+{
+    if (!p)
+        return;
+    {
+        std::lock_guard<std::mutex> lock(g_host_mu);
+        if (g_host_count < HOST_BLOCKS) {
+            g_host_blocks[g_host_count++] = HostBlock{p, dev};
+            return;
+        }
+    }
+    (void)hipHostFree(p);
+}
+
 // Scratch layout of nbody_force_noalloc for n sources: the records of the
 // context's precision (used by calls without the potential; the limit on the
 // sizes counts them for every call) and 512 bytes left free; the split
@@ -895,77 +943,71 @@ int nbody_init(nbody_ctx **out, int64_t n, const double *d_mass, const double *d
     c.cfg.cluster_offsets = nullptr;
     c.stream = (hipStream_t)cfg->stream;
     auto bail = [&](int rc) {
-        if (c.h_tot)
-            (void)hipHostFree(c.h_tot);
-        if (c.h_info)
-            (void)hipHostFree(c.h_info);
+        host_block_give(c.h_tot, c.device);
         delete h;
         return rc;
     };
     if (hipGetDevice(&c.device) != hipSuccess)
         return bail(NBODY_EDEVICE);
     ws_layout(n, nc, cfg->precision, &c, static_cast<char *>(d_workspace));
-    if (hipHostMalloc((void **)&c.h_info, 64 * sizeof(int64_t) + 64 * sizeof(double) + 64,
-                      hipHostMallocDefault) != hipSuccess)
+    c.h_tot = host_block_take(c.device);
+    if (!c.h_tot || hipHostGetDevicePointer((void **)&c.d_tot, c.h_tot, 0) != hipSuccess)
         return bail(NBODY_EDEVICE);
+    std::memset(c.h_tot, 0, HOST_BLOCK_BYTES);
+    c.h_info = c.h_tot + 16;
     c.h_red = reinterpret_cast<double *>(c.h_info + 64);
     c.h_err = reinterpret_cast<uint32_t *>(c.h_red + 64);
-    if (hipHostMalloc((void **)&c.h_tot, 16 * sizeof(int64_t),
-                      hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
-        hipHostGetDevicePointer((void **)&c.d_tot, c.h_tot, 0) != hipSuccess)
-        return bail(NBODY_EDEVICE);
-    std::memset(c.h_tot, 0, 16 * sizeof(int64_t));
     // cluster offsets, cluster of each particle, schedule chunk table
     c.off.assign(nc + 1, 0);
     if (nc > 1)
         std::copy(cfg->cluster_offsets, cfg->cluster_offsets + nc + 1, c.off.begin());
     else
         c.off[1] = n;
-    std::vector<int32_t> ch_cl;
-    std::vector<int64_t> ch_b;
-    for (int32_t k = 0; k < nc; ++k)
-        for (int64_t b = c.off[k]; b < c.off[k + 1]; b += SCHED_CHUNK) {
-            ch_cl.push_back(k);
-            ch_b.push_back(b);
-        }
-    ch_b.push_back(n);
-    c.n_chunks = (int64_t)ch_cl.size();
+    c.n_chunks = count_chunks(c.off);
     hipStream_t s = c.stream;
     int rc = NBODY_OK;
     auto H = [&](hipError_t e, const char *w) {
         if (e != hipSuccess && rc == NBODY_OK)
             rc = hip_fail(c, e, w);
     };
-    H(hipMemcpyAsync(c.d_off, c.off.data(), (nc + 1) * 8, hipMemcpyHostToDevice, s), "offsets");
-    H(hipMemcpyAsync(c.d_chunk_cluster, ch_cl.data(), c.n_chunks * 4, hipMemcpyHostToDevice, s), "chunks");
-    H(hipMemcpyAsync(c.d_chunk_begin, ch_b.data(), (c.n_chunks + 1) * 8, hipMemcpyHostToDevice, s), "chunks");
+    // one system: the tables follow from n and are filled on the device with
+    // the other words; several: the host's offsets decide
+    H(launch_init_words(c, s), "words");
+    std::vector<int32_t> ch_cl, cl;
+    std::vector<int64_t> ch_b;
     if (nc > 1) {
-        std::vector<int32_t> cl(n);
-        for (int32_t k = 0; k < nc; ++k)
+        cl.resize(n);
+        for (int32_t k = 0; k < nc; ++k) {
             std::fill(cl.begin() + c.off[k], cl.begin() + c.off[k + 1], k);
+            for (int64_t b = c.off[k]; b < c.off[k + 1]; b += SCHED_CHUNK) {
+                ch_cl.push_back(k);
+                ch_b.push_back(b);
+            }
+        }
+        ch_b.push_back(n);
+        H(hipMemcpyAsync(c.d_off, c.off.data(), (nc + 1) * 8, hipMemcpyHostToDevice, s), "offsets");
+        H(hipMemcpyAsync(c.d_chunk_cluster, ch_cl.data(), c.n_chunks * 4, hipMemcpyHostToDevice, s), "chunks");
+        H(hipMemcpyAsync(c.d_chunk_begin, ch_b.data(), (c.n_chunks + 1) * 8, hipMemcpyHostToDevice, s), "chunks");
         H(hipMemcpyAsync(c.d_cluster_of, cl.data(), n * 4, hipMemcpyHostToDevice, s), "cluster_of");
-        H(hipStreamSynchronize(s), "sync");   // host vectors go out of scope
     }
-    H(hipMemsetAsync(c.d_err, 0, 4, s), "err");
-    H(hipMemsetAsync(c.d_info, 0, 64 * 8, s), "info");
-    H(launch_sched_reset(c, s), "sched");   // the scan keeps them reset afterwards
     StateCopy in;
     in.add(c.st.mass, d_mass, 0);
     in.add(c.st.pos, d_pos, 1);
     in.add(c.st.vel, d_vel, 1);
     H(launch_state_copy(in, false, n, s), "inputs");
-    H(hipMemsetAsync(c.st.acc, 0, 3 * n * 8, s), "acc");
-    H(hipMemsetAsync(c.st.jrk, 0, 3 * n * 8, s), "jrk");
-    H(hipMemsetAsync(c.st.snp, 0, 3 * n * 8, s), "snp");
-    H(hipMemsetAsync(c.st.crk, 0, 3 * n * 8, s), "crk");
-    H(hipMemsetAsync(c.st.t, 0, n * 8, s), "t");
+    // a start-up fills every derivative and the first step sets the times
+    if (cfg->skip_startup)
+        H(hipMemsetAsync(c.st.acc, 0, (char *)(c.st.t + n) - (char *)c.st.acc, s), "derivatives");
     H(launch_check_finite(c, s), "finite");
-    H(hipStreamSynchronize(s), "sync");
-    if (rc != NBODY_OK)
+    // a large start-up waits for the check of its inputs (minutes of work at
+    // millions of bodies); below, one wait at the end is cheaper than two.
+    // The host tables above are in use until a wait.
+    if (rc == NBODY_OK && (n > 32768 || nc > 1))
+        rc = take_err(c);
+    if (rc != NBODY_OK) {
+        (void)hipStreamSynchronize(s);
         return bail(rc);
-    rc = take_err(c);
-    if (rc != NBODY_OK)
-        return bail(rc);
+    }
     // start-up evaluation, FP64 from the stored state: pass 1 gives a and da
     // (the sources' zero a and da do not enter them); pass 2 gives d2a and
     // the crackle with the pass-1 values as the sources' a and da.  Then the
@@ -979,8 +1021,10 @@ int nbody_init(nbody_ctx **out, int64_t n, const double *d_mass, const double *d
     }
     if (rc == NBODY_OK)
         rc = take_err(c);
-    if (rc != NBODY_OK)
+    if (rc != NBODY_OK) {
+        (void)hipStreamSynchronize(s);
         return bail(rc);
+    }
     *out = h;
     return NBODY_OK;
 }
@@ -994,10 +1038,7 @@ void nbody_free(nbody_ctx *ctx)
     (void)prof_collect(ctx->c);
     for (hipEvent_t e : ctx->c.prof_pool)
         (void)hipEventDestroy(e);
-    if (ctx->c.h_tot)
-        (void)hipHostFree(ctx->c.h_tot);
-    if (ctx->c.h_info)
-        (void)hipHostFree(ctx->c.h_info);
+    host_block_give(ctx->c.h_tot, ctx->c.device);
     delete ctx;
 }
 

@@ -15,6 +15,7 @@
 // ensemble loop that runs every block step of every cluster of a batched
 // context in one launch (ensemble_loop_kernel), both with the evaluation
 // body of force_body.h.
+#include <algorithm>
 #include <cfloat>
 #include <cmath>
 
@@ -244,11 +245,28 @@ __global__ __launch_bounds__(TPB) void predict_out_kernel(State st, int64_t n, d
 }
 
 // ---------------------------------------------------------- scheduling
-__global__ void sched_reset(uint64_t *tmin, int32_t nc)
+// A new context's words: the clusters' minima, the info words, the error word
+// and, for one system, its offsets and its schedule chunks.
+__global__ __launch_bounds__(TPB) void init_words_kernel(uint64_t *tmin, int32_t nc, int64_t n,
+                                                         int64_t *info, uint32_t *err, int64_t *off,
+                                                         int64_t *chunk_begin,
+                                                         int32_t *chunk_cluster, int64_t n_chunks)
 {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c < nc)
-        tmin[c] = ~0ull;
+    const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
+    if (i < nc)
+        tmin[i] = ~0ull;
+    if (i < 64)
+        info[i] = 0;
+    if (i == 0)
+        *err = 0;
+    if (nc > 1)
+        return;
+    if (i < 2)
+        off[i] = i == 0 ? 0 : n;
+    if (i < n_chunks)
+        chunk_cluster[i] = 0;
+    if (i <= n_chunks)
+        chunk_begin[i] = i < n_chunks ? i * SCHED_CHUNK : n;
 }
 
 __device__ __forceinline__ uint64_t wave_min_u64(uint64_t v)
@@ -1848,9 +1866,11 @@ hipError_t launch_predict_out(const Ctx &c, double t, double *pos, double *vel, 
     return hipGetLastError();
 }
 
-hipError_t launch_sched_reset(const Ctx &c, hipStream_t s)
+hipError_t launch_init_words(const Ctx &c, hipStream_t s)
 {
-    hipLaunchKernelGGL(sched_reset, dim3(nblk(c.nc)), dim3(TPB), 0, s, c.d_tmin, c.nc);
+    const int64_t items = std::max<int64_t>(std::max<int64_t>(c.nc, 64), c.n_chunks + 1);
+    hipLaunchKernelGGL(init_words_kernel, dim3(nblk(items)), dim3(TPB), 0, s, c.d_tmin, c.nc, c.n,
+                       c.d_info, c.d_err, c.d_off, c.d_chunk_begin, c.d_chunk_cluster, c.n_chunks);
     return hipGetLastError();
 }
 

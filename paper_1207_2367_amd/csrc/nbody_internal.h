@@ -169,7 +169,8 @@ hipError_t launch_pack_arrays(const Ctx &c, const double *mass, const double *po
 hipError_t launch_predict_out(const Ctx &c, double t, double *pos, double *vel,
                               double *acc, hipStream_t s);
 hipError_t launch_schedule(const Ctx &c, double t_target, int64_t seq, hipStream_t s);
-hipError_t launch_sched_reset(const Ctx &c, hipStream_t s);
+// words of a new context: minima, info, error word, one system's tables
+hipError_t launch_init_words(const Ctx &c, hipStream_t s);
 hipError_t launch_sched_head(const Ctx &c, double t_target, int64_t seq, hipStream_t s);
 // per-level counts of the stored state, the time of the last block and the
 // check that every step is a power of two within [dt_min, dt_max] and every
