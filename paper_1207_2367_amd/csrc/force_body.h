@@ -97,31 +97,31 @@ __device__ __forceinline__ double dpp_of(double v)
     return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
 }
 
-// v + (v of the lane 16 or 32 apart): the swap leaves the even rows (lower
-// half) of v in one register and the odd rows (upper half) in the other
+// Sums over the lanes STEP (16 or 32) apart of two values at once: the even
+// rows (lower half) get a's sum, the odd rows (upper half) b's.  The swap
+// leaves a and b's even parts in one register and their odd parts in the other.
 template <int STEP>
-__device__ __forceinline__ double swap_sum(double v)
+__device__ __forceinline__ double swap_sum(double a, double b)
 {
-    const uint64_t b = (uint64_t)__double_as_longlong(v);
-    const uint32_t lo = (uint32_t)b, hi = (uint32_t)(b >> 32);
+    const uint64_t x = (uint64_t)__double_as_longlong(a), y = (uint64_t)__double_as_longlong(b);
     double r[2];
     if constexpr (STEP == 16) {
-        const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-        const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+        const auto l = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
         for (int k = 0; k < 2; ++k)
             r[k] = __longlong_as_double((long long)((uint64_t)h[k] << 32 | l[k]));
     } else {
-        const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-        const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+        const auto l = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
         for (int k = 0; k < 2; ++k)
             r[k] = __longlong_as_double((long long)((uint64_t)h[k] << 32 | l[k]));
     }
     return r[0] + r[1];
 }
 
-// Sum over groups of LPI neighbouring lanes, on every lane of the group and
-// with the bits of a xor butterfly (at the steps of 4 and 8 a mirror of 8 or
-// 16 lanes meets the same partial sums, which are alike in a quad or half
+// Sum over groups of LPI <= 32 neighbouring lanes, on every lane of the group
+// and with the bits of a xor butterfly (at the steps of 4 and 8 a mirror of 8
+// or 16 lanes meets the same partial sums, which are alike in a quad or half
 // row by then).  Register moves only: the same sum through LDS permutes was
 // a fifth of a small block's evaluation.
 template <int LPI>
@@ -136,11 +136,43 @@ __device__ __forceinline__ double lane_sum(double v)
     if constexpr (LPI >= 16)
         v += dpp_of<0x140>(v);   // row_mirror
     if constexpr (LPI >= 32)
-        v = swap_sum<16>(v);
-    if constexpr (LPI >= 64)
-        v = swap_sum<32>(v);
+        v = swap_sum<16>(v, v);
     return v;
 }
+
+// The ten sums Q of a lane group (32 or 64 lanes) spread over its rows of 16
+// lanes: v[k] of a lane in row r ends as the sum of quantity lane_quantity(k,
+// r).  Two values share each register move of the first one or two steps, so
+// the whole takes 60-75 instructions instead of 270 (64 lanes, one value at a
+// time), a sixth of what a wave of a small block executes in all.  (Not in the
+// ensemble loop, where it measured 2 % slower: its registers are full.)
+template <int LPI>
+struct LaneSums {
+    static constexpr int N = LPI == 64 ? 3 : 5;
+    double v[N];
+    __device__ __forceinline__ LaneSums(const double *Q)
+    {
+        double p[5];
+#pragma unroll
+        for (int k = 0; k < 5; ++k)
+            p[k] = swap_sum<LPI == 64 ? 32 : 16>(Q[2 * k], Q[2 * k + 1]);
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            if constexpr (LPI == 64)
+                v[k] = k < 2 ? swap_sum<16>(p[2 * k], p[2 * k + 1]) : swap_sum<16>(p[4], p[4]);
+            else
+                v[k] = p[k];
+            v[k] = lane_sum<16>(v[k]);
+        }
+    }
+    // quantity of v[k] in the group's row r (-1: held by another row)
+    static __device__ __forceinline__ int quantity(int k, int r)
+    {
+        if (LPI == 32)
+            return 2 * k + r;
+        return k < 2 ? 4 * k + 2 * (r & 1) + (r >> 1) : ((r & 1) ? -1 : 8 + (r >> 1));
+    }
+};
 
 // LDS tile of NT source records, one 16-byte aligned record per source
 // (its fields side by side): with one lane per particle every lane reads
@@ -252,17 +284,13 @@ __device__ __forceinline__ void force_block(const R &J, const ForceWork &w, cons
     const int64_t st = rec_stride(J);
     auto fetch = [&](int64_t t0) {
         Rec r;
-        const int64_t jj = t0 + tid, e = jj * st;
-        if (jj < j1) {
-            r.x = ld<COH>(J.x + e); r.y = ld<COH>(J.y + e); r.z = ld<COH>(J.z + e);
-            r.m = ld<COH>(J.m + jj);
-            r.vx = (VV)ld<COH>(J.vx + e); r.vy = (VV)ld<COH>(J.vy + e); r.vz = (VV)ld<COH>(J.vz + e);
-            r.ax = (VA)ld<COH>(J.ax + e); r.ay = (VA)ld<COH>(J.ay + e); r.az = (VA)ld<COH>(J.az + e);
-        } else {
-            r.x = NULL_POS; r.y = NULL_POS; r.z = NULL_POS; r.m = 0.0;
-            r.vx = 0; r.vy = 0; r.vz = 0;
-            r.ax = 0; r.ay = 0; r.az = 0;
-        }
+        // past the range: the last source, without mass
+        const int64_t jt = t0 + tid, jj = jt < j1 ? jt : j1 - 1, e = jj * st;
+        r.x = ld<COH>(J.x + e); r.y = ld<COH>(J.y + e); r.z = ld<COH>(J.z + e);
+        r.m = ld<COH>(J.m + jj);
+        r.vx = (VV)ld<COH>(J.vx + e); r.vy = (VV)ld<COH>(J.vy + e); r.vz = (VV)ld<COH>(J.vz + e);
+        r.ax = (VA)ld<COH>(J.ax + e); r.ay = (VA)ld<COH>(J.ay + e); r.az = (VA)ld<COH>(J.az + e);
+        r.m = jt < j1 ? r.m : 0.0;
         return r;
     };
     Rec next;
@@ -469,7 +497,7 @@ __device__ __forceinline__ void force_block(const R &J, const ForceWork &w, cons
 
 #pragma unroll
     for (int u = 0; u < IPT; ++u) {
-        // ---- combine the LPI lanes of each active particle (xor butterfly)
+        // ---- combine the LPI lanes of each active particle
         double Q[NV + 1];
         if constexpr (P32) {
 #pragma unroll
@@ -488,28 +516,48 @@ __device__ __forceinline__ void force_block(const R &J, const ForceWork &w, cons
                 Q[q] = D[u][q];
         }
         Q[NV] = phi[u];
+        const int64_t ku = k[u], iu = i[u];
+        // the j == i pair adds exactly zero to a, da, d2a but -m_i / eps to the
+        // potential: that term, computed with the same operations, to remove it
+        auto self_phi = [&]() -> double {
+            if (EPS0 || !PHI || iu < j0 || iu >= j1)
+                return 0.0;
+            if constexpr (P32) {
+                const float e2f = (float)eps2;
+                const float ri = __builtin_amdgcn_rsqf(fmaf(0.0f, 0.0f, fmaf(0.0f, 0.0f, fmaf(0.0f, 0.0f, e2f))));
+                return (double)((float)J.m[iu] * ri);
+            } else {
+                const double r2 = fma(0.0, 0.0, fma(0.0, 0.0, fma(0.0, 0.0, eps2)));
+                return J.m[iu] * (MIXED ? rinv_mixed(r2) : rinv_f64(r2));
+            }
+        };
+        if constexpr (LPI >= 32 && AHEAD) {
+            const LaneSums<LPI> sums(Q);
+            if (!valid[u] || (lane & 15) != 0)
+                continue;
+#pragma unroll
+            for (int n = 0; n < LaneSums<LPI>::N; ++n) {
+                const int q = LaneSums<LPI>::quantity(n, js >> 4);
+                double v = sums.v[n];
+                if (q == NV)
+                    v += self_phi();
+                if (q < 0 || (q == NV && !PHI))
+                    continue;
+                if (part)
+                    put<COH>(part + ((int64_t)b * 10 + q) * n_act_total + ku, v);
+                else if (q < NV)
+                    (q < 3 ? out.vec[0] : (q < 6 ? out.vec[1] : out.vec[2]))[ku * out.sk + (q % 3) * out.sd] = v;
+                else if (out.pot)
+                    out.pot[ku] = v;
+            }
+            continue;
+        }
 #pragma unroll
         for (int q = 0; q < NV + 1; ++q)
             Q[q] = lane_sum<LPI>(Q[q]);
-
         if (!valid[u] || js != 0)
             continue;
-        const int64_t ku = k[u], iu = i[u];
-        // the j == i pair adds exactly zero to a, da, d2a but -m_i / eps to the
-        // potential: remove that term, computed with the same operations
-        if constexpr (!EPS0 && PHI) {
-            if (iu >= j0 && iu < j1) {
-                if constexpr (P32) {
-                    const float e2f = (float)eps2;
-                    const float ri = __builtin_amdgcn_rsqf(fmaf(0.0f, 0.0f, fmaf(0.0f, 0.0f, fmaf(0.0f, 0.0f, e2f))));
-                    Q[NV] += (double)((float)J.m[iu] * ri);
-                } else {
-                    const double r2 = fma(0.0, 0.0, fma(0.0, 0.0, fma(0.0, 0.0, eps2)));
-                    const double ri = MIXED ? rinv_mixed(r2) : rinv_f64(r2);
-                    Q[NV] += J.m[iu] * ri;
-                }
-            }
-        }
+        Q[NV] += self_phi();
         if (part) {
             double *pb = part + (int64_t)b * 10 * n_act_total + ku;
 #pragma unroll
