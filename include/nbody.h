@@ -281,9 +281,10 @@ int nbody_set_tuning(nbody_ctx *ctx, const nbody_launch *table, int32_t count);
    last part, where selecting the active set and reducing the split
    partials cost as much as the evaluation).  For a context with one
    system, no pinned launch shape and profiling off, nbody_step runs its
-   block steps inside one cooperative launch (64 workgroups, three grid
-   barriers per block step: schedule, prediction, evaluation with split
-   sources, fixed-order reduction and corrector) for as long as every
+   block steps inside one cooperative launch (64 workgroups and three grid
+   barriers per block step, or 128 and two for at most 4096 particles:
+   schedule, prediction, evaluation with split sources, fixed-order
+   reduction and corrector) for as long as every
    block has at most max_active active particles; a larger block goes
    through the host-sized path and the loop resumes after it.  Results
    equal the host-sized path's to the rounding of the split sums (a

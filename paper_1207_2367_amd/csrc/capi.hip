@@ -296,7 +296,7 @@ int64_t nb::ws_layout(int64_t n, int32_t nc, int32_t prec, Ctx *c, char *base)
     uint64_t *loop_min = (uint64_t *)take(2 * LOOP_GMAX * 8);
     int32_t *loop_cnt = (int32_t *)take(2 * LOOP_GMAX * 4);
     // ensemble plan: grp_of, first, size [LOOP_GMAX each], cl_off [LOOP_GMAX + 1],
-    // cl [nc]; part_off, part_cap [LOOP_GMAX each], seg [2 LOOP_GMAX]; results
+    // cl [nc]; part_off, part_cap [LOOP_GMAX each]; results
     int32_t *ens_i32 = nc > 1 ? (int32_t *)take((4 * LOOP_GMAX + 1 + nc) * 4) : nullptr;
     int64_t *ens_i64 = nc > 1 ? (int64_t *)take(4 * LOOP_GMAX * 8) : nullptr;
     unsigned long long *ens_res = nc > 1 ? (unsigned long long *)take(4 * 8) : nullptr;
@@ -720,13 +720,14 @@ int run_ensemble(Ctx &c, double t_target, nbody_step_stats *stats, bool *done)
 
 // Block steps inside one cooperative launch while the active sets stay at
 // or below the loop's limit (one system, no pinned shape, no profiling).
-// Measured on MI355X: a grid barrier costs a few microseconds and grows
-// with the number of workgroups, and the loop's few workgroups evaluate a
-// large block at low occupancy, so the loop uses 64 workgroups, takes blocks
-// of up to ~2^21 pairs, and is switched on automatically for systems of up
-// to 4096 bodies only (there it cuts the time per block step by 7-15 %
-// against the host-sized path with its schedule from per-level counts; at
-// 6144 bodies and beyond it is slower).
+// Measured on MI355X: a grid barrier costs 1 to 2 us and grows with the
+// number of workgroups, and the loop's few workgroups evaluate a large block
+// at low occupancy, so the loop uses 64 workgroups (128 for up to 4096
+// bodies), takes blocks of up to ~2^21 pairs, and is switched on
+// automatically for systems of up to 4096 bodies only (us per block step of
+// the host-sized path with its schedule from per-level counts against the
+// loop: 256 bodies 18.5 / 14.0, 1024 18.7 / 14.1, 2048 21.1 / 17.4, 4096
+// 21.7 / 18.3; with three barriers and beyond 4096 bodies it is slower).
 // *reason: LOOP_DONE (every particle at the target), LOOP_BIG (the next
 // block is larger than the limit: the host path takes it) or 0 when the
 // loop is not used.
@@ -738,7 +739,7 @@ int run_loop(Ctx &c, double t_target, nbody_step_stats *stats, int *reason)
     if (c.loop_amax < 0 && c.n > LOOP_AUTO_NMAX)
         return NBODY_OK;
     if (c.loop_grid < 0)
-        c.loop_grid = std::min(step_loop_max_grid(c), LOOP_GRID);
+        c.loop_grid = step_loop_max_grid(c);
     if (c.loop_grid <= 0)
         return NBODY_OK;
     // automatic limit: blocks of up to ~2^21 pairs, at least 4 particles,

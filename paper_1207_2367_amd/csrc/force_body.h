@@ -202,6 +202,57 @@ __device__ __forceinline__ SrcTile<PREC, NT> &src_tile()
     return t;
 }
 
+// The stored state of particle i that its prediction reads, and the Taylor
+// series of paper Sect. 3 item 1 (Horner form) to h later.
+struct PredIn {
+    double x[3], v[3], a[3], j[3], s[3], c[3], m, t;
+};
+struct Predicted {
+    double x[3], v[3], a[3];
+};
+
+template <bool COH = false>
+__device__ __forceinline__ PredIn load_pred(const State &st, int64_t n, int64_t i)
+{
+    PredIn q;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const int64_t e = (int64_t)d * n + i;
+        q.x[d] = ld<COH>(st.pos + e);
+        q.v[d] = ld<COH>(st.vel + e);
+        q.a[d] = ld<COH>(st.acc + e);
+        q.j[d] = ld<COH>(st.jrk + e);
+        q.s[d] = ld<COH>(st.snp + e);
+        q.c[d] = ld<COH>(st.crk + e);
+    }
+    q.m = st.mass[i];
+    q.t = ld<COH>(st.t + i);
+    return q;
+}
+
+__device__ __forceinline__ Predicted predict(const PredIn &q, double h)
+{
+    Predicted p;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const double x = q.x[d], v = q.v[d], a = q.a[d];
+        const double j = q.j[d], s = q.s[d], c = q.c[d];
+        p.x[d] = x + h * (v + h * (a * 0.5 + h * (j * (1.0 / 6) + h * (s * (1.0 / 24) + h * (c * (1.0 / 120))))));
+        p.v[d] = v + h * (a + h * (j * 0.5 + h * (s * (1.0 / 6) + h * (c * (1.0 / 24)))));
+        p.a[d] = a + h * (j + h * (s * 0.5 + h * (c * (1.0 / 6))));
+    }
+    return p;
+}
+
+// Sources predicted on the way to LDS: the state of a system of n particles
+// advanced to T, the active particles' indices from src0 in an LDS list.
+struct JState {
+    const State *st;
+    int64_t n;
+    double T;
+    const uint16_t *list;
+};
+
 // Distance between neighbouring particles of a source array
 template <typename R>
 __device__ __forceinline__ constexpr int64_t rec_stride(const R &)
@@ -209,10 +260,12 @@ __device__ __forceinline__ constexpr int64_t rec_stride(const R &)
     return 1;
 }
 __device__ __forceinline__ int64_t rec_stride(const JSrc &J) { return J.st; }
+__device__ __forceinline__ int64_t rec_stride(const JState &) { return 1; }
 
 // One workgroup's share of an evaluation: i-block g (IB active slots) against
 // source split b.  J: packed records of the precision, or the FP64 sources as
-// they stand (JSrc), rounded to the record's types on the way to LDS.  The launch kernel calls it with (blockIdx.x, blockIdx.y);
+// they stand (JSrc) or predicted (JState), rounded to the record's types on
+// the way to LDS.  The launch kernel calls it with (blockIdx.x, blockIdx.y);
 // the device-resident block-step loop calls it for the units it takes.
 // Every early return is uniform over the workgroup.  PHI: also sum the
 // potential (nbody_force); a block step's evaluation
@@ -286,12 +339,22 @@ __device__ __forceinline__ void force_block(const R &J, const ForceWork &w, cons
         Rec r;
         // past the range: the last source, without mass
         const int64_t jt = t0 + tid, jj = jt < j1 ? jt : j1 - 1, e = jj * st;
+        if constexpr (std::is_same<R, JState>::value) {
+            const PredIn q = load_pred<COH>(*J.st, J.n, jj);
+            const Predicted p = predict(q, J.T - q.t);
+            r.x = p.x[0]; r.y = p.x[1]; r.z = p.x[2];
+            r.m = jt < j1 ? q.m : 0.0;
+            r.vx = (VV)p.v[0]; r.vy = (VV)p.v[1]; r.vz = (VV)p.v[2];
+            r.ax = (VA)p.a[0]; r.ay = (VA)p.a[1]; r.az = (VA)p.a[2];
+            return r;
+        } else {
         r.x = ld<COH>(J.x + e); r.y = ld<COH>(J.y + e); r.z = ld<COH>(J.z + e);
         r.m = ld<COH>(J.m + jj);
         r.vx = (VV)ld<COH>(J.vx + e); r.vy = (VV)ld<COH>(J.vy + e); r.vz = (VV)ld<COH>(J.vz + e);
         r.ax = (VA)ld<COH>(J.ax + e); r.ay = (VA)ld<COH>(J.ay + e); r.az = (VA)ld<COH>(J.az + e);
         r.m = jt < j1 ? r.m : 0.0;
         return r;
+        }
     };
     Rec next;
     if constexpr (AHEAD)
@@ -307,7 +370,10 @@ __device__ __forceinline__ void force_block(const R &J, const ForceWork &w, cons
         k[u] = kb + il + u * NG;
         valid[u] = k[u] < s1;
         const int64_t kk = valid[u] ? k[u] : kb;
-        i[u] = w.idx ? (int64_t)ld<COH>(w.idx + kk) : kk;
+        if constexpr (std::is_same<R, JState>::value)
+            i[u] = o0 + J.list[kk];
+        else
+            i[u] = w.idx ? (int64_t)ld<COH>(w.idx + kk) : kk;
         if (i[u] < o0 || i[u] >= o1) {
             // an index outside its cluster (a caller's bad list): skip the
             // slot, load a valid particle, report
@@ -316,12 +382,21 @@ __device__ __forceinline__ void force_block(const R &J, const ForceWork &w, cons
             valid[u] = false;
             i[u] = o0;
         }
+        if constexpr (std::is_same<R, JState>::value) {
+            const PredIn q = load_pred<COH>(*J.st, J.n, i[u]);
+            const Predicted p = predict(q, J.T - q.t);
+            xi[u] = p.x[0]; yi[u] = p.x[1]; zi[u] = p.x[2];
+            vxi[u] = (VV)p.v[0]; vyi[u] = (VV)p.v[1]; vzi[u] = (VV)p.v[2];
+            axi[u] = (VA)p.a[0]; ayi[u] = (VA)p.a[1]; azi[u] = (VA)p.a[2];
+            continue;
+        } else {
         const int64_t e = i[u] * st;
         xi[u] = ld<COH>(J.x + e); yi[u] = ld<COH>(J.y + e); zi[u] = ld<COH>(J.z + e);
         vxi[u] = (VV)ld<COH>(J.vx + e); vyi[u] = (VV)ld<COH>(J.vy + e);
         vzi[u] = (VV)ld<COH>(J.vz + e);
         axi[u] = (VA)ld<COH>(J.ax + e); ayi[u] = (VA)ld<COH>(J.ay + e);
         azi[u] = (VA)ld<COH>(J.az + e);
+        }
     }
 
     // the active particles' values are in registers from here on: without
@@ -522,7 +597,9 @@ __device__ __forceinline__ void force_block(const R &J, const ForceWork &w, cons
         auto self_phi = [&]() -> double {
             if (EPS0 || !PHI || iu < j0 || iu >= j1)
                 return 0.0;
-            if constexpr (P32) {
+            if constexpr (std::is_same<R, JState>::value) {
+                return 0.0;   // (no potential in block steps)
+            } else if constexpr (P32) {
                 const float e2f = (float)eps2;
                 const float ri = __builtin_amdgcn_rsqf(fmaf(0.0f, 0.0f, fmaf(0.0f, 0.0f, fmaf(0.0f, 0.0f, e2f))));
                 return (double)((float)J.m[iu] * ri);

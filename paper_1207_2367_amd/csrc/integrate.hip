@@ -104,29 +104,6 @@ __device__ __forceinline__ void pack_one(const State &st, const JRecMixed &jm,
     pack_h(st, jm, jp, jd, prec, n, i, h);
 }
 
-// the stored state of particle i that its prediction reads
-struct PredIn {
-    double x[3], v[3], a[3], j[3], s[3], c[3], m, t;
-};
-
-__device__ __forceinline__ PredIn load_pred(const State &st, int64_t n, int64_t i)
-{
-    PredIn q;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        const int64_t e = (int64_t)d * n + i;
-        q.x[d] = st.pos[e];
-        q.v[d] = st.vel[e];
-        q.a[d] = st.acc[e];
-        q.j[d] = st.jrk[e];
-        q.s[d] = st.snp[e];
-        q.c[d] = st.crk[e];
-    }
-    q.m = st.mass[i];
-    q.t = st.t[i];
-    return q;
-}
-
 template <bool COH>
 __device__ __forceinline__ void store_pred(const PredIn &q, const JRecMixed &jm,
                                            const JRecPair32 &jp, const JRecF64 &jd, int prec,
@@ -168,15 +145,8 @@ __device__ __forceinline__ void store_pred(const PredIn &q, const JRecMixed &jm,
                                            const JRecPair32 &jp, const JRecF64 &jd, int prec,
                                            int64_t i, double h)
 {
-    double xp[3], vp[3], ap[3];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        const double x = q.x[d], v = q.v[d], a = q.a[d];
-        const double j = q.j[d], s = q.s[d], c = q.c[d];
-        xp[d] = x + h * (v + h * (a * 0.5 + h * (j * (1.0 / 6) + h * (s * (1.0 / 24) + h * (c * (1.0 / 120))))));
-        vp[d] = v + h * (a + h * (j * 0.5 + h * (s * (1.0 / 6) + h * (c * (1.0 / 24)))));
-        ap[d] = a + h * (j + h * (s * 0.5 + h * (c * (1.0 / 6))));
-    }
+    const Predicted p = predict(q, h);
+    const double *xp = p.x, *vp = p.v, *ap = p.a;
     const double m = q.m;
     if (prec == NBODY_PREC_MIXED) {
         put<COH>(jm.x + i, xp[0]); put<COH>(jm.y + i, xp[1]); put<COH>(jm.z + i, xp[2]);
@@ -228,14 +198,12 @@ __global__ __launch_bounds__(TPB) void predict_out_kernel(State st, int64_t n, d
     const int64_t i0 = (int64_t)blockIdx.x * TPB, i = i0 + threadIdx.x;
     if (i < n) {
         const PredIn q = load_pred(st, n, i);
-        const double h = t - q.t;
+        const Predicted p = predict(q, t - q.t);
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
-            const double x = q.x[d], v = q.v[d], a = q.a[d];
-            const double j = q.j[d], s = q.s[d], c = q.c[d];
-            rows[0][3 * threadIdx.x + d] = x + h * (v + h * (a * 0.5 + h * (j * (1.0 / 6) + h * (s * (1.0 / 24) + h * (c * (1.0 / 120))))));
-            rows[1][3 * threadIdx.x + d] = v + h * (a + h * (j * 0.5 + h * (s * (1.0 / 6) + h * (c * (1.0 / 24)))));
-            rows[2][3 * threadIdx.x + d] = a + h * (j + h * (s * 0.5 + h * (c * (1.0 / 6))));
+            rows[0][3 * threadIdx.x + d] = p.x[d];
+            rows[1][3 * threadIdx.x + d] = p.v[d];
+            rows[2][3 * threadIdx.x + d] = p.a[d];
         }
     }
     __syncthreads();
@@ -859,24 +827,27 @@ struct OldState {
     double h, t, a0[3], j0[3], s0[3], v0[3], r0[3];
 };
 
+template <bool COH = false>
 __device__ __forceinline__ OldState load_old(const State &st, int64_t n, int64_t i)
 {
     OldState o;
-    o.h = st.dt[i];
-    o.t = st.t[i];
+    o.h = ld<COH>(st.dt + i);
+    o.t = ld<COH>(st.t + i);
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         const int64_t e = (int64_t)d * n + i;
-        o.a0[d] = st.acc[e];
-        o.j0[d] = st.jrk[e];
-        o.s0[d] = st.snp[e];
-        o.v0[d] = st.vel[e];
-        o.r0[d] = st.pos[e];
+        o.a0[d] = ld<COH>(st.acc + e);
+        o.j0[d] = ld<COH>(st.jrk + e);
+        o.s0[d] = ld<COH>(st.snp + e);
+        o.v0[d] = ld<COH>(st.vel + e);
+        o.r0[d] = ld<COH>(st.pos + e);
     }
     return o;
 }
 
-__device__ __forceinline__ void correct_loaded(State st, int64_t n, int64_t i, const OldState &o,
+// Returns the particle's next time, t_new + dt_new.
+template <bool COH = false>
+__device__ __forceinline__ double correct_loaded(const State &st, int64_t n, int64_t i, const OldState &o,
                                                const double *a1, const double *j1,
                                                const double *s1, double t_target, double eta,
                                                double dt_min, double dt_max, uint32_t *err)
@@ -908,12 +879,12 @@ __device__ __forceinline__ void correct_loaded(State st, int64_t n, int64_t i, c
         a5[d] = x0;
         if (!isfinite(r1) || !isfinite(v1))
             bad |= ERR_NONFINITE;
-        st.pos[e] = r1;
-        st.vel[e] = v1;
-        st.acc[e] = a1[d];
-        st.jrk[e] = j1[d];
-        st.snp[e] = s1[d];
-        st.crk[e] = crk[d];
+        put<COH>(st.pos + e, r1);
+        put<COH>(st.vel + e, v1);
+        put<COH>(st.acc + e, a1[d]);
+        put<COH>(st.jrk + e, j1[d]);
+        put<COH>(st.snp + e, s1[d]);
+        put<COH>(st.crk + e, crk[d]);
     }
     const double A1 = sqrt(norm3(a1[0], a1[1], a1[2]) * norm3(s1[0], s1[1], s1[2]) +
                            j1[0] * j1[0] + j1[1] * j1[1] + j1[2] * j1[2]);
@@ -922,11 +893,12 @@ __device__ __forceinline__ void correct_loaded(State st, int64_t n, int64_t i, c
     const double crit = A4 == 0.0 ? INFINITY : eta * cbrt(A1 / A4);
     double dtn = h;
     bad |= block_dt(crit, h, t_new, t_target, dt_min, dt_max, &dtn);
-    st.t[i] = t_new;
+    put<COH>(st.t + i, t_new);
     if (!bad)
-        st.dt[i] = dtn;
+        put<COH>(st.dt + i, dtn);
     if (bad)
         atomicOr(err, bad);
+    return t_new + dtn;
 }
 
 __device__ __forceinline__ void correct_one(State st, int64_t n, int64_t i, const double *a1,
@@ -1105,7 +1077,8 @@ __global__ __launch_bounds__(TPB) void reduce_correct_kernel(
 // ------------------------------------------- device-resident block steps
 // Block steps of one system whose active sets stay small, run inside one
 // cooperative launch of G workgroups of TPB lanes (all resident at once),
-// with three grid barriers per step:
+// with three grid barriers per step (two for at most SMALL_N particles: see
+// small_loop_kernel):
 //   (1) each workgroup sweeps its own particle range [r0, r1) for the
 //       minimum of t + dt and how many particles reach it -> barrier;
 //   (2) every workgroup reads the G results and forms the block time T,
@@ -1285,8 +1258,8 @@ __device__ __forceinline__ const typename Smem<PREC>::R &loop_records(const JRec
 // is never reset: each pass advances it by the units plus one failed take
 // per workgroup, which every workgroup of the group adds to *base alike.
 // Which workgroup evaluates a unit does not change its partial sums.
-template <int PREC, bool EPS0, int LPI, bool AHEAD, bool COH>
-__device__ __forceinline__ void group_units(const typename Smem<PREC>::R &J, const ForceWork &w,
+template <int PREC, bool EPS0, int LPI, bool AHEAD, bool COH, typename R>
+__device__ __forceinline__ void group_units(const R &J, const ForceWork &w,
                                           double *part, int64_t n_act, double eps2, int64_t n_ib,
                                           int64_t B, int r, int W, uint32_t *ctr,
                                           uint32_t &base)
@@ -1443,6 +1416,182 @@ __global__ __launch_bounds__(TPB) void step_loop_kernel(
         }
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
+        res[0] = steps;
+        res[1] = act_sum;
+        res[2] = pairs;
+        res[3] = reason;
+        res[4] = stop_n;
+        __hip_atomic_store(&res[7], seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
+// The block steps of at most SMALL_N particles, with two barriers each
+// instead of three: every workgroup sweeps all next times by itself (kept in
+// tnext), builds the ascending active list in its own LDS and predicts the
+// sources and active particles of its evaluation units on the way to LDS, so
+// that neither the decision nor the list nor the source records are exchanged.
+//   (1) block time, N_act and the active list, alike in every workgroup; all
+//       stop together when nothing is due up to the target, when N_act
+//       exceeds a_max or when the error word is set;
+//   (2) the evaluation units -> barrier;
+//   (3) split sums and corrector, RC_SLOTS active slots per workgroup in turn
+//       -> barrier.
+// A block step here is a chain of barriers (1 to 2 us each) and reads of what
+// other workgroups wrote (about 1 us each).  Whole nbody_step calls per block
+// step, three barriers -> this kernel: 256 bodies 18.2 -> 15.4 us, 1000 19.5
+// -> 14.9, 2048 15.5 -> 13.4, 4096 18.4 -> 17.2; at 1000 bodies reading the
+// next times takes 0.9 us, decision, list and evaluation 6.7, corrector 2.6,
+// the barriers 2.2 and 0.9.
+// SMALL_N: the largest system that the automatic mode gives to a loop (the
+// sweep of all next times, K reads per thread, grows with n: 0.8 us at 256
+// bodies, 2.1 at 4096).  SMALL_GRID: the predicted sources cost each unit
+// more than packed records, so units spread over more workgroups: 2048
+// bodies 2430 us per call with 64, 2320 with 128; with 256 the barriers
+// cost more than that (2360; 1000 bodies 1590 -> 1870).
+// res as in step_loop_kernel.
+constexpr int SMALL_N = LOOP_AUTO_NMAX;
+constexpr int SMALL_GRID = 128;
+
+template <int PREC, bool EPS0>
+__global__ __launch_bounds__(TPB) void small_loop_kernel(
+    State st, int64_t n, double eps2, double t_target, double eta, double dt_min, double dt_max,
+    int64_t a_max, double *part, double *tnext, uint32_t *bar, uint32_t *err, int64_t *hist,
+    int64_t *res, int64_t seq)
+{
+    constexpr int K = SMALL_N / TPB;
+    __shared__ double sum[9][RC_SLOTS];
+    __shared__ uint16_t list[SMALL_N];
+    __shared__ uint64_t rv[TPB / 64];
+    __shared__ int cnt[K * TPB / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t G = gridDim.x;
+    uint32_t *uctr = G >= 3 ? bar + LOOP_FLAG * 2 : nullptr, ubase = 0, epoch = 0;
+    int64_t steps = 0, act_sum = 0, pairs = 0, stop_n = 0;
+    int reason = 0;
+
+    for (bool first = true;; first = false) {
+        // (1) next times of all particles: from the state at first (and into
+        // tnext, shared out over the workgroups)
+        const uint32_t failed = ld<true>(err);
+        uint64_t tn[K], m = ~0ull;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int i = k * TPB + tid;
+            tn[k] = ~0ull;
+            if (i < n) {
+                const double t = first ? st.t[i] + st.dt[i] : ld<true>(tnext + i);
+                if (first && (uint32_t)k % G == blockIdx.x)
+                    put<true>(tnext + i, t);
+                tn[k] = (uint64_t)__double_as_longlong(t);
+            }
+            m = tn[k] < m ? tn[k] : m;
+        }
+        m = wave_min_u64(m);
+        if (lane == 0)
+            rv[wave] = m;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < TPB / 64; ++w)
+            m = rv[w] < m ? rv[w] : m;
+        const double T = __longlong_as_double((long long)m);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const uint64_t mask = __ballot(tn[k] == m);
+            if (lane == 0)
+                cnt[k * (TPB / 64) + wave] = __popcll(mask);
+        }
+        __syncthreads();
+        static_assert(K * TPB / 64 == 64, "one count per lane");
+        const int c = cnt[lane];
+        int incl = c;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int y = __shfl_up(incl, d, 64);
+            incl += lane >= d ? y : 0;
+        }
+        const int64_t n_act = __builtin_amdgcn_readlane(incl, 63);
+        if (failed)
+            reason = LOOP_ERR;
+        else if (!(T <= t_target))
+            reason = LOOP_DONE;
+        else if (n_act > a_max)
+            reason = LOOP_BIG;
+        if (reason) {
+            stop_n = n_act;
+            break;
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const uint64_t mask = __ballot(tn[k] == m);
+            const int base = __shfl(incl - c, k * (TPB / 64) + wave, 64);
+            if (tn[k] == m)
+                list[base + __popcll(mask & ((1ull << lane) - 1ull))] = (uint16_t)(k * TPB + tid);
+        }
+        if (blockIdx.x == 0 && tid == 0) {
+            int bb = 0;
+            while ((int64_t(1) << (bb + 1)) <= n_act)
+                ++bb;
+            atomicAdd((unsigned long long *)&hist[bb], 1ull);
+        }
+        ++steps;
+        act_sum += n_act;
+        pairs += n_act * n;
+        __syncthreads();
+        // (2) evaluation units, shaped as in step_loop_kernel, but split down
+        // to one tile (at 1000 bodies four splits instead of two)
+        int64_t B = 1;
+        while (B * 2 <= LOOP_BMAX && (B * 2 - 1) * LOOP_NT < n)
+            B *= 2;
+        const int lpi = n_act * 8 >= TPB ? 8 : 32;
+        const int64_t ib = (int64_t)LOOP_NW * (64 / lpi);
+        const int64_t n_ib = (n_act + ib - 1) / ib;
+        ForceWork w{};
+        w.n_act = n_act;
+        w.n_src = n;
+        w.split = (int32_t)B;
+        w.nc = 1;
+        w.n_blocks = n_ib;
+        const JState J{&st, n, T, list};
+        if (lpi == 32)
+            group_units<PREC, EPS0, 32, false, true>(J, w, part, n_act, eps2, n_ib, B, (int)blockIdx.x,
+                                                    (int)G, uctr, ubase);
+        else
+            group_units<PREC, EPS0, 8, false, true>(J, w, part, n_act, eps2, n_ib, B, (int)blockIdx.x,
+                                                   (int)G, uctr, ubase);
+        if (!grid_sync(bar, G, err, epoch)) {
+            reason = LOOP_ERR;
+            break;
+        }
+        // (3) split sums (fixed order) and the corrector
+        const int64_t bc = splits_used(n, B, split_unit(lpi, LOOP_NW));
+        const int q = tid / RC_SLOTS, kl = tid % RC_SLOTS;
+        for (int64_t k0 = (int64_t)blockIdx.x * RC_SLOTS; k0 < n_act; k0 += (int64_t)G * RC_SLOTS) {
+            const int64_t k = k0 + kl;
+            const bool in = k < n_act;
+            const bool corr = tid < RC_SLOTS && in;
+            const int64_t i = in ? list[k] : 0;
+            OldState o{};
+            if (corr)
+                o = load_old<true>(st, n, i);
+            if (q < 9 && in)
+                sum[q][kl] = sum_splits<true>(part + (int64_t)q * n_act + k, 10 * n_act, bc);
+            __syncthreads();
+            if (corr) {
+                const double a1[3] = {sum[0][kl], sum[1][kl], sum[2][kl]};
+                const double j1[3] = {sum[3][kl], sum[4][kl], sum[5][kl]};
+                const double s1[3] = {sum[6][kl], sum[7][kl], sum[8][kl]};
+                const double t = correct_loaded<true>(st, n, i, o, a1, j1, s1, t_target, eta,
+                                                     dt_min, dt_max, err);
+                put<true>(tnext + i, t);
+            }
+            __syncthreads();
+        }
+        if (!grid_sync(bar, G, err, epoch)) {
+            reason = LOOP_ERR;
+            break;
+        }
+    }
+    if (blockIdx.x == 0 && tid == 0) {
         res[0] = steps;
         res[1] = act_sum;
         res[2] = pairs;
@@ -1960,17 +2109,26 @@ namespace {
 // the loop kernel for a context's precision and softening
 const void *step_loop_fn(const Ctx &c)
 {
-    const bool e0 = c.eps == 0.0;
+    const bool e0 = c.eps == 0.0, small = c.n <= SMALL_N;
+    auto pick = [&](const void *s0, const void *s1, const void *l0, const void *l1) {
+        return small ? (e0 ? s0 : s1) : (e0 ? l0 : l1);
+    };
     switch (c.cfg.precision) {
     case NBODY_PREC_FP64:
-        return e0 ? (const void *)step_loop_kernel<PREC_F64, true>
-                  : (const void *)step_loop_kernel<PREC_F64, false>;
+        return pick((const void *)small_loop_kernel<PREC_F64, true>,
+                    (const void *)small_loop_kernel<PREC_F64, false>,
+                    (const void *)step_loop_kernel<PREC_F64, true>,
+                    (const void *)step_loop_kernel<PREC_F64, false>);
     case NBODY_PREC_FP32PAIR:
-        return e0 ? (const void *)step_loop_kernel<PREC_PAIR32, true>
-                  : (const void *)step_loop_kernel<PREC_PAIR32, false>;
+        return pick((const void *)small_loop_kernel<PREC_PAIR32, true>,
+                    (const void *)small_loop_kernel<PREC_PAIR32, false>,
+                    (const void *)step_loop_kernel<PREC_PAIR32, true>,
+                    (const void *)step_loop_kernel<PREC_PAIR32, false>);
     default:
-        return e0 ? (const void *)step_loop_kernel<PREC_MIXED, true>
-                  : (const void *)step_loop_kernel<PREC_MIXED, false>;
+        return pick((const void *)small_loop_kernel<PREC_MIXED, true>,
+                    (const void *)small_loop_kernel<PREC_MIXED, false>,
+                    (const void *)step_loop_kernel<PREC_MIXED, true>,
+                    (const void *)step_loop_kernel<PREC_MIXED, false>);
     }
 }
 
@@ -2049,8 +2207,8 @@ int step_loop_max_grid(const Ctx &c)
         return 0;
     if (!coop || per_cu < 1 || cus < 1)
         return 0;
-    // one workgroup per compute unit: more would only lengthen the barriers
-    return cus < LOOP_GMAX ? cus : LOOP_GMAX;
+    // at most one workgroup per compute unit: more would only lengthen the barriers
+    return std::min(cus, c.n <= SMALL_N ? SMALL_GRID : LOOP_GRID);
 }
 
 // Device-resident block steps (see step_loop_kernel).  The caller has reset
@@ -2071,14 +2229,17 @@ hipError_t launch_step_loop(const Ctx &c, double t_target, int64_t a_max, int gr
     double *part = c.part;
     uint64_t *wmin = c.d_loop_min;
     int32_t *wcnt = c.d_loop_cnt;
+    double *tnext = c.d_phi;   // (free outside the energy)
     uint32_t *bar = c.d_loop_bar;
     uint32_t *err = c.d_err;
     int64_t *hist = c.d_info + 8;
     int64_t *res = c.d_tot + 8;
+    void *small[] = {&st, &n, &eps2, &tt, &eta, &dmin, &dmax, &am, &part, &tnext, &bar, &err,
+                     &hist, &res, &sq};
     void *args[] = {&st,   &jm,  &jp,  &jd,   &prec, &n,    &eps2, &tt,  &eta,  &dmin, &dmax, &am,
-                    &act,  &part, &wmin, &wcnt, &bar, &err, &hist, &res, &sq};
-    return hipLaunchCooperativeKernel(step_loop_fn(c), dim3((unsigned)grid), dim3(TPB), args, 0,
-                                      s);
+                    &act,  &part, &wmin, &wcnt, &bar, &err,  &hist, &res, &sq};
+    return hipLaunchCooperativeKernel(step_loop_fn(c), dim3((unsigned)grid), dim3(TPB),
+                                      n <= SMALL_N ? small : args, 0, s);
 }
 
 hipError_t launch_blocks(const Ctx &c, int64_t ib, int64_t cap, hipStream_t s)
