@@ -26,8 +26,8 @@
 //     the snap is the least amplified: the fifth-derivative estimate of the
 //     step criterion multiplies the acceleration's absolute error by
 //     ~720/h^5 but the snap's by at most ~1/h^3;
-//   - the LPI lanes of a particle are combined by a xor butterfly of wave
-//     shuffles (bitwise identical on every lane, fixed order);
+//   - the LPI lanes of a particle are combined by cross-lane register moves in
+//     a fixed order (lane_sum, LaneSums);
 //   - the FP64 passes take 1/r from the same FP32 seed, refined to FP64
 //     accuracy by one third-order step;
 //   - the potential energy (energy_kernel) takes every pair once, with a
@@ -41,6 +41,8 @@
 //   - the per-workgroup body (force_block) lives in force_body.h, shared by
 //     the launch kernel here and the device-resident block-step loop;
 //   - a block step's evaluation skips the potential (template flag PHI).
+#include <cmath>
+
 #include "force_body.h"
 
 namespace nb {
@@ -472,8 +474,9 @@ hipError_t launch_energy_pot(Ctx &c, int *split, const double **phi, hipStream_t
     for (size_t k = 0; k + 1 < c.off.size(); ++k)
         ncmax = std::max(ncmax, c.off[k + 1] - c.off[k]);
     // particles per lane: the masked ends of a workgroup's window cost 256 of
-    // them each, a few per cent of half the cluster at these sizes
-    const int ipt = ncmax >= 65536 ? 4 : (ncmax >= 16384 ? 2 : 1);
+    // them each, a few per cent of half the cluster at these sizes (two
+    // from 16,384 left too few workgroups: 25,000 bodies 283 us, one 216)
+    const int ipt = ncmax >= 65536 ? 4 : (ncmax >= 32768 ? 2 : 1);
     const int64_t ib = 256 * ipt;
     hipError_t e = hipSuccess;
     ForceWork w{};
@@ -491,14 +494,24 @@ hipError_t launch_energy_pot(Ctx &c, int *split, const double **phi, hipStream_t
         w.blk_first = c.d_blk_first;
         w.n_blocks = cap;
     }
-    // splits of at least two tiles, up to ~8192 workgroups (several rounds of
-    // the 1024-2048 resident ones: 100,003 bodies 2.72 ms in 1564 workgroups
-    // of one particle per lane, 2.47 ms in 6272 of four), and the partial
-    // sums within the split buffer
-    *split = 1;
-    while (w.n_blocks * *split * 2 <= 8192 && (ncmax / 2 + ib) / (*split * 2) >= 2 * 256 &&
-           (int64_t)*split * 2 * n <= 10 * c.part_cap)
-        *split *= 2;
+    // splits of at least a tile, up to ~8192 workgroups (several rounds of the
+    // 1024-2048 resident ones: 100,003 bodies 2.72 ms in 1564 workgroups of
+    // one particle per lane, 2.46 ms in 6000-8000 of four), and the partial
+    // sums within the split buffer; of the upper half of these the number that
+    // fills the 256 compute units most evenly (against the largest power of
+    // two of at least two tiles: 9000 bodies 88 -> 80 us, 13,000 113 -> 98,
+    // 5000 82 -> 64, 66,000 1158 -> 1139)
+    int64_t most = std::min<int64_t>(8192 / w.n_blocks, (ncmax / 2 + ib) / 256);
+    most = std::max<int64_t>(1, std::min<int64_t>(most, 10 * c.part_cap / n));
+    *split = (int)most;
+    double best = 0.0;
+    for (int64_t k = most; k > most / 2; --k) {
+        const double rounds = (double)(w.n_blocks * k) / 256.0, even = rounds / std::ceil(rounds);
+        if (even > best + 0.01) {
+            best = even;
+            *split = (int)k;
+        }
+    }
     w.split = *split;
     const double *X = c.st.pos, *Y = c.st.pos + n, *Z = c.st.pos + 2 * n;
     double *dst = *split > 1 ? c.part : c.d_phi;

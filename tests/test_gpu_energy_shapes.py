@@ -1,5 +1,5 @@
 """The energy's pair pass at the edges of its shapes: one, two and four
-particles per lane (clusters below 16,384, from there, and from 65,536 bodies),
+particles per lane (clusters below 32,768, from there, and from 65,536 bodies),
 odd and even sizes, workgroups that are partly empty, one tile and several
 splits.  Against the oracle's energy, both in FP64: the same pairs in another
 order, so 1e-12 relative for the energies and for L against the sum of its
@@ -14,7 +14,8 @@ from gpu_helpers import log_case
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("sizes", [[1], [2], [3], [255, 257], [1025], [16384], [16901, 300], [66049]],
+@pytest.mark.parametrize("sizes", [[1], [2], [3], [255, 257], [1025], [16384], [16901, 300], [32768], [33025, 300],
+                                   [66049]],
                          ids=lambda s: "-".join(map(str, s)))
 @pytest.mark.parametrize("eps", [1e-4, 0.0], ids=["soft", "eps0"])
 def test_energy_shapes(sizes, eps):
