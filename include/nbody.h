@@ -152,8 +152,12 @@ int nbody_force(nbody_ctx *ctx, int64_t n_act, const int32_t *d_idx,
    the caller's arrays d_mass[n], d_pos/d_vel/d_acc[n][3] (row-major FP64,
    one system, softening eps >= 0, evaluation precision as in
    nbody_config); outputs, index list and NULL rules as for nbody_force
-   (d_idx strictly ascending in [0, n), not checked).  The source records
-   and split-source partials live in a fixed 64 MiB device array inside the
+   (d_idx strictly ascending in [0, n), not checked).  Outputs may lie on top
+   of d_mass, d_pos, d_vel or d_acc (an update in place, such as d_acc_out =
+   d_acc with every particle listed): the inputs enter with their values from
+   before the call.  Without the potential the sources are packed into records
+   first, with it they are read where they are; those records and the
+   split-source partials live in a fixed 64 MiB device array inside the
    library, one per GPU, kept until the process ends; the call allocates
    nothing.  Limit: n * R + 80 * n_act plus about 1 KiB within 64 MiB,
    R = 68 (mixed), 56 (FP32 pair), 80 (FP64) bytes -- e.g. up to

@@ -228,6 +228,26 @@ int64_t noalloc_layout(int64_t n, int32_t prec, Ctx *c, unsigned char *base)
     return o + 2 * ALIGN;
 }
 
+// Whether one of the outputs shares memory with one of the sources, so that
+// storing the outputs while sources are still fetched would change them.
+bool outputs_on_sources(int64_t n, int64_t n_act, const double *mass, const double *pos,
+                        const double *vel, const double *acc, const ForceOut &out)
+{
+    struct Range {
+        uintptr_t b, e;
+    };
+    auto range = [](const double *p, int64_t count) {
+        const uintptr_t b = reinterpret_cast<uintptr_t>(p);
+        return Range{b, b + (uintptr_t)count * sizeof(double)};
+    };
+    for (const Range &i : {range(mass, n), range(pos, 3 * n), range(vel, 3 * n), range(acc, 3 * n)})
+        for (const Range &o : {range(out.vec[0], 3 * n_act), range(out.vec[1], 3 * n_act),
+                               range(out.vec[2], 3 * n_act), range(out.pot, n_act)})
+            if (o.b < i.e && i.b < o.e)
+                return true;
+    return false;
+}
+
 }  // namespace
 
 // Workspace layout: every array 256-byte aligned.  With base == nullptr
@@ -1563,7 +1583,10 @@ int nbody_force_noalloc(int64_t n, const double *d_mass, const double *d_pos,
     if (!d_pot_out &&
         launch_pack_arrays(c, d_mass, d_pos, d_vel, d_acc, c.stream) != hipSuccess)
         return NBODY_EDEVICE;
-    if (launch_force(c, w, L, out, n_act, c.stream) != hipSuccess)
+    // an update in place (an output on top of an input) keeps its sources until
+    // the evaluation is done; the packed records are such a copy already
+    const bool staged = d_pot_out && outputs_on_sources(n, n_act, d_mass, d_pos, d_vel, d_acc, out);
+    if (launch_force(c, w, L, out, n_act, c.stream, true, staged) != hipSuccess)
         return NBODY_EDEVICE;
     return NBODY_OK;
 }

@@ -425,14 +425,15 @@ Launch rule_launch(int64_t n_act, int64_t n_src, int64_t part_cap, int prec)
 }
 
 hipError_t launch_force(Ctx &c, const ForceWork &w, const Launch &L,
-                        const ForceOut &out, int64_t n_act_total, hipStream_t s, bool reduce)
+                        const ForceOut &out, int64_t n_act_total, hipStream_t s, bool reduce,
+                        bool staged)
 {
     if (n_act_total <= 0 || w.n_blocks <= 0)
         return hipSuccess;
     const int lg = ilog2(L.lpi);
     const bool eps0 = c.eps == 0.0;
     const double eps2 = c.eps * c.eps;
-    double *part = w.split > 1 ? c.part : nullptr;
+    double *part = w.split > 1 || staged ? c.part : nullptr;
     // one cluster: no workgroups for splits without sources
     const int64_t gy = w.blk_cluster ? w.split
                                      : splits_used(w.n_src, w.split, split_unit(L.lpi, L.waves));
@@ -455,7 +456,7 @@ hipError_t launch_force(Ctx &c, const ForceWork &w, const Launch &L,
         go(std::integral_constant<int, PREC_F64>{}, c.jd);
     prof_end(c, rec);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || w.split <= 1 || !reduce)
+    if (e != hipSuccess || !part || !reduce)
         return e;
     const int rr = prof_begin(c, PH_REDUCE);
     launch_reduce(c.part, w.split, n_act_total, out, w, c.d_cluster_of,

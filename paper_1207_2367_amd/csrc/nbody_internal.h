@@ -132,9 +132,11 @@ __host__ __device__ inline int64_t split_begin(int64_t nsrc, int64_t used, int64
 struct Ctx;
 
 // force.hip
+// (staged: the outputs overlap the sources, so that no workgroup of the
+// evaluation may store them: partial sums and the reduction even for one split)
 hipError_t launch_force(Ctx &c, const ForceWork &w, const Launch &L,
                         const ForceOut &out, int64_t n_act_total, hipStream_t s,
-                        bool reduce = true);
+                        bool reduce = true, bool staged = false);
 hipError_t launch_reduce_correct(const Ctx &c, const ForceWork &w, int split, int nt,
                                  int64_t n_act, double t_target, hipStream_t s,
                                  bool levels = false, int64_t seq = 0, bool *tail = nullptr);

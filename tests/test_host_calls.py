@@ -1,0 +1,99 @@
+"""The host side of the C ABI without a GPU: libnbody.so runs against a
+stand-in for the HIP runtime (hip_stub.c) that logs the kernels instead of
+running them, in a process of its own.
+
+* ``nbody_force_noalloc`` with an output on top of an input: the evaluation
+  may store no output while another workgroup still fetches its sources from
+  that memory, so it writes partial sums, also for a single split, and the
+  split sums write the outputs when it is done.  Calls without overlap keep
+  the single launch, calls without the potential pack their sources first.
+"""
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+LIB = os.path.join(os.path.dirname(HERE), "paper_1207_2367_amd", "libnbody.so")
+
+PRELUDE = """
+import ctypes as C, json, sys
+stub = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)   # its symbols come before the runtime's
+lib = C.CDLL(sys.argv[2])
+vp, i64 = C.c_void_p, C.c_int64
+stub.stub_name.restype, stub.stub_part.restype = C.c_char_p, vp
+def var(name):
+    return C.c_int.in_dll(stub, name)
+def log():
+    q = [(stub.stub_name(k).decode(), stub.stub_gx(k), stub.stub_gy(k), stub.stub_part(k) is not None)
+         for k in range(var("stub_launches").value)]
+    var("stub_launches").value = 0
+    return q
+"""
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("stub") / "hip_stub.so")
+    subprocess.check_call(["gcc", "-O1", "-Wall", "-shared", "-fPIC", "-o", so,
+                           os.path.join(HERE, "hip_stub.c")])
+
+    def run(code):
+        r = subprocess.run([sys.executable, "-c", PRELUDE + code, so, LIB], capture_output=True,
+                           text=True, timeout=120)
+        assert r.returncode == 0, r.stderr
+        return json.loads(r.stdout)
+    return run
+
+
+NOALLOC = """
+f = lib.nbody_force_noalloc
+f.argtypes = [i64, vp, vp, vp, vp, C.c_double, C.c_int32, i64] + [vp] * 6
+B = 1 << 32   # addresses far apart; nothing is read or written
+def call(n, na, prec, over):
+    mass, pos, vel, acc, idx, a, j, s, p = (vp((k + 2) * B).value for k in range(9))
+    if over == "acc":
+        a = acc
+    elif over == "acc tail":        # only the last particle's row
+        a = acc + 24 * (n - 1)
+    elif over == "vel":
+        s = vel
+    elif over == "pos end":         # an output that ends inside the first row
+        j = pos - 24 * na + 8
+    elif over == "mass":
+        p = mass
+    elif over == "beside":          # right behind and right before: no overlap
+        a, j = acc + 24 * n, acc - 24 * na
+    elif over == "no pot":
+        a, p = acc, None
+    rc = f(n, mass, pos, vel, acc, 1e-4, prec, na, idx, a, j, s, p, None)
+    return rc, log()
+out = []
+for n, na in ((64, 64), (256, 256), (511, 511), (1000, 1000), (1000, 3), (300000, 200000)):
+    for prec in (0, 2):
+        for over in ("", "beside", "acc", "acc tail", "vel", "pos end", "mass", "no pot"):
+            out.append((n, na, over, *call(n, na, prec, over)))
+print(json.dumps(out))
+"""
+
+
+def test_noalloc_outputs_on_inputs(host):
+    single = 0
+    for n, na, over, rc, launches in host(NOALLOC):
+        what = (n, na, over, launches)
+        assert rc == 0, what
+        names = [q[0] for q in launches]
+        if over == "no pot":
+            assert "pack_arrays" in names[0] and "force_kernel" in names[1], what
+            continue
+        assert "force_kernel" in names[0], what
+        splits, staged = launches[0][2], launches[0][3]
+        if over in ("", "beside"):
+            assert staged == (splits > 1), what
+            single += splits == 1
+        else:
+            assert staged, what
+        assert len(names) == 1 + staged and all("reduce_split" in q for q in names[1:]), what
+    assert single >= 10   # sizes that the rule evaluates in one split are among them
