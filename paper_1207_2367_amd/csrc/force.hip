@@ -54,10 +54,16 @@ struct alignas(16) PotSrc {
     double x, y, z, m;
 };
 
+// Softening of the energy pass: none; one whose square is a normal FP32 number,
+// which rinv_f64 needs; one whose square is not.  With the last, the particle's
+// own slot (r2 = eps2, masked) has no finite 1/r, so masked slots are put at
+// r2 = 1: two more instructions per pair of a masked tile, 0.6-1 % of the pass.
+enum : int { EPS_NONE, EPS_NORMAL, EPS_ODD };
+
 // Potential terms of one LDS tile of NT sources for the IPT particles of one
 // lane: phi -= m_j / r_ij, FP64.  MASK keeps only the tile slots lo <= t <= hi
 // of each particle.
-template <int NT, int IPT, bool MASK, bool EPS0>
+template <int NT, int IPT, bool MASK, int EPS>
 __device__ __forceinline__ void pot_tile(const PotSrc *s, const double *xi, const double *yi,
                                          const double *zi, double eps2, const int *lo,
                                          const int *hi, double *phi)
@@ -68,9 +74,11 @@ __device__ __forceinline__ void pot_tile(const PotSrc *s, const double *xi, cons
 #pragma unroll
         for (int u = 0; u < IPT; ++u) {
             const double dx = sx - xi[u], dy = sy - yi[u], dz = sz - zi[u];
-            const double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, eps2)));
+            double r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, eps2)));
+            if constexpr (MASK && EPS == EPS_ODD)
+                r2 = (t >= lo[u] && t <= hi[u]) ? r2 : 1.0;
             double rinv = rinv_f64(r2);
-            if constexpr (EPS0)
+            if constexpr (EPS == EPS_NONE)
                 rinv = r2 > 0.0 ? rinv : 0.0;
             // the mass is masked, not 1/r: the compiler would branch around 1/r
             double m = sm;
@@ -147,7 +155,7 @@ __global__ __launch_bounds__(NW * 64, force_waves(PREC, LPI, IPT)) void force_ke
 // lanes mask only the tiles at the two ends of the union.  Output: partial
 // sums -sum m_j / r_ij per particle and split, out[b n + i].  Nothing is done
 // if the error word says that the particles are not at one time.
-template <bool EPS0, int IPT>
+template <int EPS, int IPT>
 __global__ __launch_bounds__(256) void energy_kernel(const double *X, const double *Y,
                                                      const double *Z, const double *M,
                                                      ForceWork w, double *out, int64_t n,
@@ -206,7 +214,7 @@ __global__ __launch_bounds__(256) void energy_kernel(const double *X, const doub
         // range covers the whole tile when t0 > last and t0 + NT - 1 <= ib0 + wmin
         int lo[IPT], hi[IPT];
         if (t0 > last && t0 + NT - 1 <= ib0 + wmin) {
-            pot_tile<NT, IPT, false, EPS0>(s, xi, yi, zi, eps2, lo, hi, phi);
+            pot_tile<NT, IPT, false, EPS>(s, xi, yi, zi, eps2, lo, hi, phi);
         } else {
 #pragma unroll
             for (int u = 0; u < IPT; ++u) {
@@ -214,7 +222,7 @@ __global__ __launch_bounds__(256) void energy_kernel(const double *X, const doub
                 lo[u] = a < 0 ? 0 : (a > NT ? NT : (int)a);
                 hi[u] = z < -1 ? -1 : (z > NT - 1 ? NT - 1 : (int)z);
             }
-            pot_tile<NT, IPT, true, EPS0>(s, xi, yi, zi, eps2, lo, hi, phi);
+            pot_tile<NT, IPT, true, EPS>(s, xi, yi, zi, eps2, lo, hi, phi);
         }
     }
 #pragma unroll
@@ -517,10 +525,15 @@ hipError_t launch_energy_pot(Ctx &c, int *split, const double **phi, hipStream_t
     const double *X = c.st.pos, *Y = c.st.pos + n, *Z = c.st.pos + 2 * n;
     double *dst = *split > 1 ? c.part : c.d_phi;
     *phi = dst;
-    const bool e0 = c.eps == 0.0;
-    auto k = ipt == 4 ? (e0 ? energy_kernel<true, 4> : energy_kernel<false, 4>)
-                      : (ipt == 2 ? (e0 ? energy_kernel<true, 2> : energy_kernel<false, 2>)
-                                  : (e0 ? energy_kernel<true, 1> : energy_kernel<false, 1>));
+    const float e2 = (float)(c.eps * c.eps);
+    auto pick = [&](auto none, auto normal, auto odd) {
+        return c.eps == 0.0 ? none : (std::isnormal(e2) ? normal : odd);
+    };
+    const auto k =
+        ipt == 4 ? pick(energy_kernel<EPS_NONE, 4>, energy_kernel<EPS_NORMAL, 4>, energy_kernel<EPS_ODD, 4>)
+        : ipt == 2
+            ? pick(energy_kernel<EPS_NONE, 2>, energy_kernel<EPS_NORMAL, 2>, energy_kernel<EPS_ODD, 2>)
+            : pick(energy_kernel<EPS_NONE, 1>, energy_kernel<EPS_NORMAL, 1>, energy_kernel<EPS_ODD, 1>);
     const int rec = prof_begin(c, PH_ENERGY);
     hipLaunchKernelGGL(k, dim3((unsigned)w.n_blocks, (unsigned)*split), dim3(256), 0, s, X, Y, Z,
                        (const double *)c.st.mass, w, dst, n, c.eps * c.eps);
