@@ -149,7 +149,7 @@ __global__ __launch_bounds__(NW * 64, force_waves(PREC, LPI, IPT)) void force_ke
 // workgroup does the same work (no triangle).  A workgroup holds IB = 256 IPT
 // consecutive particles, IPT per lane (each source read from LDS serves IPT
 // pairs: with one, the two 128-bit reads per pair take 64 of the 71 cycles of
-// its vector instructions; 2150 / 2280 / 2330 G pairs/s with 1 / 2 / 4); the
+// its vector instructions; 100,003 bodies 2.38 and 2.28 ms with 1 and 2); the
 // union of their windows (virtual positions ib0 + 1 .. last + W, folded back
 // into the cluster) goes through LDS in tiles of 256, split over grid.y = B;
 // lanes mask only the tiles at the two ends of the union.  Output: partial
@@ -479,13 +479,29 @@ hipError_t launch_force(Ctx &c, const ForceWork &w, const Launch &L,
 hipError_t launch_energy_pot(Ctx &c, int *split, const double **phi, hipStream_t s)
 {
     const int64_t n = c.n;
-    int64_t ncmax = 0;
+    int64_t ncmax = 0, wg1 = 0, wg2 = 0;   // workgroups with one and two particles per lane
+    double pairs = 0.0, pairs_big = 0.0;   // pair slots, and those of clusters from half the
+    int64_t wg_big = 0;                    // largest, with one particle per lane
     for (size_t k = 0; k + 1 < c.off.size(); ++k)
         ncmax = std::max(ncmax, c.off[k + 1] - c.off[k]);
-    // particles per lane: the masked ends of a workgroup's window cost 256 of
-    // them each, a few per cent of half the cluster at these sizes (two
-    // from 16,384 left too few workgroups: 25,000 bodies 283 us, one 216)
-    const int ipt = ncmax >= 65536 ? 4 : (ncmax >= 32768 ? 2 : 1);
+    for (size_t k = 0; k + 1 < c.off.size(); ++k) {
+        const int64_t nk = c.off[k + 1] - c.off[k], wg = (nk + 255) / 256;
+        const double p = (double)wg * (double)(nk / 2 + 256);
+        wg1 += wg;
+        wg2 += (nk + 511) / 512;
+        pairs += p;
+        if (2 * nk >= ncmax) {
+            pairs_big += p;
+            wg_big += wg;
+        }
+    }
+    // Two particles per lane from 32,768 bodies (below, they leave too few
+    // workgroups: 24,000 bodies 239 us, one 216; 40,000 425 and 440; 100,003
+    // 2276 and 2377; four 2407, and nowhere better up to 2^20), unless small
+    // clusters would leave lanes without a second one: those walk their whole
+    // window all the same (65,536 bodies with 2000 clusters of 256: 2.35 ms
+    // with two, 1.60 with one; with three clusters of 30,000: 1.70 and 1.87).
+    const int ipt = ncmax >= 32768 && 2 * wg2 <= wg1 + wg1 / 8 ? 2 : 1;
     const int64_t ib = 256 * ipt;
     hipError_t e = hipSuccess;
     ForceWork w{};
@@ -504,18 +520,25 @@ hipError_t launch_energy_pot(Ctx &c, int *split, const double **phi, hipStream_t
         w.n_blocks = cap;
     }
     // splits of at least a tile, up to ~8192 workgroups (several rounds of the
-    // 1024-2048 resident ones: 100,003 bodies 2.72 ms in 1564 workgroups of
-    // one particle per lane, 2.46 ms in 6000-8000 of four), and the partial
-    // sums within the split buffer; of the upper half of these the number that
+    // 1024-2048 resident ones: 100,003 bodies 2.31 / 2.29 / 2.28 ms with up to
+    // 2048 / 4096 / 8192, 66,000 1072 / 1051 / 1032 us), and the partial sums
+    // within the split buffer; of the upper half of these the number that
     // fills the 256 compute units most evenly (against the largest power of
     // two of at least two tiles: 9000 bodies 88 -> 80 us, 13,000 113 -> 98,
-    // 5000 82 -> 64, 66,000 1158 -> 1139)
-    int64_t most = std::min<int64_t>(8192 / w.n_blocks, (ncmax / 2 + ib) / 256);
+    // 5000 82 -> 64)
+    // Several clusters: if the large ones are most of the work, the splits are
+    // counted for their workgroups alone, as the small ones' few tiles leave
+    // the chip to a few long walks (40,000 bodies with 3000 clusters of 100,
+    // split 1 / 2 / 4 / 8 / 16 / 20: 913 / 841 / 1106 / 688 / 622 / 605 us);
+    // not otherwise (65,536 with 10,000 of 256, which are 38 % of the pairs:
+    // split 1 1826 us, 20 2075).
+    const int64_t wgs = c.nc > 1 && pairs_big >= 0.75 * pairs ? std::max<int64_t>(1, wg_big / ipt) : w.n_blocks;
+    int64_t most = std::min<int64_t>(8192 / wgs, (ncmax / 2 + ib) / 256);
     most = std::max<int64_t>(1, std::min<int64_t>(most, 10 * c.part_cap / n));
     *split = (int)most;
     double best = 0.0;
     for (int64_t k = most; k > most / 2; --k) {
-        const double rounds = (double)(w.n_blocks * k) / 256.0, even = rounds / std::ceil(rounds);
+        const double rounds = (double)(wgs * k) / 256.0, even = rounds / std::ceil(rounds);
         if (even > best + 0.01) {
             best = even;
             *split = (int)k;
@@ -530,8 +553,7 @@ hipError_t launch_energy_pot(Ctx &c, int *split, const double **phi, hipStream_t
         return c.eps == 0.0 ? none : (std::isnormal(e2) ? normal : odd);
     };
     const auto k =
-        ipt == 4 ? pick(energy_kernel<EPS_NONE, 4>, energy_kernel<EPS_NORMAL, 4>, energy_kernel<EPS_ODD, 4>)
-        : ipt == 2
+        ipt == 2
             ? pick(energy_kernel<EPS_NONE, 2>, energy_kernel<EPS_NORMAL, 2>, energy_kernel<EPS_ODD, 2>)
             : pick(energy_kernel<EPS_NONE, 1>, energy_kernel<EPS_NORMAL, 1>, energy_kernel<EPS_ODD, 1>);
     const int rec = prof_begin(c, PH_ENERGY);

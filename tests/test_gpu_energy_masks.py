@@ -28,3 +28,22 @@ def test_energy_tiny_softening(sizes, eps):
     rk, rp, _ = oracle.energy(m, x, v, eps, off)
     assert abs(ek - rk) <= 1e-12 * abs(rk)
     assert abs(ep - rp) <= 1e-12 * abs(rp)
+
+
+@pytest.mark.parametrize("sizes", [[33000] + [100] * 40, [40000, 33000, 129], [3000] + [1, 2, 255, 256, 257] * 5],
+                         ids=["one-large", "two-per-lane", "one-of-3000"])
+@pytest.mark.parametrize("eps", [1e-4, 0.0], ids=["soft", "eps0"])
+def test_energy_mixed_clusters(sizes, eps):
+    """Clusters of mixed sizes: splits counted for the large ones alone, which
+    leave the small ones with more splits than they have tiles."""
+    from paper_1207_2367_amd import System
+    parts = [ics.plummer(max(k, 2), 810 + k) for k in sizes]
+    m, x, v = (np.concatenate([p[q][:k] for p, k in zip(parts, sizes)]) for q in range(3))
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    log_case(test="energy_mixed_clusters", sizes=sizes[:3], eps=eps)
+    s = System(m, x, v, eps, offsets=list(off), skip_startup=True)
+    ek, ep, _ = s.energy()
+    s.close()
+    rk, rp, _ = oracle.energy(m, x, v, eps, off)
+    assert abs(ek - rk) <= 1e-12 * abs(rk)
+    assert abs(ep - rp) <= 1e-12 * abs(rp)

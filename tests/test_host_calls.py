@@ -7,9 +7,13 @@ running them, in a process of its own.
   that memory, so it writes partial sums, also for a single split, and the
   split sums write the outputs when it is done.  Calls without overlap keep
   the single launch, calls without the potential pack their sources first.
+* ``nbody_energy`` with clusters of mixed sizes: the launch shape of the largest
+  must not leave the small ones' lanes without particles, nor the large ones
+  in a few long workgroups.
 """
 import json
 import os
+import re
 import subprocess
 import sys
 
@@ -97,3 +101,62 @@ def test_noalloc_outputs_on_inputs(host):
             assert staged, what
         assert len(names) == 1 + staged and all("reduce_split" in q for q in names[1:]), what
     assert single >= 10   # sizes that the rule evaluates in one split are among them
+
+
+CONTEXT = """
+class Config(C.Structure):
+    _fields_ = [("eta", C.c_double), ("eta_init", C.c_double), ("dt_min", C.c_double), ("dt_max", C.c_double),
+                ("precision", C.c_int32), ("n_clusters", C.c_int32), ("cluster_offsets", C.POINTER(i64)),
+                ("stream", vp), ("validate", C.c_int32), ("skip_startup", C.c_int32)]
+lib.nbody_workspace_bytes.restype = C.c_size_t
+lib.nbody_workspace_bytes.argtypes = [i64, vp]
+lib.nbody_init.argtypes = [vp, i64, vp, vp, vp, C.c_double, vp, vp, C.c_size_t]
+lib.nbody_free.argtypes = [vp]
+lib.nbody_free.restype = None
+def context(sizes):
+    cfg = Config()
+    lib.nbody_default_config(C.byref(cfg))
+    cfg.skip_startup = 1
+    off = [0]
+    for k in sizes:
+        off.append(off[-1] + k)
+    n = off[-1]
+    cfg.cluster_offsets = (i64 * len(off))(*off)
+    cfg.n_clusters = len(sizes)
+    size = lib.nbody_workspace_bytes(n, C.byref(cfg))
+    ws = C.create_string_buffer(size + 256)
+    base = (C.addressof(ws) + 255) // 256 * 256
+    rows = [(C.c_double * (n * k))() for k in (1, 3, 3)]
+    ctx = vp()
+    rc = lib.nbody_init(C.byref(ctx), n, *rows, 1e-4, C.byref(cfg), base, size)
+    assert rc == 0, rc
+    log()
+    return ctx, ws
+"""
+
+ENERGY = CONTEXT + """
+lib.nbody_energy.argtypes = [vp, vp, vp, vp]
+out = []
+for sizes in ([32767], [65536], [100003], [40000] + [100] * 900, [65536] + [256] * 300, [40000, 40000],
+              [65536, 30000, 30000, 30000]):
+    ctx, ws = context(sizes)
+    assert lib.nbody_energy(ctx, None, None, None) == 0
+    out.append((sizes, [q for q in log() if "energy_kernel" in q[0]]))
+    lib.nbody_free(ctx)
+print(json.dumps(out))
+"""
+
+
+def test_energy_shape_of_mixed_clusters(host):
+    for sizes, launches in host(ENERGY):
+        (name, gx, gy, _), = launches
+        per_lane = int(re.search(r"energy_kernelIL[ib]\dELi(\d)E", name).group(1))
+        what = (sizes[:2], len(sizes), gx, gy, per_lane)
+        # particle slots of the workgroups, at most an eighth above one
+        # particle per lane (and one idle workgroup per cluster in the grid)
+        slots = sum(-(-k // (256 * per_lane)) * 256 * per_lane for k in sizes)
+        assert slots <= 1.125 * sum(-(-k // 256) * 256 for k in sizes), what
+        # the largest cluster's windows spread over the chip
+        assert max(sizes) // (256 * per_lane) * gy >= 2048, what
+        if min(sizes) >= 40000:
+            assert per_lane == 2, what
