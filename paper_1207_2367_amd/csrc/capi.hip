@@ -146,8 +146,11 @@ hipError_t scratch_address(int dev, unsigned char **out)
 // A context's words in pinned, mapped, coherent host memory: the GPU-written
 // totals (16 words), readback words (64), sums (64) and the error word.
 // Allocating and freeing such memory takes longer than starting a system of a
-// few thousand bodies, so up to HOST_BLOCKS blocks of closed contexts are kept
-// for the next ones (per device, any thread; more are freed at once).
+// few thousand bodies (init and free of 1000: 250 -> 110 us with the rest of
+// the set-up), so up to HOST_BLOCKS blocks of closed contexts are kept for the
+// next ones (per device, any thread; more are freed at once).  A block whose
+// context could not wait for its work (its stream destroyed first, a device
+// error) is freed and not kept, as a kernel may still write it.
 constexpr int64_t HOST_BLOCK_BYTES = (16 + 64 + 64 + 8) * 8;
 constexpr int HOST_BLOCKS = 8;
 struct HostBlock {
@@ -158,30 +161,39 @@ std::mutex g_host_mu;
 HostBlock g_host_blocks[HOST_BLOCKS];
 int g_host_count = 0;
 
-int64_t *host_block_take(int dev)
+// (*d: the block's device address.  A kept block that the runtime no longer
+// knows went with a reset of the device and is forgotten.)
+int64_t *host_block_take(int dev, int64_t **d)
 {
-    {
-        std::lock_guard<std::mutex> lock(g_host_mu);
-        for (int k = 0; k < g_host_count; ++k)
-            if (g_host_blocks[k].dev == dev) {
-                int64_t *p = g_host_blocks[k].p;
-                g_host_blocks[k] = g_host_blocks[--g_host_count];
-                return p;
-            }
+    std::lock_guard<std::mutex> lock(g_host_mu);
+    for (int k = 0; k < g_host_count;) {
+        if (g_host_blocks[k].dev != dev) {
+            ++k;
+            continue;
+        }
+        int64_t *p = g_host_blocks[k].p;
+        g_host_blocks[k] = g_host_blocks[--g_host_count];
+        if (hipHostGetDevicePointer((void **)d, p, 0) == hipSuccess)
+            return p;
+        (void)hipGetLastError();
     }
     void *p = nullptr;
     if (hipHostMalloc(&p, HOST_BLOCK_BYTES, hipHostMallocMapped | hipHostMallocCoherent) !=
         hipSuccess)
         return nullptr;
+    if (hipHostGetDevicePointer((void **)d, p, 0) != hipSuccess) {
+        (void)hipHostFree(p);
+        return nullptr;
+    }
     return static_cast<int64_t *>(p);
 }
 
-// (no work that writes the block may be in flight)
-void host_block_give(int64_t *p, int dev)
+// idle: no work that writes the block is in flight
+void host_block_give(int64_t *p, int dev, bool idle)
 {
     if (!p)
         return;
-    {
+    if (idle) {
         std::lock_guard<std::mutex> lock(g_host_mu);
         if (g_host_count < HOST_BLOCKS) {
             g_host_blocks[g_host_count++] = HostBlock{p, dev};
@@ -964,15 +976,17 @@ int nbody_init(nbody_ctx **out, int64_t n, const double *d_mass, const double *d
     c.cfg.cluster_offsets = nullptr;
     c.stream = (hipStream_t)cfg->stream;
     auto bail = [&](int rc) {
-        host_block_give(c.h_tot, c.device);
+        // (the inputs and host tables may still be in use by queued work)
+        const bool idle = !c.h_tot || hipStreamSynchronize(c.stream) == hipSuccess;
+        host_block_give(c.h_tot, c.device, idle);
         delete h;
         return rc;
     };
     if (hipGetDevice(&c.device) != hipSuccess)
         return bail(NBODY_EDEVICE);
     ws_layout(n, nc, cfg->precision, &c, static_cast<char *>(d_workspace));
-    c.h_tot = host_block_take(c.device);
-    if (!c.h_tot || hipHostGetDevicePointer((void **)&c.d_tot, c.h_tot, 0) != hipSuccess)
+    c.h_tot = host_block_take(c.device, &c.d_tot);
+    if (!c.h_tot)
         return bail(NBODY_EDEVICE);
     std::memset(c.h_tot, 0, HOST_BLOCK_BYTES);
     c.h_info = c.h_tot + 16;
@@ -1025,10 +1039,8 @@ int nbody_init(nbody_ctx **out, int64_t n, const double *d_mass, const double *d
     // The host tables above are in use until a wait.
     if (rc == NBODY_OK && (n > 32768 || nc > 1))
         rc = take_err(c);
-    if (rc != NBODY_OK) {
-        (void)hipStreamSynchronize(s);
+    if (rc != NBODY_OK)
         return bail(rc);
-    }
     // start-up evaluation, FP64 from the stored state: pass 1 gives a and da
     // (the sources' zero a and da do not enter them); pass 2 gives d2a and
     // the crackle with the pass-1 values as the sources' a and da.  Then the
@@ -1042,10 +1054,8 @@ int nbody_init(nbody_ctx **out, int64_t n, const double *d_mass, const double *d
     }
     if (rc == NBODY_OK)
         rc = take_err(c);
-    if (rc != NBODY_OK) {
-        (void)hipStreamSynchronize(s);
+    if (rc != NBODY_OK)
         return bail(rc);
-    }
     *out = h;
     return NBODY_OK;
 }
@@ -1055,11 +1065,11 @@ void nbody_free(nbody_ctx *ctx)
     if (!ctx)
         return;
     // kernels still queued on the stream may write the mapped host words
-    (void)hipStreamSynchronize(ctx->c.stream);
+    const bool idle = hipStreamSynchronize(ctx->c.stream) == hipSuccess;
     (void)prof_collect(ctx->c);
     for (hipEvent_t e : ctx->c.prof_pool)
         (void)hipEventDestroy(e);
-    host_block_give(ctx->c.h_tot, ctx->c.device);
+    host_block_give(ctx->c.h_tot, ctx->c.device, idle);
     delete ctx;
 }
 

@@ -10,6 +10,8 @@ running them, in a process of its own.
 * ``nbody_energy`` with clusters of mixed sizes: the launch shape of the largest
   must not leave the small ones' lanes without particles, nor the large ones
   in a few long workgroups.
+* a context's pinned words: kept for the next context only if the wait for the
+  context's own work succeeded, and only while the runtime knows them.
 """
 import json
 import os
@@ -113,7 +115,7 @@ lib.nbody_workspace_bytes.argtypes = [i64, vp]
 lib.nbody_init.argtypes = [vp, i64, vp, vp, vp, C.c_double, vp, vp, C.c_size_t]
 lib.nbody_free.argtypes = [vp]
 lib.nbody_free.restype = None
-def context(sizes):
+def context(sizes, want=0):
     cfg = Config()
     lib.nbody_default_config(C.byref(cfg))
     cfg.skip_startup = 1
@@ -129,7 +131,7 @@ def context(sizes):
     rows = [(C.c_double * (n * k))() for k in (1, 3, 3)]
     ctx = vp()
     rc = lib.nbody_init(C.byref(ctx), n, *rows, 1e-4, C.byref(cfg), base, size)
-    assert rc == 0, rc
+    assert rc == want, rc
     log()
     return ctx, ws
 """
@@ -160,3 +162,40 @@ def test_energy_shape_of_mixed_clusters(host):
         assert max(sizes) // (256 * per_lane) * gy >= 2048, what
         if min(sizes) >= 40000:
             assert per_lane == 2, what
+
+
+BLOCKS = CONTEXT + """
+out = []
+def state(what):
+    out.append((what, var("stub_mallocs").value, var("stub_frees").value))
+EDEVICE, DEAD = -2, 709
+a, ws = context([64])
+lib.nbody_free(a)
+b, ws = context([64])
+state("kept")
+var("stub_sync_rc").value = DEAD             # the stream is gone: no wait is possible
+lib.nbody_free(b)
+var("stub_sync_rc").value = 0
+c, ws = context([64])
+state("not kept after a failed wait")
+var("stub_sync_rc").value = DEAD
+context([64], EDEVICE)
+var("stub_sync_rc").value = 0
+state("freed by a failed init")
+lib.nbody_free(c)
+C.c_void_p.in_dll(stub, "stub_block").value = None   # a device reset: old blocks are unknown
+var("stub_mapped_rc").value = 1
+d, ws = context([64])
+state("forgotten after a reset")
+e, ws = context([64, 64])
+lib.nbody_free(d)
+lib.nbody_free(e)
+state("two at once")
+print(json.dumps(out))
+"""
+
+
+def test_pinned_words_of_closed_contexts(host):
+    assert host(BLOCKS) == [["kept", 1, 0], ["not kept after a failed wait", 2, 1],
+                            ["freed by a failed init", 3, 2], ["forgotten after a reset", 4, 2],
+                            ["two at once", 5, 2]]
