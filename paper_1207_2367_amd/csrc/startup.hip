@@ -4,23 +4,23 @@
 //
 // Bound: FP64 vector issue (a wave's FP64 instruction takes ~4.4 cycles at a
 // clock of ~2.13 GHz under this load, measured), so the count of operations
-// per pair is what matters.  Each pass forms only what it returns, and every
-// pair term is a sum of a weight times a plain difference, so that the
-// constant factors are applied once per particle instead of once per pair:
-// with d, v, a, j the differences of position, velocity, acceleration and
-// jerk, rho = 1 / r^2, w = m / r^3, alpha = (d.v) rho, q = (v.v + d.a) rho,
-// t = (3 v.a + d.j) rho,
-//   a    = sum w d
-//   da   = sum w v - 3 sum w alpha d
-//   d2a  = sum w a - 6 sum w alpha v + 3 sum w kappa d
-//   d3a  = sum w j - 9 sum w alpha a + 9 sum w kappa v - 3 sum w lambda d
-// kappa = 5 alpha^2 - q, lambda = t + 5 alpha (7 alpha^2 - 3 q): the terms
-// A, J, S, C of the pairwise differentiation collected by difference.
-// 31 FP64 operations per pair in pass 1 and 72 in pass 2.  Measured at 65,536
-// bodies: pass 1 4.68 ms (918 G pairs/s), pass 2 10.3 ms (415 G pairs/s);
-// one kernel with all four terms written out took 14.3 ms in either pass.
-// With one particle per lane instead of two: 5.02 and 10.8 ms (each source's
-// LDS reads then serve one pair).
+// per pair is what matters.  Each pass forms only what it returns; with d, v,
+// a, j the differences of position, velocity, acceleration and jerk,
+// rho = 1 / r^2, w = m / r^3, alpha = (d.v) rho, beta = (v.v + d.a) rho +
+// alpha^2, gamma = (3 v.a + d.j) rho + alpha (3 beta - 4 alpha^2),
+//   p = v - 3 alpha d                           a  = sum w d, da = sum w p
+//   s = a - 6 alpha p - 3 beta d                d2a = sum w s
+//   c = j - 9 alpha s - 9 beta p - 3 gamma d    d3a = sum w c
+// Every term is completed within its pair, where its parts largely cancel.
+// (The parts summed apart over all pairs, with the factors 3, 6, 9 applied to
+// the sums, take 72 operations instead of 76 in pass 2, 10.3 instead of 10.6
+// ms at 65,536 bodies, but the rms error of the jerk at 4096 bodies over 30
+// spheres was 6.1e-16 with them and one chain of split sums, and is 5.2e-16.)
+// 31 FP64 operations per pair in pass 1 and 76 in pass 2.  Measured at 65,536
+// bodies: pass 1 4.64 ms (926 G pairs/s), pass 2 10.6 ms (405 G pairs/s);
+// one kernel with all four terms took 14.3 ms in either pass.
+// Two particles per lane, so that each source's LDS reads serve two pairs (with
+// the parts summed apart: 4.68 and 10.3 ms, with one per lane 5.02 and 10.8).
 #include "force_body.h"
 
 namespace nb {
@@ -51,7 +51,6 @@ __global__ __launch_bounds__(SU_NT) void startup_kernel(State st, int64_t n, For
 {
     constexpr int GI = SU_NT / LPI;        // lane groups per workgroup
     constexpr int IB = GI * IPT;           // particles per workgroup
-    constexpr int NA = PASS == 1 ? 9 : 21; // running sums
     __shared__ SuSrc<PASS> tl[SU_NT];
     const int64_t g = blockIdx.x;
     const int b = blockIdx.y;
@@ -77,7 +76,7 @@ __global__ __launch_bounds__(SU_NT) void startup_kernel(State st, int64_t n, For
     int64_t i[IPT];
     double xi[IPT], yi[IPT], zi[IPT], vxi[IPT], vyi[IPT], vzi[IPT];
     double axi[IPT], ayi[IPT], azi[IPT], jxi[IPT], jyi[IPT], jzi[IPT];
-    double S[IPT][NA];
+    double S[IPT][6];
 #pragma unroll
     for (int u = 0; u < IPT; ++u) {
         i[u] = o0 + (g - gfirst) * IB + il + u * GI;
@@ -89,7 +88,7 @@ __global__ __launch_bounds__(SU_NT) void startup_kernel(State st, int64_t n, For
             jxi[u] = JX[k]; jyi[u] = JY[k]; jzi[u] = JZ[k];
         }
 #pragma unroll
-        for (int q = 0; q < NA; ++q)
+        for (int q = 0; q < 6; ++q)
             S[u][q] = 0.0;
     }
 
@@ -126,29 +125,29 @@ __global__ __launch_bounds__(SU_NT) void startup_kernel(State st, int64_t n, For
                 const double rho = rinv * rinv, wt = s.m * rinv * rho;
                 const double vx = s.vx - vxi[u], vy = s.vy - vyi[u], vz = s.vz - vzi[u];
                 const double al = fma(dx, vx, fma(dy, vy, dz * vz)) * rho;
-                const double wa = wt * al;
+                const double a3 = -3.0 * al;
+                const double px = fma(a3, dx, vx), py = fma(a3, dy, vy), pz = fma(a3, dz, vz);
                 double *Q = S[u];
                 if constexpr (PASS == 1) {
                     Q[0] = fma(wt, dx, Q[0]); Q[1] = fma(wt, dy, Q[1]); Q[2] = fma(wt, dz, Q[2]);
-                    Q[3] = fma(wt, vx, Q[3]); Q[4] = fma(wt, vy, Q[4]); Q[5] = fma(wt, vz, Q[5]);
-                    Q[6] = fma(wa, dx, Q[6]); Q[7] = fma(wa, dy, Q[7]); Q[8] = fma(wa, dz, Q[8]);
+                    Q[3] = fma(wt, px, Q[3]); Q[4] = fma(wt, py, Q[4]); Q[5] = fma(wt, pz, Q[5]);
                 } else {
                     const double ax = s.ax - axi[u], ay = s.ay - ayi[u], az = s.az - azi[u];
                     const double jx = s.jx - jxi[u], jy = s.jy - jyi[u], jz = s.jz - jzi[u];
-                    const double q = rho * fma(vx, vx, fma(vy, vy, fma(vz, vz,
-                                           fma(dx, ax, fma(dy, ay, dz * az)))));
+                    const double vv = fma(vx, vx, fma(vy, vy, fma(vz, vz,
+                                      fma(dx, ax, fma(dy, ay, dz * az)))));
                     const double va = fma(vx, ax, fma(vy, ay, vz * az));
                     const double tt = fma(3.0, va, fma(dx, jx, fma(dy, jy, dz * jz)));
-                    const double a5 = 5.0 * al;
-                    const double wk = wt * fma(a5, al, -q);
-                    const double wl = wt * fma(a5, fma(7.0 * al, al, -3.0 * q), tt * rho);
-                    Q[0] = fma(wt, ax, Q[0]); Q[1] = fma(wt, ay, Q[1]); Q[2] = fma(wt, az, Q[2]);
-                    Q[3] = fma(wa, vx, Q[3]); Q[4] = fma(wa, vy, Q[4]); Q[5] = fma(wa, vz, Q[5]);
-                    Q[6] = fma(wk, dx, Q[6]); Q[7] = fma(wk, dy, Q[7]); Q[8] = fma(wk, dz, Q[8]);
-                    Q[9] = fma(wt, jx, Q[9]); Q[10] = fma(wt, jy, Q[10]); Q[11] = fma(wt, jz, Q[11]);
-                    Q[12] = fma(wa, ax, Q[12]); Q[13] = fma(wa, ay, Q[13]); Q[14] = fma(wa, az, Q[14]);
-                    Q[15] = fma(wk, vx, Q[15]); Q[16] = fma(wk, vy, Q[16]); Q[17] = fma(wk, vz, Q[17]);
-                    Q[18] = fma(wl, dx, Q[18]); Q[19] = fma(wl, dy, Q[19]); Q[20] = fma(wl, dz, Q[20]);
+                    const double aa = al * al;
+                    const double b3 = -3.0 * fma(vv, rho, aa);
+                    const double g3 = fma(a3, fma(-4.0, aa, -b3), -3.0 * (tt * rho));
+                    const double a6 = a3 + a3, a9 = 3.0 * a3, b9 = 3.0 * b3;
+                    const double sx = fma(a6, px, fma(b3, dx, ax)), sy = fma(a6, py, fma(b3, dy, ay)),
+                                 sz = fma(a6, pz, fma(b3, dz, az));
+                    Q[0] = fma(wt, sx, Q[0]); Q[1] = fma(wt, sy, Q[1]); Q[2] = fma(wt, sz, Q[2]);
+                    Q[3] = fma(wt, fma(a9, sx, fma(b9, px, fma(g3, dx, jx))), Q[3]);
+                    Q[4] = fma(wt, fma(a9, sy, fma(b9, py, fma(g3, dy, jy))), Q[4]);
+                    Q[5] = fma(wt, fma(a9, sz, fma(b9, pz, fma(g3, dz, jz))), Q[5]);
                 }
             }
         }
@@ -156,18 +155,7 @@ __global__ __launch_bounds__(SU_NT) void startup_kernel(State st, int64_t n, For
 
 #pragma unroll
     for (int u = 0; u < IPT; ++u) {
-        double R[6];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            if constexpr (PASS == 1) {
-                R[d] = S[u][d];
-                R[3 + d] = fma(-3.0, S[u][6 + d], S[u][3 + d]);
-            } else {
-                R[d] = fma(3.0, S[u][6 + d], fma(-6.0, S[u][3 + d], S[u][d]));
-                R[3 + d] = fma(-3.0, S[u][18 + d], fma(9.0, S[u][15 + d],
-                               fma(-9.0, S[u][12 + d], S[u][9 + d])));
-            }
-        }
+        double *R = S[u];
         // lanes of a particle, in a fixed order (xor butterfly)
 #pragma unroll
         for (int msk = 1; msk < LPI; msk <<= 1)
@@ -186,8 +174,10 @@ __global__ __launch_bounds__(SU_NT) void startup_kernel(State st, int64_t n, For
     }
 }
 
-// sums over the splits in use, in the order b = 0, 1, ...; one lane per
-// (component, particle)
+// sums over the splits in use, in a fixed order: every fourth split, then the
+// four sums (one chain over 16 splits gave the acceleration at 4096 bodies an
+// rms error of 1.56e-16, this 1.26e-16, 64 lanes' sums in a tree 1.27e-16; the
+// same time, 3.8 us); one lane per (component, particle)
 __global__ __launch_bounds__(256) void startup_reduce(const double *part, int32_t B, int64_t n,
                                                       const int64_t *off,
                                                       const int32_t *cluster_of, double *out0,
@@ -200,11 +190,13 @@ __global__ __launch_bounds__(256) void startup_reduce(const double *part, int32_
     const int64_t i = t - (int64_t)q * n;
     const int c = cluster_of ? cluster_of[i] : 0;
     const int64_t used = splits_used(cluster_of ? off[c + 1] - off[c] : n, B, SU_NT);
-    double r = 0.0;
-#pragma unroll 8
-    for (int64_t b = 0; b < used; ++b)
-        r += part[(b * 6 + q) * n + i];
-    (q < 3 ? out0 : out1)[(q % 3) * n + i] = r;
+    double r[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 2
+    for (int64_t b = 0; b < used; b += 4)
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            r[k] += b + k < used ? part[((b + k) * 6 + q) * n + i] : 0.0;
+    (q < 3 ? out0 : out1)[(q % 3) * n + i] = (r[0] + r[1]) + (r[2] + r[3]);
 }
 
 using KStart = void (*)(State, int64_t, ForceWork, double *, double *, double *, double);
