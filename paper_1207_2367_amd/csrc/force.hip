@@ -114,12 +114,23 @@ __device__ __forceinline__ void xcd_order(int64_t &g, int &b)
 // active particles per lane group.
 // Waves per SIMD that the registers are allotted for: as many as a shape
 // holds with hardly a spill outside its pair loop (left alone, the compiler
-// spends registers on deeper unrolling and drops to two waves).
+// spends registers on deeper unrolling and drops to two waves).  FP32-pair with
+// one particle per lane group, 65,536 sources: 1000 active 109.1 us with three
+// and 103.1 with four.
 constexpr int force_waves(int prec, int lpi, int ipt)
 {
     if (ipt == 2)
         return prec == PREC_PAIR32 && lpi == 1 ? 2 : 3;
-    return prec == PREC_PAIR32 ? 3 : 4;
+    return 4;
+}
+
+// Whether a tile's sources are fetched one tile ahead (force_block).  Not by
+// one lane per particle with FP32 pairs: those tiles are 256 short pairs per
+// lane, four waves hide the fetch, and its registers are missed in the pair
+// loop (65,536 active, 524,288 sources: 37.3 ms with, 36.9 without).
+constexpr bool force_ahead(int prec, int lpi)
+{
+    return !(prec == PREC_PAIR32 && lpi == 1);
 }
 
 // Sources of an evaluation: with the potential (nbody_force, at the stored
@@ -136,7 +147,7 @@ __global__ __launch_bounds__(NW * 64, force_waves(PREC, LPI, IPT)) void force_ke
     int64_t g;
     int b;
     xcd_order(g, b);
-    force_block<PREC, LPI, NW, EPS0, PHI, IPT>(J, w, out, part, n_act_total, eps2, g, b);
+    force_block<PREC, LPI, NW, EPS0, PHI, IPT, force_ahead(PREC, LPI)>(J, w, out, part, n_act_total, eps2, g, b);
 }
 
 // Potential energy of the stored state (paper Sect. 5.1): every unordered
