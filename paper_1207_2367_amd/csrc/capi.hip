@@ -447,12 +447,27 @@ bool has_tuned(const Ctx &c, int64_t n_act)
     return b < (int)c.tuned.size() && c.tuned[b].lpi > 0;
 }
 
-int64_t max_cluster(const Ctx &c)
+int64_t max_cluster(const Ctx &c) { return c.sizes.largest; }
+
+ClusterSizes cluster_sizes(const std::vector<int64_t> &off)
 {
-    int64_t m = 0;
-    for (size_t k = 0; k + 1 < c.off.size(); ++k)
-        m = std::max(m, c.off[k + 1] - c.off[k]);
-    return m;
+    ClusterSizes z;
+    for (size_t k = 0; k + 1 < off.size(); ++k)
+        z.largest = std::max(z.largest, off[k + 1] - off[k]);
+    double pairs = 0.0, big = 0.0;
+    for (size_t k = 0; k + 1 < off.size(); ++k) {
+        const int64_t nk = off[k + 1] - off[k], wg = (nk + 255) / 256;
+        const double p = (double)wg * (double)(nk / 2 + 256);   // a workgroup's window
+        z.wg1 += wg;
+        z.wg2 += (nk + 511) / 512;
+        pairs += p;
+        if (2 * nk >= z.largest) {
+            big += p;
+            z.wg_big += wg;
+        }
+    }
+    z.big_share = big / pairs;
+    return z;
 }
 
 // force of the active slots described by c.d_seg (and idx) into out
@@ -998,6 +1013,7 @@ int nbody_init(nbody_ctx **out, int64_t n, const double *d_mass, const double *d
         std::copy(cfg->cluster_offsets, cfg->cluster_offsets + nc + 1, c.off.begin());
     else
         c.off[1] = n;
+    c.sizes = cluster_sizes(c.off);
     c.n_chunks = count_chunks(c.off);
     hipStream_t s = c.stream;
     int rc = NBODY_OK;

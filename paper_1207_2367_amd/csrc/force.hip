@@ -490,29 +490,15 @@ hipError_t launch_force(Ctx &c, const ForceWork &w, const Launch &L,
 hipError_t launch_energy_pot(Ctx &c, int *split, const double **phi, hipStream_t s)
 {
     const int64_t n = c.n;
-    int64_t ncmax = 0, wg1 = 0, wg2 = 0;   // workgroups with one and two particles per lane
-    double pairs = 0.0, pairs_big = 0.0;   // pair slots, and those of clusters from half the
-    int64_t wg_big = 0;                    // largest, with one particle per lane
-    for (size_t k = 0; k + 1 < c.off.size(); ++k)
-        ncmax = std::max(ncmax, c.off[k + 1] - c.off[k]);
-    for (size_t k = 0; k + 1 < c.off.size(); ++k) {
-        const int64_t nk = c.off[k + 1] - c.off[k], wg = (nk + 255) / 256;
-        const double p = (double)wg * (double)(nk / 2 + 256);
-        wg1 += wg;
-        wg2 += (nk + 511) / 512;
-        pairs += p;
-        if (2 * nk >= ncmax) {
-            pairs_big += p;
-            wg_big += wg;
-        }
-    }
+    const ClusterSizes &z = c.sizes;
+    const int64_t ncmax = z.largest;
     // Two particles per lane from 32,768 bodies (below, they leave too few
     // workgroups: 24,000 bodies 239 us, one 216; 40,000 425 and 440; 100,003
     // 2276 and 2377; four 2407, and nowhere better up to 2^20), unless small
     // clusters would leave lanes without a second one: those walk their whole
     // window all the same (65,536 bodies with 2000 clusters of 256: 2.35 ms
     // with two, 1.60 with one; with three clusters of 30,000: 1.70 and 1.87).
-    const int ipt = ncmax >= 32768 && 2 * wg2 <= wg1 + wg1 / 8 ? 2 : 1;
+    const int ipt = ncmax >= 32768 && 2 * z.wg2 <= z.wg1 + z.wg1 / 8 ? 2 : 1;
     const int64_t ib = 256 * ipt;
     hipError_t e = hipSuccess;
     ForceWork w{};
@@ -543,7 +529,7 @@ hipError_t launch_energy_pot(Ctx &c, int *split, const double **phi, hipStream_t
     // split 1 / 2 / 4 / 8 / 16 / 20: 913 / 841 / 1106 / 688 / 622 / 605 us);
     // not otherwise (65,536 with 10,000 of 256, which are 38 % of the pairs:
     // split 1 1826 us, 20 2075).
-    const int64_t wgs = c.nc > 1 && pairs_big >= 0.75 * pairs ? std::max<int64_t>(1, wg_big / ipt) : w.n_blocks;
+    const int64_t wgs = c.nc > 1 && z.big_share >= 0.75 ? std::max<int64_t>(1, z.wg_big / ipt) : w.n_blocks;
     int64_t most = std::min<int64_t>(8192 / wgs, (ncmax / 2 + ib) / 256);
     most = std::max<int64_t>(1, std::min<int64_t>(most, 10 * c.part_cap / n));
     *split = (int)most;

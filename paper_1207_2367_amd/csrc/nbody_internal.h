@@ -261,6 +261,16 @@ struct ProfRec {
     double pairs;
 };
 
+// What a context's cluster sizes say about its launch shapes, worked out once
+// by nbody_init (a pass over 10,000 clusters in each nbody_energy took 15 us of
+// 890): the largest, the energy pass' workgroups with one and two particles
+// per lane, and those with one of the clusters from half the largest, with the
+// share of the pairs that they hold.
+struct ClusterSizes {
+    int64_t largest = 0, wg1 = 0, wg2 = 0, wg_big = 0;
+    double big_share = 0.0;
+};
+
 struct Ctx {
     int64_t n = 0;
     int32_t nc = 1;
@@ -276,6 +286,7 @@ struct Ctx {
     // [nc + 1] device copies of the cluster offsets, host copy too
     int64_t *d_off = nullptr;
     std::vector<int64_t> off;
+    ClusterSizes sizes;
     int32_t *d_cluster_of = nullptr;  // [n] cluster of each particle (nc > 1)
     // split-source partials: [B][10][n_act]
     double *part = nullptr;
