@@ -531,7 +531,7 @@ int run_force(Ctx &c, const int32_t *idx, int64_t n_act, int64_t n_act_typ, cons
 // the two start-up passes over every particle (see nbody_init)
 int run_force_init(Ctx &c)
 {
-    const StartupShape sh = startup_shape(c.n, c.nc, max_cluster(c), c.part_cap);
+    const StartupShape sh = startup_shape(c);
     ForceWork w{};
     w.off = c.d_off;
     w.split = sh.split;

@@ -154,7 +154,7 @@ struct StartupShape {
     int64_t ib = 1, n_blocks = 1;
     int32_t split = 1;
 };
-StartupShape startup_shape(int64_t n, int32_t nc, int64_t n_src, int64_t part_cap);
+StartupShape startup_shape(const Ctx &c);
 // pass 1: acceleration and jerk of every particle from the stored positions
 // and velocities, into the stored state; pass 2: snap and crackle from those.
 // w.split = sh.split and, with several clusters, the i-block table for sh.ib.

@@ -215,26 +215,39 @@ KStart pick_startup(int lpi)
 }  // namespace
 
 // Launch shape: the fewest lanes per particle (1 with two particles per
-// lane, 4, 16, 64) with which i-blocks times tiles of sources still give the
-// chip's 256 compute units four workgroups each, then splits of whole tiles
-// up to eight workgroups per unit, while the 6 B n partial sums fit the
-// split buffer.  Fewer lanes mean fewer LDS reads and no lane sums; more
-// than eight workgroups per unit only add partial sums.
-StartupShape startup_shape(int64_t n, int32_t nc, int64_t n_src, int64_t part_cap)
+// lane, 4, 16, 64) with which the units of a workgroup and a tile of its
+// cluster's sources still give the chip's 256 compute units four each, then
+// splits of whole tiles up to eight workgroups per unit, while the 6 B n
+// partial sums fit the split buffer.  Fewer lanes mean fewer LDS reads and no
+// lane sums; more than eight workgroups per unit only add partial sums.  With
+// clusters, one lane per particle only if at most an eighth of the pair slots
+// is empty for want of a second particle, and the workgroups of all are counted
+// as if their units were of the largest cluster's length, so that its walks
+// are short against a compute unit's share of the whole.
+StartupShape startup_shape(const Ctx &c)
 {
-    const int64_t want = 1024, most = 2048;
-    const int64_t tiles = (n_src + SU_NT - 1) / SU_NT;
+    const int64_t want = 1024, most = 2048, n = c.n;
+    const int64_t tiles = (c.sizes.largest + SU_NT - 1) / SU_NT;
     StartupShape s;
+    int64_t units = 0;
     for (int lpi : {1, 4, 16, 64}) {
         s.lpi = lpi;
         s.ib = SU_NT / lpi * (lpi == 1 ? 2 : 1);
-        s.n_blocks = nc == 1 ? (n + s.ib - 1) / s.ib : n / s.ib + nc + 1;
-        if (s.n_blocks * tiles >= want)
+        s.n_blocks = c.nc == 1 ? (n + s.ib - 1) / s.ib : n / s.ib + c.nc + 1;
+        int64_t slots = 0, slots1 = 0;
+        units = 0;
+        for (size_t k = 0; k + 1 < c.off.size(); ++k) {
+            const int64_t nk = c.off[k + 1] - c.off[k], t = (nk + SU_NT - 1) / SU_NT;
+            units += (nk + s.ib - 1) / s.ib * t;
+            slots += (nk + s.ib - 1) / s.ib * s.ib * t;
+            slots1 += t * SU_NT * t;
+        }
+        if (units >= want && (c.nc == 1 || lpi > 1 || slots <= slots1 + slots1 / 8))
             break;
     }
     s.split = 1;
-    while (s.n_blocks * s.split * 2 <= most && s.split * 2 <= tiles &&
-           (int64_t)s.split * 2 * 6 * n <= 10 * part_cap)
+    while (units * s.split * 2 <= most * tiles && s.split * 2 <= tiles &&
+           (int64_t)s.split * 2 * 6 * n <= 10 * c.part_cap)
         s.split *= 2;
     return s;
 }

@@ -7,9 +7,9 @@ running them, in a process of its own.
   that memory, so it writes partial sums, also for a single split, and the
   split sums write the outputs when it is done.  Calls without overlap keep
   the single launch, calls without the potential pack their sources first.
-* ``nbody_energy`` with clusters of mixed sizes: the launch shape of the largest
-  must not leave the small ones' lanes without particles, nor the large ones
-  in a few long workgroups.
+* ``nbody_energy`` and the start-up with clusters of mixed sizes: the launch
+  shape of the largest must not leave the small ones' lanes without particles,
+  nor the large ones in a few long workgroups.
 * a context's pinned words: kept for the next context only if the wait for the
   context's own work succeeded, and only while the runtime knows them.
 """
@@ -115,10 +115,11 @@ lib.nbody_workspace_bytes.argtypes = [i64, vp]
 lib.nbody_init.argtypes = [vp, i64, vp, vp, vp, C.c_double, vp, vp, C.c_size_t]
 lib.nbody_free.argtypes = [vp]
 lib.nbody_free.restype = None
-def context(sizes, want=0):
+def context(sizes, want=0, startup=False):
+    global launches
     cfg = Config()
     lib.nbody_default_config(C.byref(cfg))
-    cfg.skip_startup = 1
+    cfg.skip_startup = not startup
     off = [0]
     for k in sizes:
         off.append(off[-1] + k)
@@ -132,7 +133,7 @@ def context(sizes, want=0):
     ctx = vp()
     rc = lib.nbody_init(C.byref(ctx), n, *rows, 1e-4, C.byref(cfg), base, size)
     assert rc == want, rc
-    log()
+    launches = log()
     return ctx, ws
 """
 
@@ -162,6 +163,35 @@ def test_energy_shape_of_mixed_clusters(host):
         assert max(sizes) // (256 * per_lane) * gy >= 2048, what
         if min(sizes) >= 40000:
             assert per_lane == 2, what
+
+
+STARTUP = CONTEXT + """
+out = []
+for sizes in ([4096], [40000], [4096] + [256] * 500, [16384] + [2048] * 100, [1000] + [33] * 50, [256] * 3000,
+              [2000] + [60] * 300):
+    ctx, ws = context(sizes, startup=True)
+    out.append((sizes, [q for q in launches if "startup_kernel" in q[0]]))
+    lib.nbody_free(ctx)
+print(json.dumps(out))
+"""
+
+
+def test_startup_shape_of_mixed_clusters(host):
+    for sizes, launches in host(STARTUP):
+        assert len(launches) == 2
+        for name, gx, gy, _ in launches:
+            lpi, ipt = (int(q) for q in re.search(r"startup_kernelILi\dELi(\d+)ELi(\d)E", name).groups())
+            ib = 256 // lpi * ipt
+            blocks = [(-(-k // ib), -(-k // 256)) for k in sizes]     # workgroups, tiles each
+            what = (sizes[:2], len(sizes), lpi, ipt, gy)
+            # pair slots that hold no particle: at most an eighth more than with one per lane
+            assert sum(b * ib * t for b, t in blocks) <= 1.125 * sum(256 * t * t for _, t in blocks), what
+            # no walk is longer than half of a compute unit's share of the units,
+            # unless twice the splits' partial sums exceed the split buffer
+            n = sum(sizes)
+            longest = max(t for _, t in blocks) / gy
+            assert (longest <= max(1, sum(b * t for b, t in blocks) / 512) or
+                    12 * gy * n > 10 * max(2 * n, 1 << 20)), what
 
 
 BLOCKS = CONTEXT + """
