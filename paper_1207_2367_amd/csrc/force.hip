@@ -250,7 +250,8 @@ __global__ __launch_bounds__(256) void energy_kernel(const double *X, const doub
 // bound of a small active set is the chain of dependent round trips to L2,
 // which R lanes cut R-fold.  With the evaluation's ForceWork, only the splits
 // that hold sources of the slot's cluster are read (the evaluation's splits
-// are whole units of nt sources).
+// are whole units of nt sources), and a slot whose particle is out of range,
+// which the evaluation skipped, is not written.
 template <int R>
 __global__ __launch_bounds__(256) void reduce_split(const double *part, int32_t B,
                                                     int64_t n_act, ForceOut out, ForceWork w,
@@ -264,13 +265,14 @@ __global__ __launch_bounds__(256) void reduce_split(const double *part, int32_t 
     const int q = (int)(t / n_act);
     const int64_t k = t - (int64_t)q * n_act;
     double r = 0.0;
+    bool valid = in;
     if (in) {
+        const int64_t i = w.idx ? (int64_t)w.idx[k] : k;
+        valid = i >= 0 && i < (w.n_src > 0 ? w.n_src : w.off[w.nc]);
         if (w.n_src > 0) {
             B = (int32_t)splits_used(w.n_src, B, nt);
-        } else if (w.off) {
-            const int64_t i = w.idx ? (int64_t)w.idx[k] : k;
-            // (an index out of range was skipped by the evaluation: any cluster)
-            const int c = cluster_of && i >= 0 && i < w.off[w.nc] ? cluster_of[i] : 0;
+        } else {
+            const int c = cluster_of && valid ? cluster_of[i] : 0;
             B = (int32_t)splits_used(w.off[c + 1] - w.off[c], B, nt);
         }
         const int64_t stride = 10 * n_act;
@@ -298,7 +300,7 @@ __global__ __launch_bounds__(256) void reduce_split(const double *part, int32_t 
         for (int u = 1; u < R; ++u)
             r += ps[u][kl];
     }
-    if (!in || rl != 0)
+    if (!valid || rl != 0)
         return;
     if (q == 9) {
         if (out.pot)
