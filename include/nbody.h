@@ -312,7 +312,7 @@ int nbody_set_step_loop(nbody_ctx *ctx, int64_t max_active);
    call): the next block time is the earliest next multiple of an occupied
    level's step, its particles those of the levels whose step divides it, so
    no sweep over all particles is needed; the active list is then filled in
-   chunk order of completion (the results do not depend on it).  mode 1: a
+   the order in which workgroups finish (the results do not depend on it).  mode 1: a
    sweep of every particle's next time per block step (always used for
    several clusters, by the device-resident loops and by nbody_schedule and
    nbody_block_step).  Both give the same blocks.  Returns NBODY_EINVAL for

@@ -20,9 +20,9 @@ struct nbody_ctx {
     Ctx c;
 };
 
-// Scratch of nbody_force_noalloc: the source records, the one-cluster work
-// tables and the split-source partials of one evaluation, in a fixed device
-// array instead of a caller workspace.  Each device the library runs on
+// Scratch of nbody_force_noalloc: the source records and the split-source
+// partials of one evaluation, in a fixed device array instead of a caller
+// workspace.  Each device the library runs on
 // holds its own copy until the process ends.  Host code never uses the
 // array's name as an address: the device address is looked up once per
 // device (scratch_address below) and only that address is passed on.
@@ -205,9 +205,9 @@ void host_block_give(int64_t *p, int dev, bool idle)
 
 // Scratch layout of nbody_force_noalloc for n sources: the records of the
 // context's precision (used by calls without the potential; the limit on the
-// sizes counts them for every call) and 512 bytes left free; the split
-// partials follow at the returned offset.  With base == nullptr only the size
-// is computed.
+// sizes counts them for every call) and 512 bytes left free, so that the limit
+// stays where callers know it; the split partials follow at the returned
+// offset.  With base == nullptr only the size is computed.
 int64_t noalloc_layout(int64_t n, int32_t prec, Ctx *c, unsigned char *base)
 {
     int64_t o = 0;
@@ -328,7 +328,8 @@ int64_t nb::ws_layout(int64_t n, int32_t nc, int32_t prec, Ctx *c, char *base)
     uint64_t *loop_min = (uint64_t *)take(2 * LOOP_GMAX * 8);
     int32_t *loop_cnt = (int32_t *)take(2 * LOOP_GMAX * 4);
     // ensemble plan: grp_of, first, size [LOOP_GMAX each], cl_off [LOOP_GMAX + 1],
-    // cl [nc]; part_off, part_cap [LOOP_GMAX each]; results
+    // cl [nc]; part_off, part_cap [LOOP_GMAX each] (and as much left free, so
+    // that a workspace's size stays what callers know); results
     int32_t *ens_i32 = nc > 1 ? (int32_t *)take((4 * LOOP_GMAX + 1 + nc) * 4) : nullptr;
     int64_t *ens_i64 = nc > 1 ? (int64_t *)take(4 * LOOP_GMAX * 8) : nullptr;
     unsigned long long *ens_res = nc > 1 ? (unsigned long long *)take(4 * 8) : nullptr;
@@ -585,9 +586,11 @@ int wait_totals(Ctx &c, int64_t seq, int64_t tot[6]) { return wait_words(c, 0, 6
 // workgroups costs N_c^2 / W + L_W, where L_W stands for the latency of its
 // block steps (thousands of steps of a few barriers and memory round trips
 // each, about the same count for every cluster of a King ensemble);
-// measured on the 256-cluster King W0 = 6 ensemble on the MI355X: a
-// one-workgroup cluster of 256 bodies takes as long as 6e5 N^2 units
-// (~775^2), a multi-workgroup group about twice that.  The plan is the
+// measured on the 256-cluster King W0 = 6 ensemble on the MI355X, with barriers
+// that wrote back and invalidated the caches (3.3 us; they take 1.8 without,
+// and the constants were not fitted again): a one-workgroup cluster of 256
+// bodies took as long as 6e5 N^2 units (~775^2), a multi-workgroup group about
+// twice that.  The plan is the
 // smallest makespan M (bisection) for which: a cluster with N_c^2 + L_1 > M
 // gets a group of its own of ceil(N_c^2 / (M - L_W)) workgroups (at most
 // ENS_GROUP_MAX), and the others are packed first-fit-decreasing onto
@@ -686,7 +689,7 @@ int plan_ensemble(Ctx &c, int G)
     if (ng > LOOP_GMAX)
         return 0;
     std::vector<int32_t> i32(4 * LOOP_GMAX + 1 + nc, 0);
-    std::vector<int64_t> i64(4 * LOOP_GMAX, 0);
+    std::vector<int64_t> i64(2 * LOOP_GMAX, 0);
     int32_t *grp_of = i32.data(), *first = grp_of + LOOP_GMAX, *size = first + LOOP_GMAX;
     int32_t *cl_off = size + LOOP_GMAX, *cl = cl_off + LOOP_GMAX + 1;
     int64_t *part_off = i64.data(), *part_cap = part_off + LOOP_GMAX;
@@ -1110,7 +1113,7 @@ int nbody_force(nbody_ctx *ctx, int64_t n_act, const int32_t *d_idx, double *d_a
     // with the potential the kernels read the stored state itself (see
     // SrcOf in force.hip); without it, records packed from it
     if (!d_pot)
-        HIPCHK(c, launch_pack(c, nullptr, 1, nullptr, c.stream));
+        HIPCHK(c, launch_pack(c, c.stream));
     if (c.nc > 1)
         HIPCHK(c, launch_segments(c, d_idx, n_act, c.stream));
     ForceOut out{};
@@ -1410,7 +1413,7 @@ int nbody_autotune(nbody_ctx *ctx, double max_ms)
         }
     hipStream_t s = c.stream;
     // sources = the stored state; outputs to the integrator's scratch
-    HIPCHK(c, launch_pack(c, nullptr, 1, nullptr, s));
+    HIPCHK(c, launch_pack(c, s));
     const bool was_prof = c.prof;
     c.prof = false;
     const Launch pinned = c.pinned;

@@ -78,9 +78,9 @@ __device__ uint32_t block_dt(double crit, double dt_old, double t_new, double t_
 }
 
 // ------------------------------------------------------------- predictor
-// Taylor series of paper Sect. 3 item 1 (Horner form) to the source
-// records.  T is the block time of the particle's cluster, or its own time
-// (h = 0: the records are the stored state) when own_time is set.
+// Taylor series of paper Sect. 3 item 1 (Horner form) to the source records,
+// at the block time of the particle's cluster (pack_one) or h after the
+// particle's own time (pack_h).
 template <bool COH = false>
 __device__ __forceinline__ void pack_h(const State &st, const JRecMixed &jm,
                                        const JRecPair32 &jp, const JRecF64 &jd, int prec,
@@ -90,18 +90,14 @@ __device__ __forceinline__ void pack_one(const State &st, const JRecMixed &jm,
                                          const JRecPair32 &jp, const JRecF64 &jd, int prec,
                                          int64_t n,
                                          const double *Tc, const int32_t *cluster_of,
-                                         int own_time, int64_t i)
+                                         int64_t i)
 {
     if (i >= n)
         return;
-    double h = 0.0;
-    if (!own_time) {
-        const double T = Tc[cluster_of ? cluster_of[i] : 0];
-        if (!(T < DBL_MAX))
-            return;  // cluster has reached the target: not a source this step
-        h = T - st.t[i];
-    }
-    pack_h(st, jm, jp, jd, prec, n, i, h);
+    const double T = Tc[cluster_of ? cluster_of[i] : 0];
+    if (!(T < DBL_MAX))
+        return;  // cluster has reached the target: not a source this step
+    pack_h(st, jm, jp, jd, prec, n, i, T - st.t[i]);
 }
 
 template <bool COH>
@@ -167,11 +163,11 @@ __device__ __forceinline__ void store_pred(const PredIn &q, const JRecMixed &jm,
 }
 
 __global__ __launch_bounds__(TPB) void pack_kernel(State st, JRecMixed jm, JRecPair32 jp, JRecF64 jd,
-                                                   int prec, int64_t n, const double *Tc,
-                                                   const int32_t *cluster_of, int own_time)
+                                                   int prec, int64_t n)
 {
-    pack_one(st, jm, jp, jd, prec, n, Tc, cluster_of, own_time,
-             (int64_t)blockIdx.x * TPB + threadIdx.x);
+    const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
+    if (i < n)
+        pack_h(st, jm, jp, jd, prec, n, i, 0.0);
 }
 
 // A workgroup's TPB particles as [TPB][3] in LDS, and out to dst[n][3] in whole
@@ -530,7 +526,7 @@ __global__ __launch_bounds__(TPB) void scatter_pack_kernel(State st, JRecMixed j
         scatter_chunk(st.t, st.dt, chunk_begin, chunk_cluster, tblock, chunk_pos, act,
                       blockIdx.x);
     else
-        pack_one(st, jm, jp, jd, prec, n, tblock, cluster_of, 0,
+        pack_one(st, jm, jp, jd, prec, n, tblock, cluster_of,
                  ((int64_t)blockIdx.x - n_chunks) * TPB + threadIdx.x);
 }
 
@@ -901,14 +897,6 @@ __device__ __forceinline__ double correct_loaded(const State &st, int64_t n, int
     return t_new + dtn;
 }
 
-__device__ __forceinline__ void correct_one(State st, int64_t n, int64_t i, const double *a1,
-                                            const double *j1, const double *s1,
-                                            double t_target, double eta, double dt_min,
-                                            double dt_max, uint32_t *err)
-{
-    correct_loaded(st, n, i, load_old(st, n, i), a1, j1, s1, t_target, eta, dt_min, dt_max, err);
-}
-
 // a workgroup's changes of the per-level counts (old step -> new step of the
 // particles it corrected), gathered in LDS and added to lvl[] once per level
 struct LevelDelta {
@@ -1076,9 +1064,10 @@ __global__ __launch_bounds__(TPB) void reduce_correct_kernel(
 
 // ------------------------------------------- device-resident block steps
 // Block steps of one system whose active sets stay small, run inside one
-// cooperative launch of G workgroups of TPB lanes (all resident at once),
-// with three grid barriers per step (two for at most SMALL_N particles: see
-// small_loop_kernel):
+// cooperative launch of G workgroups of TPB lanes (all resident at once).
+// Systems of at most SMALL_N particles take small_loop_kernel; this general
+// form, with three grid barriers per step, serves larger ones whose caller set
+// a limit (the automatic mode leaves those to the host-sized path):
 //   (1) each workgroup sweeps its own particle range [r0, r1) for the
 //       minimum of t + dt and how many particles reach it -> barrier;
 //   (2) every workgroup reads the G results and forms the block time T,
@@ -1442,6 +1431,8 @@ __global__ __launch_bounds__(TPB) void step_loop_kernel(
 // -> 14.9, 2048 15.5 -> 13.4, 4096 18.4 -> 17.2; at 1000 bodies reading the
 // next times takes 0.9 us, decision, list and evaluation 6.7, corrector 2.6,
 // the barriers 2.2 and 0.9.
+// Its body takes all 256 vector registers and spills into the accumulation
+// registers, one wave per SIMD: there is one workgroup on a compute unit anyway.
 // SMALL_N: the largest system that the automatic mode gives to a loop (the
 // sweep of all next times, K reads per thread, grows with n: 0.8 us at 256
 // bodies, 2.1 at 4096).  SMALL_GRID: the predicted sources cost each unit
@@ -1449,8 +1440,6 @@ __global__ __launch_bounds__(TPB) void step_loop_kernel(
 // bodies 2430 us per call with 64, 2320 with 128; with 256 the barriers
 // cost more than that (2360; 1000 bodies 1590 -> 1870).
 // res as in step_loop_kernel.
-constexpr int SMALL_N = LOOP_AUTO_NMAX;
-constexpr int SMALL_GRID = 128;
 
 template <int PREC, bool EPS0>
 __global__ __launch_bounds__(TPB) void small_loop_kernel(
@@ -1830,9 +1819,9 @@ __global__ __launch_bounds__(TPB) void recap_kernel(State st, int64_t n, double 
 }
 
 // ------------------------------------------------------------- energy
-// per-workgroup partial sums of E_kin, sum_i m_i phi_i (phi_i over j > i,
-// so each pair once, its `split` parts added in order), L; then one wave per
-// quantity adds the partials in a fixed order
+// per-workgroup partial sums of E_kin, sum_i m_i phi_i (phi_i over the
+// particle's half-window, so each pair once, its `split` parts added in order),
+// L; then one wave per quantity adds the partials in a fixed order
 __device__ __forceinline__ double wave_sum(double v)
 {
 #pragma unroll
@@ -1999,11 +1988,10 @@ hipError_t launch_pack_arrays(const Ctx &c, const double *mass, const double *po
     return hipGetLastError();
 }
 
-hipError_t launch_pack(const Ctx &c, const double *T_cluster, int own_time,
-                       const int32_t *cluster_of, hipStream_t s)
+hipError_t launch_pack(const Ctx &c, hipStream_t s)
 {
     hipLaunchKernelGGL(pack_kernel, dim3(nblk(c.n)), dim3(TPB), 0, s, c.st, c.jm, c.jp, c.jd,
-                       (int)c.cfg.precision, c.n, T_cluster, cluster_of, own_time);
+                       (int)c.cfg.precision, c.n);
     return hipGetLastError();
 }
 

@@ -78,9 +78,6 @@ struct ForceWork {
     uint32_t *err;
 };
 
-// Launch shape of the evaluation: lanes per active particle, waves per
-// workgroup, split-source factor, active particles per lane group (1 or 2;
-// 2 only with lpi <= 4).
 // Work split of the ensemble loop (independent clusters in one persistent
 // launch): group g holds the size[g] consecutive workgroups from first[g]
 // and integrates the clusters cl[cl_off[g] .. cl_off[g+1]) one after
@@ -96,6 +93,9 @@ struct EnsPlan {
     const int64_t *part_cap;   // [ng]
 };
 
+// Launch shape of the evaluation: lanes per active particle, waves per
+// workgroup, split-source factor, active particles per lane group (1 or 2;
+// 2 only with lpi <= 4).
 struct Launch {
     int lpi = 0, waves = 0, split = 0, ipt = 1;
 };
@@ -162,8 +162,8 @@ hipError_t launch_startup(Ctx &c, const ForceWork &w, const StartupShape &sh, in
                           hipStream_t s);
 
 // integrate.hip
-hipError_t launch_pack(const Ctx &c, const double *T_cluster, int own_time,
-                       const int32_t *cluster_of, hipStream_t s);
+// records of the stored state, every particle at its own time
+hipError_t launch_pack(const Ctx &c, hipStream_t s);
 // records of c.n particles from caller arrays (c.jm / c.jp / c.jd per the
 // precision)
 hipError_t launch_pack_arrays(const Ctx &c, const double *mass, const double *pos,
@@ -241,8 +241,11 @@ enum : int { LVL_TPREV = LVL_N, LVL_BAD = LVL_N + 1, LVL_POS = LVL_N + 2, LVL_NA
 // Device-resident block-step loop: why it stopped, and the largest grid.
 enum : int { LOOP_DONE = 1, LOOP_BIG = 2, LOOP_ERR = 3 };
 constexpr int LOOP_GMAX = 1024;
-constexpr int LOOP_GRID = 64;            // workgroups the loop uses
-constexpr int64_t LOOP_AUTO_NMAX = 4096; // automatic mode: systems up to this size
+// Automatic mode: systems up to LOOP_AUTO_NMAX.  These (and no others) run in
+// small_loop_kernel, on SMALL_GRID workgroups; larger ones, which only a limit
+// set by the caller gives to a loop, in step_loop_kernel on LOOP_GRID.
+constexpr int64_t LOOP_AUTO_NMAX = 4096;
+constexpr int SMALL_N = LOOP_AUTO_NMAX, SMALL_GRID = 128, LOOP_GRID = 64;
 constexpr int64_t LOOP_BAR_WORDS = 32 * LOOP_GMAX;         // barrier lines (128 B each)
 // largest group of the ensemble loop (a barrier's cost grows with the
 // group's size: beyond 256 workgroups it outweighs the extra lanes)
@@ -327,7 +330,7 @@ struct Ctx {
     // not yet planned, 0 unavailable), and its result counters
     EnsPlan ens{};
     int32_t *d_ens_i32 = nullptr;        // grp_of, first, size, cl_off, cl
-    int64_t *d_ens_i64 = nullptr;        // part_off, part_cap, seg
+    int64_t *d_ens_i64 = nullptr;        // part_off, part_cap
     int ens_grid = -1;
     unsigned long long *d_ens_res = nullptr;   // [4]
     uint32_t *d_loop_bar = nullptr;      // [2 LOOP_BAR_WORDS] barrier words, then the ensemble
