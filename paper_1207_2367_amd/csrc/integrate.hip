@@ -1864,14 +1864,23 @@ __global__ __launch_bounds__(TPB) void energy_partial(State st, int64_t n, const
 __global__ __launch_bounds__(320) void energy_final(const double *red, int64_t nblk,
                                                     double *out)
 {
+    // 16 partial sums per lane: loads in flight together, and chains of a
+    // sixteenth of the length (2^20 bodies: 4 terms each, not 64)
+    constexpr int U = 16;
     const int r = threadIdx.x >> 6;
-    double v = 0.0;
-#pragma unroll 8
-    for (int64_t b = threadIdx.x & 63; b < nblk; b += 64)
-        v += red[b * 5 + r];
-    v = wave_sum(v);
+    double v[U] = {};
+    for (int64_t b = threadIdx.x & 63; b < nblk; b += 64 * U)
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            v[u] += b + 64 * u < nblk ? red[(b + 64 * u) * 5 + r] : 0.0;
+#pragma unroll
+    for (int m = U / 2; m >= 1; m >>= 1)
+#pragma unroll
+        for (int u = 0; u < m; ++u)
+            v[u] += v[u + m];
+    const double s = wave_sum(v[0]);
     if ((threadIdx.x & 63) == 0)
-        out[r] = v;
+        out[r] = s;
 }
 
 // ------------------------------------------------------------ utilities
