@@ -371,7 +371,9 @@ def summarize_profile(d):
         per = {}
         for r in rows:
             name = r["Kernel_Name"]
-            if not ("force_kernel" in name or "copy" in name.lower() or "reduce_split" in name):
+            # (the runtime's copies: the library has a state_copy_kernel of its own)
+            copy = "copy" in name.lower() and "nb::" not in name
+            if not ("force_kernel" in name or copy or "reduce_split" in name):
                 continue
             key = (int(r["Dispatch_Id"]),
                    name.replace("(anonymous namespace)::", "").split("(")[0][:70], r["Grid_Size"])
